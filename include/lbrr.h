@@ -52,6 +52,10 @@
  *                               moment-storage step, n >= 1 (read every step)
  *      LBRR_CLOSURE_WPR=1|2     waves per row of the fused closure step with
  *                               FP32 or FP16 storage (read every step)
+ *      LBRR_PAIR_LZ=n           z-planes per block of the launches that take two
+ *                               population steps, n >= 1, 0 for single steps only
+ *                               (read by every lb_step call)
+ *      LBRR_PAIR_ROWS=n         rows per block of those launches, if built for n
  *      LBRR_STEP_BLOCKS_PER_CU=n  blocks of the population step per compute
  *                               unit, 1..8, 0 for no limit (read every step)
  */
@@ -137,7 +141,8 @@ int lb_init_fields(lb_handle h, const void* rho, const void* u, const void* pi1,
  * kernels (no allocation, memset or synchronisation), so it can be captured
  * in a HIP graph on the handle's stream.  Each step swaps the handle's two
  * state buffers: replays of a captured run keep the handle's bookkeeping
- * right only if n is even. */
+ * right only if n is even.  A call of four steps or more may take them two to a
+ * launch (an even number of such launches), with the bits of single steps. */
 int lb_step(lb_handle h, long long n);
 
 /* Resting no-slip walls (u = 0) on the first and last node of each axis in

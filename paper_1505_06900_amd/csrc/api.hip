@@ -89,6 +89,62 @@ int moment_lz(int nvalues, int q, int nx, int ny, int nz, size_t es) {
   return 6;
 }
 
+// Tile height and chunk length of the step pair (k_step_pair); lz = 0 where
+// lb_step takes single steps.
+//
+// A compute unit holds one block, a block's time grows with the planes it
+// rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are dealt
+// to the eight XCDs in turn, so the plan taken is the one with the smallest
+//   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
+// Measured (GLUPS, order 4, single steps -> pairs), cubes of side n:
+//            n = 256         320         200         128          64
+//   D3Q27 FP32 27.3 -> 44.1  27.0 -> 41.7  22.9 -> 33.1  26.4 -> 37.5  22.3 -> 30.9
+//   D3Q19 FP32 40.0 -> 61.5  39.1 -> 61.2  33.1 -> 49.3  38.0 -> 49.2  30.8 -> 35.3
+//   D3Q27 FP64 12.5 -> 21.6  11.7 -> 21.0  12.9 -> 17.9  13.0 -> 20.5  12.2 -> 16.5
+//   D3Q19 FP64 18.3 -> 33.0  17.2 -> 31.6  18.9 -> 25.7  18.6 -> 29.5  16.5 -> 23.7
+// Smaller boxes leave most compute units without a block, and the pair's march
+// along z is then longer than two single steps (D3Q27 FP32 48^3 13.7 -> 15.0, 36^3
+// 8.6 -> 8.0, 32^3 7.3 -> 5.9; D3Q19 FP32 48^3 18.2 -> 17.6, 24 x 24 x 330 20.3 -> 19.5):
+// pairs are taken where the state, weighted by the used share of a tile's 64
+// columns, has at least 6.5 MB.
+// LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
+struct PairPlan {
+  int rows = 0, lz = 0;
+};
+PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz) {
+  PairPlan p;
+  int forced_lz = -1, forced_rows = 0;
+  if (const char* e = std::getenv("LBRR_PAIR_LZ")) forced_lz = std::atoi(e);
+  if (const char* e = std::getenv("LBRR_PAIR_ROWS")) forced_rows = std::atoi(e);
+  const int64_t gx = (nx + 63) / 64;
+  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
+  if (forced_lz == 0 || (forced_lz < 0 && state < 6.5e6)) return p;
+  int cus = 256;
+  int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t slots = cus / 8 > 0 ? cus / 8 : 1;
+  int64_t cost = 0;
+  bool listed = false;
+  for (int i = 0; const int rows = ops.pair_rows(storage, i); ++i) listed = listed || rows == forced_rows;
+  for (int i = 0; const int rows = ops.pair_rows(storage, i); ++i) {
+    if (listed && rows != forced_rows) continue;
+    const int64_t gy = (ny + rows - 1) / rows;
+    for (int chunks = 1; chunks <= nz; ++chunks) {
+      const int lz = forced_lz > 0 ? forced_lz : (nz + chunks - 1) / chunks;
+      const int64_t g = gy * ((nz + lz - 1) / lz);
+      const int64_t rounds = (gx * ((g + 7) / 8) + slots - 1) / slots;
+      const int64_t c = rounds * (lz + 2) * (rows + 3);
+      if (p.lz == 0 || c < cost) {
+        p.rows = rows;
+        p.lz = lz;
+        cost = c;
+      }
+      if (forced_lz > 0) break;
+    }
+  }
+  return p;
+}
+
 // Extra bytes after each population plane (layouts 0 and 2).  Planes whose
 // size is a large power of two would otherwise start at addresses that map to
 // the same HBM channels; the default adds 4 KiB + 256 B when the plane is a
@@ -184,6 +240,7 @@ struct lb_ctx {
     a.rho0 = rho0;
     a.omega1 = 1.0 - 1.0 / tau;
     a.lz = moment() ? moment_lz(nvalues(), q(), nx, ny, nz, elem_size(storage)) : 1;
+    a.rows = 0;
     a.walls = moment() ? walls : 0;
     return a;
   }
@@ -474,8 +531,40 @@ int lb_step(lb_handle h, long long n) {
   if (h->closure_on && h->moment()) return fail(LB_ERR_UNSUPPORTED, "the learned closure needs population storage");
   if (h->walls && h->closure_on) return fail(LB_ERR_UNSUPPORTED, "walls and the learned closure exclude each other");
   const StepArgs a = h->args();
+  // Two steps in one launch where the population step has that form, always two
+  // such launches at a time: every call then swaps the state buffers as often,
+  // modulo 2, as single steps would (an even number of steps ends in the buffer
+  // it started from, which replays of a captured run rely on).
+  StepArgs ap = a;
+  ap.lz = 0;
+  if (n >= 4 && !h->moment() && !h->closure_on && !h->walls) {
+    const PairPlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz);
+    ap.rows = p.rows;
+    ap.lz = p.lz;
+  }
   for (long long k = 0; k < n; ++k) {
-    hipError_t e;
+    long long left = n - k;  // steps up to the end of the call or the next check
+    if (h->check_every > 0) {
+      const long long to_check = h->check_every - h->steps % h->check_every;
+      if (to_check < left) left = to_check;
+    }
+    hipError_t e = hipSuccess;
+    if (ap.lz > 0 && left >= 4) {
+      for (int j = 0; j < 2 && e == hipSuccess; ++j) {
+        e = h->ops->step_pair(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], ap, h->stream);
+        if (e == hipSuccess) {
+          h->cur ^= 1;
+          h->steps += 2;
+        }
+      }
+      if (e != hipSuccess) return hip_fail(e, "step kernel launch");
+      k += 3;
+      if (h->check_every > 0 && h->steps % h->check_every == 0) {
+        double t[5];
+        if (int r = totals(h, t)) return r;
+      }
+      continue;
+    }
     if (h->closure_on)
       e = lbrr::closure_step(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], a, h->cl_packed, h->cl_params,
                              h->cl_norm, h->stream);

@@ -57,102 +57,113 @@ struct Hydro {
 
 // ---- moments -------------------------------------------------------------
 
-// Tensor-product lattices: sums along x, then y, then z.  f is indexed by the
-// D3Q27 position (cx+1) + 3(cy+1) + 9(cz+1) restricted to the lattice.
-template <class L, class R>
-__device__ __forceinline__ Moments<R> moments_product(const R* f) {
-  constexpr int NZ = (L::D == 3) ? 3 : 1;
-  R X[3][3][3];  // X[a][cy][cz] = sum_cx cx^a f
-  sfor<0, NZ>([&](auto Z) {
-    sfor<0, 3>([&](auto Y) {
-      constexpr int base = 3 * Y + 9 * Z;
-      const R fm = f[base + 0], f0 = f[base + 1], fp = f[base + 2];
+// Does the lattice carry velocity (cx, cy, cz)?
+template <class L>
+constexpr bool has_velocity(int cx, int cy, int cz) {
+  if (L::D == 2 && cz != 0) return false;
+  if (!L::kProduct && cx != 0 && cy != 0 && cz != 0) return false;
+  return true;
+}
+
+// Lattice index of velocity (cx, cy, cz) (-1 if the lattice lacks it).
+template <class L>
+constexpr int velocity_index(int cx, int cy, int cz) {
+  for (int i = 0; i < L::Q; ++i)
+    if (L::cx(i) == cx && L::cy(i) == cy && L::cz(i) == cz) return i;
+  return -1;
+}
+
+// sum_{cx, cy} cx^a cy^b f of the populations with one c_z, a + b <= 2.
+template <class R>
+struct LayerSums {
+  R s00, s10, s01, s20, s11, s02;
+};
+
+// Sums of layer c_z = CZ along x, then y.  get(I) returns population I, I an
+// integral constant; velocities the lattice lacks are left out.
+template <class L, int CZ, class R, class G>
+__device__ __forceinline__ LayerSums<R> layer_sums(G&& get) {
+  R x0[3], x1[3], x2[3];  // per c_y: sum of f, cx f, cx^2 f
+  sfor<0, 3>([&](auto Y) {
+    constexpr int cy = int(Y) - 1;
+    constexpr bool sides = has_velocity<L>(1, cy, CZ), centre = has_velocity<L>(0, cy, CZ);
+    static_assert(centre && sides == has_velocity<L>(-1, cy, CZ), "the +-1 entries come in pairs around the centre");
+    const R f0 = get(std::integral_constant<int, velocity_index<L>(0, cy, CZ)>{});
+    if constexpr (sides) {
+      const R fm = get(std::integral_constant<int, velocity_index<L>(-1, cy, CZ)>{});
+      const R fp = get(std::integral_constant<int, velocity_index<L>(1, cy, CZ)>{});
       const R s = fp + fm;
-      X[0][Y][Z] = s + f0;
-      X[1][Y][Z] = fp - fm;
-      X[2][Y][Z] = s;
-    });
+      x0[Y] = s + f0;
+      x1[Y] = fp - fm;
+      x2[Y] = s;
+    } else {
+      x0[Y] = f0;
+    }
   });
-  R Yv[3][3][3];  // Yv[a][b][cz] = sum_{cx,cy} cx^a cy^b f, a + b <= 2
-  sfor<0, NZ>([&](auto Z) {
-    sfor<0, 3>([&](auto A) {
-      const R m = X[A][0][Z], z0 = X[A][1][Z], p = X[A][2][Z];
-      const R s = p + m;
-      Yv[A][0][Z] = s + z0;
-      if constexpr (A <= 1) Yv[A][1][Z] = p - m;
-      if constexpr (A == 0) Yv[A][2][Z] = s;
-    });
-  });
-  Moments<R> r;
-  if constexpr (L::D == 2) {
-    r.d0 = Yv[0][0][0];
-    r.jx = Yv[1][0][0];
-    r.jy = Yv[0][1][0];
-    r.jz = R(0);
-    r.pxx = Yv[2][0][0];
-    r.pyy = Yv[0][2][0];
-    r.pxy = Yv[1][1][0];
-    r.pzz = r.pxz = r.pyz = R(0);
+  LayerSums<R> r;
+  const R e = x0[2] + x0[0];
+  r.s00 = e + x0[1];
+  r.s01 = x0[2] - x0[0];
+  r.s02 = e;
+  if constexpr (has_velocity<L>(1, 1, CZ)) {
+    r.s10 = (x1[2] + x1[0]) + x1[1];
+    r.s11 = x1[2] - x1[0];
+    r.s20 = (x2[2] + x2[0]) + x2[1];
   } else {
-    auto zs = [&](int a, int b, R& m0, R& m1, R& m2, int need) {
-      const R m = Yv[a][b][0], z0 = Yv[a][b][1], p = Yv[a][b][2];
-      const R s = p + m;
-      m0 = s + z0;
-      if (need >= 1) m1 = p - m;
-      if (need >= 2) m2 = s;
-    };
-    R t0, t1, t2;
-    zs(0, 0, r.d0, r.jz, r.pzz, 2);
-    zs(1, 0, r.jx, r.pxz, t2, 1);
-    zs(0, 1, r.jy, r.pyz, t2, 1);
-    zs(2, 0, r.pxx, t1, t2, 0);
-    zs(0, 2, r.pyy, t1, t2, 0);
-    zs(1, 1, r.pxy, t1, t2, 0);
-    (void)t0;
+    r.s10 = x1[1];
+    r.s11 = R(0);
+    r.s20 = x2[1];
   }
   return r;
 }
 
-// Sum over the q velocities of cx^A cy^B cz^C f_i (zero terms dropped at compile time).
-template <class L, int A, int B, int C, class R>
-__device__ __forceinline__ R moment_direct(const R* f) {
-  R s = R(-0.0);  // -0 + x == x exactly, so the first add folds away
-  sfor<0, L::Q>([&](auto I) {
-    constexpr int p = (A == 0 ? 1 : (A == 1 ? L::cx(I) : L::cx(I) * L::cx(I))) *
-                      (B == 0 ? 1 : (B == 1 ? L::cy(I) : L::cy(I) * L::cy(I))) *
-                      (C == 0 ? 1 : (C == 1 ? L::cz(I) : L::cz(I) * L::cz(I)));
-    if constexpr (p == 1) s = s + f[I];
-    if constexpr (p == -1) s = s - f[I];
-  });
-  return s;
-}
-
+// Moments from the layer sums of c_z = -1, 0, +1 (3D).  Kernels that receive
+// the layers of a node one after the other form the same sums in the same
+// order as raw_moments, so they give the same bits.
 template <class L, class R>
-__device__ __forceinline__ Moments<R> moments_direct(const R* f) {
+__device__ __forceinline__ Moments<R> join_layers(const LayerSums<R>& m, const LayerSums<R>& z, const LayerSums<R>& p) {
   Moments<R> r;
-  r.d0 = moment_direct<L, 0, 0, 0>(f);
-  r.jx = moment_direct<L, 1, 0, 0>(f);
-  r.jy = moment_direct<L, 0, 1, 0>(f);
-  r.jz = moment_direct<L, 0, 0, 1>(f);
-  r.pxx = moment_direct<L, 2, 0, 0>(f);
-  r.pyy = moment_direct<L, 0, 2, 0>(f);
-  r.pzz = moment_direct<L, 0, 0, 2>(f);
-  r.pxy = moment_direct<L, 1, 1, 0>(f);
-  r.pxz = moment_direct<L, 1, 0, 1>(f);
-  r.pyz = moment_direct<L, 0, 1, 1>(f);
+  const R e = p.s00 + m.s00;
+  r.d0 = e + z.s00;
+  r.jz = p.s00 - m.s00;
+  r.pzz = e;
+  r.jx = (p.s10 + m.s10) + z.s10;
+  r.pxz = p.s10 - m.s10;
+  r.jy = (p.s01 + m.s01) + z.s01;
+  r.pyz = p.s01 - m.s01;
+  r.pxx = (p.s20 + m.s20) + z.s20;
+  r.pyy = (p.s02 + m.s02) + z.s02;
+  r.pxy = has_velocity<L>(1, 1, 1) ? (p.s11 + m.s11) + z.s11 : z.s11;
   return r;
 }
 
 // f holds the lattice's q populations in lattice order.
 template <class L, class R>
 __device__ __forceinline__ Moments<R> raw_moments(const R* f) {
-  if constexpr (L::kProduct) {
-    // product lattices keep the D3Q27 positions (D2Q9: cz = 0 plane, offset 0)
-    return moments_product<L, R>(f);
+  auto get = [&](auto I) { return f[int(I)]; };
+  const LayerSums<R> z = layer_sums<L, 0, R>(get);
+  if constexpr (L::D == 3) {
+    return join_layers<L>(layer_sums<L, -1, R>(get), z, layer_sums<L, 1, R>(get));
   } else {
-    return moments_direct<L, R>(f);
+    Moments<R> r;
+    r.d0 = z.s00;
+    r.jx = z.s10;
+    r.jy = z.s01;
+    r.jz = R(0);
+    r.pxx = z.s20;
+    r.pyy = z.s02;
+    r.pxy = z.s11;
+    r.pzz = r.pxz = r.pyz = R(0);
+    return r;
   }
 }
+
+// Fused multiply-adds, written out: every product of the collision that meets a
+// sum does so in one of these, and no other product feeds a sum.  A contraction
+// left to the compiler can depend on what else a kernel does with the operands;
+// written out, every kernel that collides a node gives the same bits.
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // 1/rho for rho = rho0 + drho rounded: the exact rounding error of the sum
 // (two-sum) corrects the reciprocal to first order.  Rounding rho to the
@@ -163,7 +174,7 @@ __device__ __forceinline__ R inv_density(R rho0, R drho, R rho) {
   const R bb = rho - rho0;
   const R err = (rho0 - (rho - bb)) + (drho - bb);
   const R inv = R(1) / rho;
-  return inv - inv * inv * err;
+  return fused(-(inv * inv), err, inv);
 }
 // FP32: the hardware reciprocal (within 1 ulp) and one Newton step
 // r (2 - rho r) in place of the IEEE division sequence; rho is near rho0, far
@@ -173,7 +184,7 @@ __device__ __forceinline__ float inv_density(float rho0, float drho, float rho) 
   const float err = (rho0 - (rho - bb)) + (drho - bb);
   float inv = __builtin_amdgcn_rcpf(rho);
   inv = __builtin_fmaf(inv, __builtin_fmaf(-rho, inv, 1.0f), inv);
-  return inv - inv * inv * err;
+  return fused(-(inv * inv), err, inv);
 }
 
 // rho, u and a1^(2) = Pi - rho cs2 I - rho u u, written with deviations:
@@ -189,15 +200,15 @@ __device__ __forceinline__ Hydro<R> hydro(const Moments<R>& m, R rho0) {
   h.jy = m.jy;
   h.ux = m.jx * inv;
   h.uy = m.jy * inv;
-  h.axx = m.pxx - m.d0 * cs2 - m.jx * h.ux;
-  h.ayy = m.pyy - m.d0 * cs2 - m.jy * h.uy;
-  h.axy = m.pxy - m.jx * h.uy;
+  h.axx = fused(-m.jx, h.ux, fused(-m.d0, cs2, m.pxx));
+  h.ayy = fused(-m.jy, h.uy, fused(-m.d0, cs2, m.pyy));
+  h.axy = fused(-m.jx, h.uy, m.pxy);
   if constexpr (L::D == 3) {
     h.jz = m.jz;
     h.uz = m.jz * inv;
-    h.azz = m.pzz - m.d0 * cs2 - m.jz * h.uz;
-    h.axz = m.pxz - m.jx * h.uz;
-    h.ayz = m.pyz - m.jy * h.uz;
+    h.azz = fused(-m.jz, h.uz, fused(-m.d0, cs2, m.pzz));
+    h.axz = fused(-m.jx, h.uz, m.pxz);
+    h.ayz = fused(-m.jy, h.uz, m.pyz);
   } else {
     h.jz = h.uz = h.azz = h.axz = h.ayz = R(0);
   }
@@ -235,31 +246,55 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
           } else if constexpr (n == 1) {
             C[a][b][c] = (a == 1) ? h.jx : ((b == 1) ? h.jy : h.jz);
           } else {
-            // a0: rho u^k, written as j_d times the remaining velocities
-            R e;
-            if constexpr (a > 0) e = h.jx * px[a - 1] * py[b] * pz[c];
-            else if constexpr (b > 0) e = h.jy * py[b - 1] * pz[c];
-            else e = h.jz * pz[c - 1];
-            // a1: pair sum of the recursion
-            R s = R(-0.0);
-            if constexpr (!L::kProduct && n == 4) {
-              // D3Q19: f1 stops at order 3 while f0 keeps order 4.  The population
-              // vector f1^(3) has, on the fourth-order polynomial H_aabb of D3Q19,
-              // the moment -a1_cc / 6 (c the axis with exponent 0): the weights
-              // couple H_aabb to H_cc only.  With that value in place of the
-              // recursion's a1^(4), the order-4 reconstruction below returns
-              // f0^(4) + omega1 f1^(3).  (An f1 at order 4 through the same
-              // projection makes the rest state grow for tau near 1/2.)
-              s = R(-1.0 / 6.0) * (a == 0 ? sxx : (b == 0 ? syy : szz));
+            // a0: rho u^k, written as j_d times the remaining velocities; a1: pair
+            // sum of the recursion
+            if constexpr (n == 2) {
+              if constexpr (a == 2) C[a][b][c] = fused(h.jx, h.ux, sxx);
+              else if constexpr (b == 2) C[a][b][c] = fused(h.jy, h.uy, syy);
+              else if constexpr (c == 2) C[a][b][c] = fused(h.jz, h.uz, szz);
+              else if constexpr (c == 0) C[a][b][c] = fused(h.jx, h.uy, sxy);
+              else if constexpr (b == 0) C[a][b][c] = fused(h.jx, h.uz, sxz);
+              else C[a][b][c] = fused(h.jy, h.uz, syz);
             } else {
-              if constexpr (a == 2) s = s + sxx * py[b] * pz[c];
-              if constexpr (b == 2) s = s + syy * px[a] * pz[c];
-              if constexpr (c == 2) s = s + szz * px[a] * py[b];
-              if constexpr (a > 0 && b > 0) s = s + R(a * b) * sxy * px[a - 1] * py[b - 1] * pz[c];
-              if constexpr (a > 0 && c > 0) s = s + R(a * c) * sxz * px[a - 1] * py[b] * pz[c - 1];
-              if constexpr (b > 0 && c > 0) s = s + R(b * c) * syz * px[a] * py[b - 1] * pz[c - 1];
+              R s;
+              if constexpr (!L::kProduct && n == 4) {
+                // D3Q19: f1 stops at order 3 while f0 keeps order 4.  The population
+                // vector f1^(3) has, on the fourth-order polynomial H_aabb of D3Q19,
+                // the moment -a1_cc / 6 (c the axis with exponent 0): the weights
+                // couple H_aabb to H_cc only.  With that value in place of the
+                // recursion's a1^(4), the order-4 reconstruction below returns
+                // f0^(4) + omega1 f1^(3).  (An f1 at order 4 through the same
+                // projection makes the rest state grow for tau near 1/2.)
+                s = R(-1.0 / 6.0) * (a == 0 ? sxx : (b == 0 ? syy : szz));
+              } else {
+                s = R(-0.0);
+                // s += v * (ux^i uy^j uz^k), the last velocity in the multiply-add
+                auto term = [&](R v, auto I, auto J, auto K) __attribute__((always_inline)) {
+                  constexpr int i = I, j = J, k = K;
+                  static_assert(i + j + k >= 1, "a velocity factor per term");
+                  if constexpr (k > 0) s = fused(v * px[i] * py[j], pz[k], s);
+                  else if constexpr (j > 0) s = fused(v * px[i], py[j], s);
+                  else s = fused(v, px[i], s);
+                };
+                using std::integral_constant;
+                if constexpr (a == 2) term(sxx, integral_constant<int, 0>{}, B, Cc);
+                if constexpr (b == 2) term(syy, A, integral_constant<int, 0>{}, Cc);
+                if constexpr (c == 2) term(szz, A, B, integral_constant<int, 0>{});
+                if constexpr (a > 0 && b > 0)
+                  term(R(a * b) * sxy, integral_constant<int, a - 1>{}, integral_constant<int, b - 1>{}, Cc);
+                if constexpr (a > 0 && c > 0)
+                  term(R(a * c) * sxz, integral_constant<int, a - 1>{}, B, integral_constant<int, c - 1>{});
+                if constexpr (b > 0 && c > 0)
+                  term(R(b * c) * syz, A, integral_constant<int, b - 1>{}, integral_constant<int, c - 1>{});
+              }
+              // + rho u^k, the last velocity in the multiply-add
+              const R e = a > 0 ? h.jx * px[a > 0 ? a - 1 : 0] : h.jy;
+              constexpr int eb = a > 0 ? b : b - 1;
+              if constexpr (c > 0) s = fused(e * py[eb], pz[c], s);
+              else if constexpr (eb > 0) s = fused(e, py[eb], s);
+              else s = fused(h.jx, px[a - 1], s);
+              C[a][b][c] = s;
             }
-            C[a][b][c] = e + s;
           }
         }
       });
@@ -274,11 +309,6 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
 // w = (1/6, 2/3, 1/6) and n_a = (1, 1/3, 2/9):
 //   g(0) = 2/3 C0 - C2,  g(+-1) = 1/6 C0 +- 1/2 C1 + 1/2 C2.
 // Plain (D3Q19, after the Gram solve): g(0) = C0 - C2/3, g(+-1) = C0 +- C1 + 2/3 C2.
-// Every multiply-add of the transform is an explicit fused multiply-add, so
-// the bits of each output do not depend on which other outputs the caller
-// uses (a contraction left to the compiler can change with that).
-__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // The collision conserves mass and momentum (Sec. 2), and the weighted form
 // keeps that in any precision: g(0) is formed first and the outer values share
@@ -292,7 +322,7 @@ template <bool Weighted, bool Has1, bool Has2, class R>
 __device__ __forceinline__ void axis3(R c0, R c1, R c2, R& gm, R& g0, R& gp) {
   if constexpr (Weighted) {
     g0 = Has2 ? fused(R(2.0 / 3.0), c0, -c2) : R(2.0 / 3.0) * c0;
-    const R t = R(0.5) * (c0 - g0);
+    const R t = R(0.5) * (Has2 ? c0 - g0 : fused(R(-2.0 / 3.0), c0, c0));
     if constexpr (Has1) {
       gm = fused(R(-0.5), c1, t);
       gp = fused(R(0.5), c1, t);
@@ -454,14 +484,6 @@ static_assert(GramBlock19::block_ok(), "the order-4 D3Q19 Gram block has the axi
 // c_z = +-1 layers enter the z step and only layer c_z = 0 is changed after
 // it.  A layer-selected rebuild (ZSel = +-1) therefore computes both c_z = +-1
 // layers and gets the same bits for them as a full one.
-// Lattice index of velocity (cx, cy, cz) (-1 if the lattice lacks it).
-template <class L>
-constexpr int velocity_index(int cx, int cy, int cz) {
-  for (int i = 0; i < L::Q; ++i)
-    if (L::cx(i) == cx && L::cy(i) == cy && L::cz(i) == cz) return i;
-  return -1;
-}
-
 template <class L, class R>
 __device__ __forceinline__ void conserve_layers(const R (&C)[3][3][3], R* out) {
   constexpr int zp = velocity_index<L>(0, 0, 1), zm = velocity_index<L>(0, 0, -1);
@@ -543,6 +565,7 @@ __device__ __forceinline__ void reconstruct(R (&C)[3][3][3], R* out) {
             if constexpr (g != 0.0) s = fused(R(g), C[a2][b2][c2], s);
           }
         });
+        asm("" : "+v"(s));  // a sum of one term is a product: rounded before the transforms add it
         B[a][b][c] = s;
       }
     });

@@ -42,6 +42,22 @@ __device__ __forceinline__ int64_t node_offset(const StepArgs& a, uint32_t n) {
   return int64_t(z) * a.sz + int64_t(y) * a.sy + x;
 }
 
+// Element at a byte offset from a base pointer.
+template <class S>
+__device__ __forceinline__ S at_offset(const S* base, uint32_t off) {
+  return *reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + off);
+}
+template <class S>
+__device__ __forceinline__ S* ptr_at_offset(S* base, uint32_t off) {
+  return reinterpret_cast<S*>(reinterpret_cast<char*>(base) + off);
+}
+
+// v mod n, n > 0 (periodic index along an axis).
+__device__ __forceinline__ int wrap_axis(int v, int n) {
+  v %= n;
+  return v < 0 ? v + n : v;
+}
+
 // Block barrier for an LDS exchange: waits for the LDS accesses of every wave
 // but leaves global loads and stores in flight (for kernels whose threads
 // share nothing through global memory within a launch), so a prefetch
@@ -186,11 +202,11 @@ __global__ void __launch_bounds__(256) k_step_walls(const S* __restrict__ src, S
     h.drho = drho;
     h.rho = R(a.rho0) + drho;
     h.ux = h.uy = h.uz = h.jx = h.jy = h.jz = R(0);
-    h.axx = m.pxx - drho * cs2;
-    h.ayy = m.pyy - drho * cs2;
+    h.axx = fused(-drho, cs2, m.pxx);
+    h.ayy = fused(-drho, cs2, m.pyy);
     h.axy = m.pxy;
     if constexpr (L::D == 3) {
-      h.azz = m.pzz - drho * cs2;
+      h.azz = fused(-drho, cs2, m.pzz);
       h.axz = m.pxz;
       h.ayz = m.pyz;
     } else {

@@ -122,14 +122,6 @@ __device__ __forceinline__ void clear(Moments<R>& s) {
   s.d0 = s.jx = s.jy = s.jz = s.pxx = s.pyy = s.pzz = s.pxy = s.pxz = s.pyz = R(0);
 }
 
-// Does the lattice carry velocity (cx, cy, cz)?
-template <class L>
-constexpr bool has_velocity(int cx, int cy, int cz) {
-  if (L::D == 2 && cz != 0) return false;
-  if (!L::kProduct && cx != 0 && cy != 0 && cz != 0) return false;
-  return true;
-}
-
 // Add the populations of the layer c_z = CZ that arrive at inner node (tx, ty)
 // to its moment sums s: population (cx, cy, CZ) comes from patch node
 // (tx - cx, ty - cy).  Sums along x, then y, then the c_z factors.
@@ -336,21 +328,6 @@ __device__ __forceinline__ void finalize_walls(const Moments<R>& s, int sx, int 
   }
 }
 
-// Element at a byte offset from a base pointer.
-template <class S>
-__device__ __forceinline__ S at_offset(const S* base, uint32_t off) {
-  return *reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + off);
-}
-template <class S>
-__device__ __forceinline__ S* ptr_at_offset(S* base, uint32_t off) {
-  return reinterpret_cast<S*>(reinterpret_cast<char*>(base) + off);
-}
-
-__device__ __forceinline__ int wrap(int v, int n) {
-  v %= n;
-  return v < 0 ? v + n : v;
-}
-
 // One step of the moment-state update (see the file comment).
 template <class L, int N, class S, int TY, int MX, bool W>
 __global__ void __launch_bounds__(MX * TY) k_mstep(const S* __restrict__ src, S* __restrict__ dst, StepArgs a) {
@@ -365,7 +342,7 @@ __global__ void __launch_bounds__(MX * TY) k_mstep(const S* __restrict__ src, S*
   const int bxi = t % gx, byi = (t / gx) % gy, bz = t / (gx * gy);
   const int x0 = bxi * (MX - 2), y0 = byi * (TY - 2);
   // the patch node this thread rebuilds, and the node it updates if inner
-  const int px = wrap(x0 - 1 + tx, a.nx), py = wrap(y0 - 1 + ty, a.ny);
+  const int px = wrap_axis(x0 - 1 + tx, a.nx), py = wrap_axis(y0 - 1 + ty, a.ny);
   const bool inner = tx >= 1 && tx <= MX - 2 && ty >= 1 && ty <= TY - 2 && x0 + tx - 1 < a.nx && y0 + ty - 1 < a.ny;
   // Byte offsets of the node within its plane of one field (32 bits: the host
   // checks that a plane fits); the plane and field bases are block-uniform, so
@@ -451,15 +428,15 @@ __global__ void __launch_bounds__(MX * TY) k_mstep(const S* __restrict__ src, S*
     const int n = z1 - z0;
     Moments<R> T[3];  // sums of targets j = k, k - 1, k - 2 (mod 3) at plane k
     R B[3][NM];       // moments of planes k, k + 1, k + 2 (mod 3)
-    load(wrap(z0 - 1, a.nz), B[0]);
-    load(wrap(z0, a.nz), B[1]);
+    load(wrap_axis(z0 - 1, a.nz), B[0]);
+    load(wrap_axis(z0, a.nz), B[1]);
     R out[NM];  // moments of target k - 3, stored during plane k
     // E = 2: plane inside the chunk; +1: plane 0; -1: plane n + 1.  PH = k mod 3.
     auto iteration = [&](int k, auto PHS, auto ES) __attribute__((always_inline)) {
       constexpr int PH = decltype(PHS)::value, E = decltype(ES)::value;
       constexpr int P1 = (PH + 2) % 3, P2 = (PH + 1) % 3;  // (k - 1) mod 3, (k - 2) mod 3
       const int pz = z0 - 1 + k;
-      if (k + kPrefetch <= n + 1) load(wrap(pz + kPrefetch, a.nz), B[P1]);  // buffer (k + 2) mod 3
+      if (k + kPrefetch <= n + 1) load(wrap_axis(pz + kPrefetch, a.nz), B[P1]);  // buffer (k + 2) mod 3
       if (inner && k >= 3) put(z0 + k - 3, out);
       rebuild(B[PH], ES);
       lds_barrier();
@@ -549,9 +526,9 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_mstep_t(const S* __restrict__
     writes = lane < 2 * RW;
     r = left ? lane : (writes ? lane - RW : 0);
     col = left ? 0 : width + 1;
-    px = wrap(left ? x0 - 1 : x0 + width, a.nx);
+    px = wrap_axis(left ? x0 - 1 : x0 + width, a.nx);
   }
-  const int py = wrap(y0 - 1 + r, a.ny);
+  const int py = wrap_axis(y0 - 1 + r, a.ny);
   // the node this thread updates, if inner: (x0 + lane, y0 + r - 1), LDS (lane + 1, r)
   const bool inner = wave < RW && r >= 1 && r <= TY && lane < width && y0 + r - 1 < a.ny;
   const int tc = lane + 1;
@@ -627,8 +604,8 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_mstep_t(const S* __restrict__
     const int n = z1 - z0;
     Moments<R> T[3];
     R B[3][NM];
-    load(wrap(z0 - 1, a.nz), B[0]);
-    load(wrap(z0, a.nz), B[1]);
+    load(wrap_axis(z0 - 1, a.nz), B[0]);
+    load(wrap_axis(z0, a.nz), B[1]);
     // a completed target is stored at once (with 1024 threads a block has 128
     // VGPRs per lane, and holding it for the next iteration spilled)
     auto complete = [&](const Moments<R>& sums, int target) __attribute__((always_inline)) {
@@ -640,7 +617,7 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_mstep_t(const S* __restrict__
       constexpr int PH = decltype(PHS)::value, E = decltype(ES)::value;
       constexpr int P1 = (PH + 2) % 3, P2 = (PH + 1) % 3;
       const int pz = z0 - 1 + k;
-      if (k + kPrefetch <= n + 1) load(wrap(pz + kPrefetch, a.nz), B[P1]);
+      if (k + kPrefetch <= n + 1) load(wrap_axis(pz + kPrefetch, a.nz), B[P1]);
       rebuild(B[PH], ES);
       lds_barrier();
       if (inner) {
@@ -699,7 +676,7 @@ __global__ void __launch_bounds__(BX) k_mstep2(const S* __restrict__ src, S* __r
   __shared__ R pop[L::Q][BX];
   const int tx = threadIdx.x;
   const int x0 = blockIdx.x * (BX - 2);
-  const int px = wrap(x0 - 1 + tx, a.nx);
+  const int px = wrap_axis(x0 - 1 + tx, a.nx);
   const bool inner = tx >= 1 && tx <= BX - 2 && x0 + tx - 1 < a.nx;
   const int xo = x0 + tx - 1;
   const R rho0 = R(a.rho0), om = R(a.omega1);
@@ -724,14 +701,14 @@ __global__ void __launch_bounds__(BX) k_mstep2(const S* __restrict__ src, S* __r
   const int n = y1 - y0;
   Moments<R> T[3];
   R B[3][NM];
-  load(wrap(y0 - 1, a.ny), B[0]);
-  load(wrap(y0, a.ny), B[1]);
+  load(wrap_axis(y0 - 1, a.ny), B[0]);
+  load(wrap_axis(y0, a.ny), B[1]);
   R out[NM];  // moments of target k - 3, stored during row k
   auto iteration = [&](int k, auto PHS) __attribute__((always_inline)) {
     constexpr int PH = decltype(PHS)::value;
     constexpr int P1 = (PH + 2) % 3, P2 = (PH + 1) % 3;  // (k - 1) mod 3, (k - 2) mod 3
     const int py = y0 - 1 + k;
-    if (k + kPrefetch <= n + 1) load(wrap(py + kPrefetch, a.ny), B[P1]);  // buffer (k + 2) mod 3
+    if (k + kPrefetch <= n + 1) load(wrap_axis(py + kPrefetch, a.ny), B[P1]);  // buffer (k + 2) mod 3
     if (inner && k >= 3) put(y0 + k - 3, out);
     {
       const Hydro<R> h = state_hydro<L, R>(B[PH], rho0);

@@ -44,6 +44,12 @@ hipError_t step_walls_by_order(int order, const void* src, void* dst, const Step
   return hipErrorInvalidValue;
 }
 
+// Instantiated in the lattice's pair translation unit (kernels_pair_*.hip).
+template <class L, class S>
+hipError_t step_pair_by_order(int order, const void* src, void* dst, const StepArgs& a, hipStream_t s);
+template <class L>
+int pair_rows_of(int storage, int i);
+
 template <class L>
 struct OpsImpl {
   static hipError_t step(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s) {
@@ -55,6 +61,19 @@ struct OpsImpl {
       case 4: return mstep_by_order<L, float>(order, src, dst, a, s);
     }
     return hipErrorInvalidValue;
+  }
+  static hipError_t step_pair(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s) {
+    if constexpr (L::D == 3) {
+      switch (storage) {
+        case 0: return step_pair_by_order<L, double>(order, src, dst, a, s);
+        case 1: return step_pair_by_order<L, float>(order, src, dst, a, s);
+      }
+    }
+    return hipErrorInvalidValue;
+  }
+  static int pair_rows(int storage, int i) {
+    if constexpr (L::D == 3) return pair_rows_of<L>(storage, i);
+    return 0;
   }
   static hipError_t init(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1,
                          void* dst, const StepArgs& a, hipStream_t s) {
@@ -126,7 +145,7 @@ struct OpsImpl {
     return hipErrorInvalidValue;
   }
   static const LatticeOps& table() {
-    static const LatticeOps t = {L::Q, L::D, L::NMAX, &step, &init, &moments, &totals, &velocity, &repack,
+    static const LatticeOps t = {L::Q, L::D, L::NMAX, &step, &step_pair, &pair_rows, &init, &moments, &totals, &velocity, &repack,
                                  &mpopulations, &step_walls};
     return t;
   }

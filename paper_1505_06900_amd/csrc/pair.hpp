@@ -1,0 +1,227 @@
+// Two steps of the population update in one launch (FP32 and FP64 storage, 3D,
+// no walls).
+//
+// k_step moves the state through HBM once per step and is held by that
+// traffic.  Here a block pulls and collides the nodes of a tile and of its
+// one-node rim (first step) into LDS, and the tile's own nodes pull those
+// populations and collide again (second step), so the state is read and
+// written once for two steps.  Both collisions are the ones k_step runs, in
+// the same operations and order, on values of the storage type: two steps here
+// give the bits of two launches of k_step.
+//
+// D3Q27 order 4 FP32 at 256^3: 0.762 ms for two steps (44.1 GLUPS) against
+// 2 x 0.614 ms (27.3).  rocprofv3 at 8 rows and 16 planes a block: reads 1.34x the state
+// (rim rows and chunk edges), writes 1.00x, 4.24 GB at 5.1 TB/s; VALU busy 40%.
+// FP64: 1.56 ms against 2 x 1.34 ms, reads 1.61x, 6.1 TB/s.  So it is held by its
+// traffic again, at 0.54 of the traffic of two single steps.
+//
+// FP16 storage keeps single steps: they are near their VALU bound (D3Q19) or
+// would have to round the first step's populations to keep the bits.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "kernels.hpp"
+
+namespace lbrr {
+
+// Tile of a block: 64 columns (a row segment starting at a multiple of 64) by
+// TY rows, marching along z through a chunk of a.lz planes.  TY + 2 waves run
+// the first step on the tile's 64 columns of rows y0 - 1 .. y0 + TY (a wave per
+// row) and one more wave on the two columns beside the tile.  The first step's
+// populations on plane p with c_z = +1, 0, -1 arrive on planes p + 1, p, p - 1:
+// an inner thread keeps the layer sums of the planes it is waiting for
+// (LayerSums, 6 values a layer) and collides plane p - 1 when the c_z = -1
+// layer of plane p is there.  The pull of the next plane is issued as soon as
+// the moments of the present one are formed, and is in flight through both
+// collisions.
+template <class L, int N, class S, int TY>
+__global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict__ src, S* __restrict__ dst,
+                                                             StepArgs a) {
+  static_assert(L::D == 3, "3D lattices");
+  static_assert(2 * (TY + 2) <= 64, "one wave holds both rim columns of every patch row");
+  using R = S;
+  constexpr int RW = TY + 2, MXL = 66;
+  __shared__ R pop[L::Q][RW][MXL];
+  const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  // Blocks reach the eight XCDs round-robin by id, and each XCD has its own
+  // L2: blocks b and b + 8 take x-neighbouring tiles of one tile row, so the rim
+  // columns a block reads are lines its XCD's L2 holds for the neighbour.  Tile
+  // rows past the last of a group of eight are empty.
+  const int gx = (a.nx + 63) / 64, gy = (a.ny + TY - 1) / TY, gz = (a.nz + a.lz - 1) / a.lz;
+  const int b = int(blockIdx.x);
+  const int bxi = (b / 8) % gx, g = (b / (8 * gx)) * 8 + b % 8;
+  if (g >= gy * gz) return;
+  const int byi = g % gy, bz = g / gy;
+  const int x0 = bxi * 64, y0 = byi * TY;
+  const int width = (a.nx - x0 < 64) ? a.nx - x0 : 64;
+  // the node of the first step: patch row r, LDS column col, lattice node (px, py)
+  int r, col, px;
+  bool writes;
+  if (wave < RW) {
+    r = wave;
+    writes = lane < width;
+    col = lane + 1;
+    px = x0 + (writes ? lane : 0);
+  } else {
+    const bool left = lane < RW;
+    writes = lane < 2 * RW;
+    r = left ? lane : (writes ? lane - RW : 0);
+    col = left ? 0 : width + 1;
+    px = wrap_axis(left ? x0 - 1 : x0 + width, a.nx);
+  }
+  const int py = wrap_axis(y0 - 1 + r, a.ny);
+  // the node of the second step: (x0 + lane, y0 + r - 1), LDS column lane + 1
+  const bool inner = wave < RW && r >= 1 && r <= TY && lane < width && y0 + r - 1 < a.ny;
+  // Byte offsets of the nodes populations come from, within a plane of one
+  // population (the host checks that it fits 32 bits); plane and population
+  // bases are block-uniform.
+  const int xs[3] = {px == a.nx - 1 ? 0 : px + 1, px, px == 0 ? a.nx - 1 : px - 1};
+  const int ys[3] = {py == a.ny - 1 ? 0 : py + 1, py, py == 0 ? a.ny - 1 : py - 1};
+  uint32_t off[3][3];  // [c_y + 1][c_x + 1]
+  sfor<0, 3>([&](auto Y) {
+    sfor<0, 3>([&](auto X) { off[Y][X] = uint32_t((int64_t(ys[Y]) * a.sy + xs[X]) * int64_t(sizeof(S))); });
+  });
+  const uint32_t off_out =
+      inner ? uint32_t((int64_t(y0 + r - 1) * a.sy + (x0 + lane)) * int64_t(sizeof(S))) : 0u;
+  const R rho0 = R(a.rho0), om = R(a.omega1);
+
+  auto pull = [&](int z, R (&f)[L::Q]) __attribute__((always_inline)) {
+    const int zs[3] = {z == a.nz - 1 ? 0 : z + 1, z, z == 0 ? a.nz - 1 : z - 1};
+    // An empty asm hides that the offsets are the same in every plane, so that
+    // each access keeps the form scalar base + 32-bit lane offset.
+#pragma unroll
+    for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(off[i / 3][i % 3]));
+    sfor<0, L::Q>([&](auto I) {
+      constexpr int cx = L::cx(I), cy = L::cy(I), cz = L::cz(I);
+      f[I] = at_offset(src + int64_t(I) * a.si + int64_t(zs[cz + 1]) * a.sz, off[cy + 1][cx + 1]);
+    });
+  };
+
+  const int z0 = bz * a.lz;
+  const int z1 = (z0 + a.lz < a.nz) ? z0 + a.lz : a.nz;
+  const int n = z1 - z0;
+  // First-step planes z0 - 1 .. z1 (plane z0 - 1 + k, k = 0 .. n + 1), targets
+  // z0 .. z1 - 1: plane k brings layer c_z = +1 to target k, 0 to target k - 1,
+  // -1 to target k - 2, which is then complete.
+  struct {  // a struct: a plain array carried around the loop ends in one 32-register tuple, copied whole
+    R v[L::Q];
+  } f;
+  LayerSums<R> up1, up2, mid2;  // c_z = +1 layers of targets k - 1 and k - 2, c_z = 0 layer of target k - 2
+  // First step of plane k into LDS; ZS selects all populations (2) or those
+  // with c_z = ZS.  Next: pull plane k + 1 once the moments of plane k are formed.
+  auto first = [&](int k, auto ZS, auto Next) __attribute__((always_inline)) {
+    constexpr int Z = decltype(ZS)::value;
+    Moments<R> m = raw_moments<L, R>(f.v);
+    if constexpr (decltype(Next)::value) {
+      // the moments are pinned here, so that the pull can take the registers of f
+      asm volatile("" : "+v"(m.d0), "+v"(m.jx), "+v"(m.jy), "+v"(m.jz), "+v"(m.pxx), "+v"(m.pyy), "+v"(m.pzz),
+                   "+v"(m.pxy), "+v"(m.pxz), "+v"(m.pyz));
+      pull(wrap_axis(z0 + k, a.nz), f.v);
+    }
+    const Hydro<R> h = hydro<L, R>(m, rho0);
+    R C[3][3][3], out[L::Q];
+    coefficients<L, N, R>(h, om, C);
+    reconstruct<L, N, R, Z>(C, out);
+    if (writes) {
+      sfor<0, L::Q>([&](auto I) {
+        if constexpr (Z == 2 || L::cz(I) == Z) pop[I][r][col] = out[I];
+      });
+    }
+  };
+  // population I arriving at the inner node
+  auto arrived = [&](auto I) { return pop[I][r - L::cy(I)][lane + 1 - L::cx(I)]; };
+  // second step of plane z from its layer sums
+  auto second = [&](int z, const LayerSums<R>& lo, const LayerSums<R>& mid, const LayerSums<R>& up)
+      __attribute__((always_inline)) {
+    const Hydro<R> h = hydro<L, R>(join_layers<L>(lo, mid, up), rho0);
+    R C[3][3][3], out[L::Q];
+    coefficients<L, N, R>(h, om, C);
+    reconstruct<L, N, R>(C, out);
+    S* d = dst + int64_t(z) * a.sz;
+    uint32_t o = off_out;
+    asm volatile("" : "+v"(o));
+    sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(out[I], ptr_at_offset(d + int64_t(I) * a.si, o)); });
+  };
+  using all = std::integral_constant<int, 2>;
+  using layer_m = std::integral_constant<int, -1>;
+  using layer_p = std::integral_constant<int, 1>;
+  pull(wrap_axis(z0 - 1, a.nz), f.v);
+  first(0, layer_p{}, std::true_type{});
+  lds_barrier();
+  if (inner) up1 = layer_sums<L, 1, R>(arrived);
+  lds_barrier();
+  for (int k = 1; k <= n; ++k) {
+    first(k, all{}, std::true_type{});
+    lds_barrier();
+    LayerSums<R> lo, mid, up;
+    if (inner) {
+      lo = layer_sums<L, -1, R>(arrived);
+      mid = layer_sums<L, 0, R>(arrived);
+      up = layer_sums<L, 1, R>(arrived);
+    }
+    lds_barrier();
+    if (inner) {
+      if (k >= 2) second(z0 + k - 2, lo, mid2, up2);
+      up2 = up1;
+      mid2 = mid;
+      up1 = up;
+    }
+  }
+  first(n + 1, layer_m{}, std::false_type{});
+  lds_barrier();
+  if (inner) second(z1 - 1, layer_sums<L, -1, R>(arrived), mid2, up2);
+}
+
+// Tile heights the host chooses from (pair_plan in api.hip).  GLUPS at 256^3,
+// order 4, by rows: D3Q27 FP32 5 / 7 / 8 / 9 / 10 rows 40.4 / 38.7 / 43.6 / 40.6 / 31.9 (10 and
+// more rows spill: 128 VGPRs), D3Q19 FP32 5 / 8 / 9 / 11 / 13 rows 57.1 / 56.7 / 56.5 /
+// 59.4 / 60.6, D3Q27 FP64 3 / 4 / 5 rows 19.8 / 21.5 / 20.4, D3Q19 FP64 29.1 / 32.5 / 29.2 (6
+// rows spill).  The second height serves boxes whose rows the first divides badly.
+template <class L, class S>
+constexpr int pair_rows_option(int i) {
+  if (sizeof(S) == 8) return i == 0 ? 4 : (i == 1 ? 3 : 0);
+  if (L::Q == 19) return i == 0 ? 13 : (i == 1 ? 9 : 0);
+  return i == 0 ? 8 : (i == 1 ? 9 : 0);
+}
+
+template <class L, int N, class S, int TY>
+hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
+  if (a.lz < 1) return hipErrorInvalidValue;
+  const int64_t plane = (int64_t(a.ny - 1) * a.sy + a.nx) * int64_t(sizeof(S));
+  if (plane >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // 32-bit lane byte offsets
+  const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
+  const int64_t blocks = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
+  if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_step_pair<L, N, S, TY>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+                     static_cast<const S*>(src), static_cast<S*>(dst), a);
+  return hipGetLastError();
+}
+
+template <class L, int N, class S>
+hipError_t step_pair_by_rows(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
+  if (a.rows == pair_rows_option<L, S>(0)) return launch_step_pair<L, N, S, pair_rows_option<L, S>(0)>(src, dst, a, s);
+  if (a.rows == pair_rows_option<L, S>(1)) return launch_step_pair<L, N, S, pair_rows_option<L, S>(1)>(src, dst, a, s);
+  return hipErrorInvalidValue;
+}
+
+template <class L, class S>
+hipError_t step_pair_by_order(int order, const void* src, void* dst, const StepArgs& a, hipStream_t s) {
+  switch (order) {
+    case 2: return step_pair_by_rows<L, 2, S>(src, dst, a, s);
+    case 3: return step_pair_by_rows<L, 3, S>(src, dst, a, s);
+    case 4: return step_pair_by_rows<L, 4, S>(src, dst, a, s);
+    case 5: if constexpr (L::NMAX >= 5) return step_pair_by_rows<L, 5, S>(src, dst, a, s); break;
+    case 6: if constexpr (L::NMAX >= 6) return step_pair_by_rows<L, 6, S>(src, dst, a, s); break;
+  }
+  return hipErrorInvalidValue;
+}
+
+template <class L>
+int pair_rows_of(int storage, int i) {
+  return storage == 0 ? pair_rows_option<L, double>(i) : (storage == 1 ? pair_rows_option<L, float>(i) : 0);
+}
+
+}  // namespace lbrr

@@ -1,0 +1,57 @@
+"""Launches of two population steps against single steps, bit for bit.
+
+lb_step may take steps two to a launch (3D, FP64 and FP32 population storage, no walls); the
+single steps are held to the oracle elsewhere.  Boxes at the edges of the launch's tiles: one
+node, fewer rows or planes than a tile, rows of 64 +- 1 nodes, chunk lengths that leave one
+plane over, both tile heights; every order.  LBRR_PAIR_LZ=0 gives the single steps.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROWS = {("D3Q27", "fp32"): (8, 9), ("D3Q19", "fp32"): (13, 9), ("D3Q27", "fp64"): (4, 3), ("D3Q19", "fp64"): (4, 3)}
+SHAPES = [(1, 1, 1), (3, 2, 130), (7, 19, 65), (25, 37, 63), (20, 26, 64)]
+
+
+def _run(lbrr, torch, lattice, shape, order, storage, calls, check=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rho = 1.0 + 0.01 * torch.randn(shape, generator=g, device="cuda", dtype=torch.float64)
+    u = 0.03 * torch.randn((3,) + shape, generator=g, device="cuda", dtype=torch.float64)
+    sim = lbrr.Simulation(lattice, shape, 0.62, order, storage=storage)
+    sim.set_check_interval(check)
+    sim.init_fields(rho, u)
+    for n in calls:
+        sim.step(n)
+    out, steps = sim.get_populations(), sim.steps
+    sim.close()
+    return out, steps
+
+
+@pytest.mark.parametrize("lattice,order", [("D3Q27", n) for n in (2, 3, 4, 5, 6)] + [("D3Q19", n) for n in (2, 3, 4)])
+@pytest.mark.parametrize("storage", ["fp32", "fp64"])
+def test_pairs_equal_single_steps(lbrr, gpu, lattice, order, storage, monkeypatch):
+    for shape in SHAPES:
+        monkeypatch.setenv("LBRR_PAIR_LZ", "0")
+        want, steps = _run(lbrr, gpu, lattice, shape, order, storage, [9])
+        assert steps == 9
+        for rows in ROWS[lattice, storage]:
+            for lz in (1, 6, 24):
+                monkeypatch.setenv("LBRR_PAIR_LZ", str(lz))
+                monkeypatch.setenv("LBRR_PAIR_ROWS", str(rows))
+                got, steps = _run(lbrr, gpu, lattice, shape, order, storage, [9])
+                assert steps == 9
+                assert gpu.isfinite(got).all()
+                assert gpu.equal(got, want), (shape, rows, lz)
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp64"])
+def test_own_choice_splits_and_checks(lbrr, gpu, storage, monkeypatch):
+    """The library's own plan on a box it pairs: one call of 23 steps, calls of 1 to 8 steps, and
+    calls with a check interval that ends inside a pair all give the same state."""
+    shape = (40, 70, 100)
+    want, _ = _run(lbrr, gpu, "D3Q27", shape, 4, storage, [1] * 23)
+    for calls, check in (([23], 0), ([4, 5, 6, 8], 0), ([2, 3, 7, 11], 0), ([23], 5), ([9, 14], 1), ([23], 6)):
+        got, steps = _run(lbrr, gpu, "D3Q27", shape, 4, storage, calls, check)
+        assert steps == 23
+        assert gpu.equal(got, want), (calls, check)
