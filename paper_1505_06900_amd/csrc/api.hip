@@ -781,6 +781,61 @@ int workspace(size_t bytes, void** out) {
   return LB_OK;
 }
 
+// Scratch of one call, allocated and freed in stream order from a pool of the
+// device's own, so calls on any streams and threads have their own.  The pool
+// keeps at most kScratchKeep bytes between calls.  ptr stays NULL under stream
+// capture (an allocation has no place in the graph) and where the device has no
+// memory pools.
+constexpr uint64_t kScratchKeep = uint64_t(8) << 20;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDevices] = {};
+
+struct Scratch {
+  void* ptr = nullptr;
+  hipStream_t stream = nullptr;
+  Scratch() = default;
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  ~Scratch() {
+    if (ptr) (void)hipFreeAsync(ptr, stream);
+  }
+  int allocate(size_t bytes, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return LB_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return LB_OK;
+    int dev = 0, has = 0;
+    HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
+    if (dev < 0 || dev >= kMaxDevices) return LB_OK;
+    hipMemPool_t pool = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_pool_mu);
+      if (!g_pool[dev]) {
+        HIP_TRY(hipDeviceGetAttribute(&has, hipDeviceAttributeMemoryPoolsSupported, dev), "hipDeviceGetAttribute");
+        if (!has) return LB_OK;
+        hipMemPoolProps props{};
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        HIP_TRY(hipMemPoolCreate(&g_pool[dev], &props), "hipMemPoolCreate");
+        uint64_t keep = kScratchKeep;
+        HIP_TRY(hipMemPoolSetAttribute(g_pool[dev], hipMemPoolAttrReleaseThreshold, &keep), "hipMemPoolSetAttribute");
+      }
+      pool = g_pool[dev];
+    }
+    const hipError_t e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
+    if (e != hipSuccess) {
+      ptr = nullptr;
+      (void)hipGetLastError();
+      return fail(LB_ERR_OOM, "scratch of %zu bytes: %s", bytes, hipGetErrorString(e));
+    }
+    stream = s;
+    return LB_OK;
+  }
+};
+
 }  // namespace
 
 int lb_set_closure(lb_handle h, const float* params, const float* norm, int enable) {
@@ -845,11 +900,7 @@ int lb_mlp_forward(const float* params, const float* norm, const float* x, long 
   if (!params || !norm || (n > 0 && (!x || !y))) return fail(LB_ERR_INVALID_ARG, "NULL pointer");
   if (n < 0) return fail(LB_ERR_INVALID_ARG, "n must be >= 0");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  void* ws = nullptr;
-  if (int r = workspace(sizeof(uint16_t) * lbrr::kMlpNPacked, &ws)) return r;
-  uint16_t* packed = static_cast<uint16_t*>(ws);
-  hipError_t e = lbrr::mlp_pack(params, packed, s);
-  if (e == hipSuccess) e = lbrr::mlp_infer(x, n, packed, params, norm, y, s);
+  const hipError_t e = lbrr::mlp_infer(x, n, params, norm, y, s);
   if (e != hipSuccess) return hip_fail(e, "MLP forward");
   return LB_OK;
 }
@@ -877,7 +928,13 @@ int lb_mlp_gradient(const float* params, const float* norm, const float* x, cons
 int lb_column_stats(const float* x, long long n, int dim, float* mean, float* std, void* hip_stream) {
   if (!x || !mean || !std) return fail(LB_ERR_INVALID_ARG, "NULL pointer");
   if (n < 1 || dim < 1) return fail(LB_ERR_INVALID_ARG, "n and dim must be >= 1");
-  hipError_t e = lbrr::column_stats(x, n, dim, mean, std, static_cast<hipStream_t>(hip_stream));
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  Scratch part;
+  if (!lbrr::column_stats_direct(n, dim)) {
+    const size_t bytes = sizeof(double) * 2 * size_t(dim) * size_t(lbrr::column_stats_runs(n, dim));
+    if (int r = part.allocate(bytes, s)) return r;
+  }
+  const hipError_t e = lbrr::column_stats(x, n, dim, static_cast<double*>(part.ptr), mean, std, s);
   if (e != hipSuccess) return hip_fail(e, "column stats kernel");
   return LB_OK;
 }

@@ -151,27 +151,6 @@ __global__ void __launch_bounds__(256) k_features(const S* __restrict__ src, con
 }
 
 // ---------------------------------------------------------------------------
-// Per-block constants of the inference kernels, staged in LDS: biases b1 (64),
-// b2 (64), b3 (3, padded to 4), then x_mean (36), 1/x_std (36), y_mean (3), y_std (3).
-constexpr int kCB1 = 0, kCB2 = kCB1 + kH, kCB3 = kCB2 + kH, kCMean = kCB3 + 4, kCInv = kCMean + kIn,
-              kCYMean = kCInv + kIn, kCYStd = kCYMean + kOut, kNConst = kCYStd + kOut;
-// Per-wave activation region: 64 rows (one per sample) of kLdH BF16 values.
-constexpr int kRegion = 64 * kLdH;
-
-__device__ __forceinline__ void load_constants(const float* __restrict__ params, const float* __restrict__ norm,
-                                               float* c) {
-  for (int k = threadIdx.x; k < kNConst; k += blockDim.x) {
-    float v;
-    if (k < kCB2) v = params[kOffB1 + k];
-    else if (k < kCB3) v = params[kOffB2 + k - kCB2];
-    else if (k < kCMean) v = (k - kCB3 < kOut) ? params[kOffB3 + k - kCB3] : 0.0f;
-    else if (k < kCInv) v = norm[k - kCMean];
-    else if (k < kCYMean) v = 1.0f / norm[kIn + k - kCInv];
-    else v = norm[2 * kIn + k - kCYMean];
-    c[k] = v;
-  }
-}
-
 // Standardised BF16 features of one sample into its LDS row (kInP values,
 // inputs kIn .. kInP - 1 zero): (x - mean) * (1 / std).
 __device__ __forceinline__ void write_features(const float (&feat)[kIn], const float* mean, const float* inv,
@@ -184,88 +163,111 @@ __device__ __forceinline__ void write_features(const float (&feat)[kIn], const f
   for (int k4 = 0; k4 < kInP / 4; ++k4) xr[k4] = pack_bf16(v[4 * k4], v[4 * k4 + 1], v[4 * k4 + 2], v[4 * k4 + 3]);
 }
 
-// Forward pass of a group of 64 samples shared by NW waves; every thread of
-// the block calls it (barriers inside).  Wave `part` (0..NW-1) of the group
-// computes every NW-th output tile of each layer; wave 0 holds the samples
-// (sample s = its lane s): it writes their features and reads their outputs.
-// The products are computed transposed, features x samples (weights as the
-// matrix-core A operand), so a lane's result, four consecutive features of
-// one sample, goes to the sample's LDS row with one 8-byte write and is read
-// back as the next layer's operand with one 8-byte read.  feat: the lane's raw
-// features (wave 0); w: packed weights in LDS; r0, r1: the group's two
-// activation regions; c: constants.  The barriers wait for LDS only, so global
-// loads a caller issued before the call stay in flight through it.
-template <int NW>
-__device__ __forceinline__ void forward_group(const float (&feat)[kIn], int part, const uint16_t* w, uint16_t* r0,
-                                              uint16_t* r1, const float* c, float (&out)[kOut]) {
-  const int lane = threadIdx.x & 63, q = lane >> 4;
-  if (part == 0) {  // standardised BF16 features, row = sample (stride kLd1, inputs 36..47 zero)
-    write_features(feat, c + kCMean, c + kCInv, r0 + lane * kLd1);
-  }
-  lds_barrier();
-  // layer 1: H1 = gelu(W1 X + b1), 4 x 4 tiles (features j0, samples s0) -> r1
-#pragma unroll
-  for (int t = part; t < 16; t += NW) {
-    const int j0 = 16 * (t & 3), s0 = 16 * (t >> 2), j = j0 + 4 * q;
-    f32x4 acc = *reinterpret_cast<const f32x4*>(c + kCB1 + j);
-    acc = tile_kc<kInP>(w + kPW1, kLd1, r0, kLd1, j0, s0, acc);
-    *reinterpret_cast<bf16x4*>(r1 + (s0 + (lane & 15)) * kLdH + j) =
-        pack_bf16(gelu(acc[0]), gelu(acc[1]), gelu(acc[2]), gelu(acc[3]));
-  }
-  lds_barrier();
-  // layer 2: H2 = gelu(W2 H1 + b2) -> r0
-#pragma unroll
-  for (int t = part; t < 16; t += NW) {
-    const int j0 = 16 * (t & 3), s0 = 16 * (t >> 2), j = j0 + 4 * q;
-    f32x4 acc = *reinterpret_cast<const f32x4*>(c + kCB2 + j);
-    acc = tile_kc<kH>(w + kPW2, kLdH, r1, kLdH, j0, s0, acc);
-    *reinterpret_cast<bf16x4*>(r0 + (s0 + (lane & 15)) * kLdH + j) =
-        pack_bf16(gelu(acc[0]), gelu(acc[1]), gelu(acc[2]), gelu(acc[3]));
-  }
-  lds_barrier();
-  // layer 3: Y = W3 H2 + b3 (rows 0..2 of one 16-row tile), FP32 -> r1 as [64][4]
-  float* ys = reinterpret_cast<float*>(r1);
-#pragma unroll
-  for (int t = part; t < 4; t += NW) {
-    const int s0 = 16 * t;
-    f32x4 acc = {0, 0, 0, 0};
-    acc = tile_kc<kH>(w + kPW3, kLdH, r0, kLdH, 0, s0, acc);
-    if (q == 0) {
-#pragma unroll
-      for (int o = 0; o < kOut; ++o) ys[(s0 + lane) * 4 + o] = acc[o] + c[kCB3 + o];
-    }
-  }
-  lds_barrier();
-  if (part == 0) {
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) out[o] = ys[lane * 4 + o] * c[kCYStd + o] + c[kCYMean + o];
-  }
-  lds_barrier();
+// Four consecutive floats, 4-byte aligned: caller arrays (samples, parameters,
+// normalisation) may start at any float.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+__device__ __forceinline__ bf16x4 load4_bf16(const float* p) {
+  const f32x4 v = load4(p);
+  return pack_bf16(v[0], v[1], v[2], v[3]);
 }
 
-constexpr int kInferWaves = 2;
+constexpr int kInferWaves = 4, kInferBlocksPerCu = 2;
 
 // Batched inference: raw features (n x 36) -> de-normalised outputs (n x 3).
+//
+// A wave takes 16 samples at a time and keeps the whole network in registers,
+// the products transposed (weights as the matrix-core A operand, samples as B):
+// lane (q, l16) holds k = 16 j + 4 q .. + 3 of every operand chunk j, so it reads its
+// features of sample l16 as three 16-byte loads, and the four outputs 16 j + 4 q
+// .. + 3 that a layer leaves it are, after the activation, chunk j of the next
+// layer's operand as they stand: nothing passes through LDS and no barrier is
+// met.  The weights are rounded to BF16 as they are loaded, once per wave; waves
+// stride over the samples with the next 16 in flight.  Bound: the activations'
+// VALU work (128 a sample, about 50 us a million at full issue).  1 M samples a
+// call: 97 us with weights and activations in LDS and a packing launch before it,
+// 72 us so; 10000: 10.4 -> 6.3 us.  (Biases in LDS and three waves a SIMD in place
+// of two: 73 us.)
 __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float* __restrict__ x, int64_t n,
-                                                                const uint16_t* __restrict__ packed,
                                                                 const float* __restrict__ params,
                                                                 const float* __restrict__ norm, float* __restrict__ y) {
-  __shared__ __attribute__((aligned(16))) uint16_t w[kNPacked];
-  __shared__ __attribute__((aligned(16))) uint16_t reg[kInferWaves][2][kRegion];
-  __shared__ __attribute__((aligned(16))) float cst[kNConst];
-  load_weights<64 * kInferWaves>(packed, w);
-  load_constants(params, norm, cst);
-  const int wave = threadIdx.x >> 6;
-  const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t sc = s < n ? s : n - 1;  // every lane takes part in the matrix-core tiles
-  float feat[kIn];
+  const int lane = threadIdx.x & 63, q = lane >> 4, l16 = lane & 15;
+  const bool first = q == 0;
+  const int64_t tiles = (n + 15) / 16, waves = int64_t(gridDim.x) * kInferWaves;
+  int64_t tile = int64_t(blockIdx.x) * kInferWaves + (threadIdx.x >> 6);
+  if (tile >= tiles) return;
+  auto features = [&](int64_t t, f32x4 (&v)[3]) __attribute__((always_inline)) {
+    const int64_t s = t * 16 + l16;
+    const float* row = x + (s < n ? s : n - 1) * kIn + 4 * q;
+    v[0] = load4(row);
+    v[1] = load4(row + 16);
+    v[2] = first ? load4(row + 32) : f32x4{0, 0, 0, 0};  // inputs 36 .. 47 are zero
+  };
+  f32x4 v[3];
+  features(tile, v);
+  f32x4 mean[3], inv[3];
 #pragma unroll
-  for (int k = 0; k < kIn; ++k) feat[k] = x[sc * kIn + k];
-  __syncthreads();
-  float out[kOut];
-  forward_group<1>(feat, 0, w, reg[wave][0], reg[wave][1], cst, out);
-  if (s < n)
-    for (int o = 0; o < kOut; ++o) y[s * kOut + o] = out[o];
+  for (int c = 0; c < 3; ++c) {
+    const bool in = c < 2 || first;
+    const f32x4 sd = in ? load4(norm + kIn + 16 * c + 4 * q) : f32x4{1, 1, 1, 1};
+    mean[c] = in ? load4(norm + 16 * c + 4 * q) : f32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) inv[c][r] = 1.0f / sd[r];
+  }
+  bf16x4 w1[4][3], w2[4][4], w3[4];
+  f32x4 b1[4], b2[4];
+  const bf16x4 zero = pack_bf16(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) {
+    const float* r1 = params + kOffW1 + (16 * jt + l16) * kIn + 4 * q;
+    w1[jt][0] = load4_bf16(r1);
+    w1[jt][1] = load4_bf16(r1 + 16);
+    w1[jt][2] = first ? load4_bf16(r1 + 32) : zero;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) w2[jt][c] = load4_bf16(params + kOffW2 + (16 * jt + l16) * kH + 16 * c + 4 * q);
+    w3[jt] = l16 < kOut ? load4_bf16(params + kOffW3 + l16 * kH + 16 * jt + 4 * q) : zero;
+    b1[jt] = load4(params + kOffB1 + 16 * jt + 4 * q);
+    b2[jt] = load4(params + kOffB2 + 16 * jt + 4 * q);
+  }
+  float b3[kOut], ym[kOut], ysd[kOut];
+#pragma unroll
+  for (int o = 0; o < kOut; ++o) {
+    b3[o] = params[kOffB3 + o];
+    ym[o] = norm[2 * kIn + o];
+    ysd[o] = norm[2 * kIn + kOut + o];
+  }
+  for (; tile < tiles; tile += waves) {
+    bf16x4 in[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const f32x4 t = (v[c] - mean[c]) * inv[c];
+      in[c] = pack_bf16(t[0], t[1], t[2], t[3]);
+    }
+    if (tile + waves < tiles) features(tile + waves, v);
+    bf16x4 h1[4], h2[4];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {  // H1 = gelu(W1 X + b1)
+      f32x4 acc = b1[jt];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w1[jt][c], in[c], acc, 0, 0, 0);
+      h1[jt] = pack_bf16(gelu(acc[0]), gelu(acc[1]), gelu(acc[2]), gelu(acc[3]));
+    }
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {  // H2 = gelu(W2 H1 + b2)
+      f32x4 acc = b2[jt];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w2[jt][c], h1[c], acc, 0, 0, 0);
+      h2[jt] = pack_bf16(gelu(acc[0]), gelu(acc[1]), gelu(acc[2]), gelu(acc[3]));
+    }
+    f32x4 acc = {0, 0, 0, 0};  // Y = W3 H2 + b3: rows 0..2 of the tile, in lanes 0..15
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w3[c], h2[c], acc, 0, 0, 0);
+    const int64_t s = tile * 16 + l16;
+    if (first && s < n) {
+#pragma unroll
+      for (int o = 0; o < kOut; ++o) y[s * kOut + o] = (acc[o] + b3[o]) * ysd[o] + ym[o];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -454,7 +456,88 @@ __global__ void __launch_bounds__(256) k_grad_reduce(const float* __restrict__ g
   }
 }
 
-// Column mean / std of x (n x dim): one block per column, fixed-order FP64 sums.
+// Column mean and standard deviation of x (n x dim), FP64 sums in a fixed order.
+//
+// A block takes a run of consecutive rows and reads them as they lie: its
+// threads cover 256 / width whole rows at a time (width = min(dim, 256) columns;
+// a wider x is cut into groups of 256 columns, a block to each), so a wave's
+// loads are contiguous, and a thread stays in one column.  Per block and column one partial {sum, sum of
+// squares}; k_column_final adds the partials.  Bound: HBM.  One block per
+// column, each reading 4 bytes of every row, took 2.1 ms for 1.3 M x 36 (36
+// compute units, every line fetched 36 times), 35 us so.
+constexpr int kStatsUnroll = 8;
+__global__ void __launch_bounds__(256) k_column_partial(const float* __restrict__ x, int64_t n, int dim,
+                                                        int64_t rows_per_block, double* __restrict__ part) {
+  __shared__ double red[2][256];
+  const int groups = int((int64_t(dim) + 255) / 256), rb = int(blockIdx.x) / groups;
+  const int c0 = int(blockIdx.x) % groups * 256, width = dim - c0 < 256 ? dim - c0 : 256, per = 256 / width;
+  const int t = int(threadIdx.x), c = t % width, sub = t / width;
+  const int64_t begin = int64_t(rb) * rows_per_block;
+  const int64_t end = begin + rows_per_block < n ? begin + rows_per_block : n;
+  double s = 0.0, q = 0.0;
+  if (sub < per) {
+    const float* p = x + c0 + c;
+    int64_t r = begin + sub;
+    for (; r + int64_t(kStatsUnroll - 1) * per < end; r += int64_t(kStatsUnroll) * per) {
+      float v[kStatsUnroll];
+#pragma unroll
+      for (int u = 0; u < kStatsUnroll; ++u) v[u] = p[(r + int64_t(u) * per) * dim];
+#pragma unroll
+      for (int u = 0; u < kStatsUnroll; ++u) {
+        s += double(v[u]);
+        q += double(v[u]) * double(v[u]);
+      }
+    }
+    for (; r < end; r += per) {
+      const double v = double(p[r * dim]);
+      s += v;
+      q += v * v;
+    }
+  }
+  red[0][t] = s;
+  red[1][t] = q;
+  __syncthreads();
+  if (t < width) {
+    for (int k = 1; k < per; ++k) {
+      s += red[0][t + k * width];
+      q += red[1][t + k * width];
+    }
+    double* o = part + (int64_t(rb) * dim + c0 + t) * 2;
+    o[0] = s;
+    o[1] = q;
+  }
+}
+
+// One block per column: thread t adds partials t, t + 256, ..., then a fixed tree.
+__global__ void __launch_bounds__(256) k_column_final(const double* __restrict__ part, int nblocks, int64_t n, int dim,
+                                                      float* __restrict__ mean, float* __restrict__ sd) {
+  __shared__ double red[2][256];
+  const int c = blockIdx.x;
+  double s = 0.0, q = 0.0;
+  for (int b = threadIdx.x; b < nblocks; b += 256) {
+    s += part[(int64_t(b) * dim + c) * 2];
+    q += part[(int64_t(b) * dim + c) * 2 + 1];
+  }
+  red[0][threadIdx.x] = s;
+  red[1][threadIdx.x] = q;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (int(threadIdx.x) < o) {
+      red[0][threadIdx.x] += red[0][threadIdx.x + o];
+      red[1][threadIdx.x] += red[1][threadIdx.x + o];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const double m = red[0][0] / double(n);
+    const double var = red[1][0] / double(n) - m * m;
+    mean[c] = float(m);
+    sd[c] = var > 0.0 ? float(sqrt(var)) : 1.0f;
+  }
+}
+
+// The same with one block per column and no partials, for calls under stream
+// capture (whose scratch could not be allocated on the stream).
 __global__ void __launch_bounds__(256) k_column_stats(const float* __restrict__ x, int64_t n, int dim,
                                                       float* __restrict__ mean, float* __restrict__ sd) {
   __shared__ double red[2][256];
@@ -826,18 +909,47 @@ hipError_t mlp_pack_step(const float* params, uint16_t* packed_and_image, hipStr
   return hipGetLastError();
 }
 
-hipError_t mlp_infer(const float* x, int64_t n, const uint16_t* packed, const float* params, const float* norm,
-                     float* y, hipStream_t s) {
+hipError_t mlp_infer(const float* x, int64_t n, const float* params, const float* norm, float* y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int bs = 64 * kInferWaves;
-  hipLaunchKernelGGL(k_mlp_infer, dim3(unsigned((n + bs - 1) / bs)), dim3(bs), 0, s, x, n, packed, params, norm, y);
+  int cus = 256;
+  int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  // as many blocks as the chip holds at once (two a compute unit), fewer for few samples
+  const int64_t need = (n + 16 * kInferWaves - 1) / (16 * kInferWaves), most = int64_t(cus) * kInferBlocksPerCu;
+  hipLaunchKernelGGL(k_mlp_infer, dim3(unsigned(need < most ? need : most)), dim3(64 * kInferWaves), 0, s, x, n, params,
+                     norm, y);
   return hipGetLastError();
 }
 
 int mlp_train_blocks(int batch) { return (batch + kTS - 1) / kTS; }
 
-hipError_t column_stats(const float* x, int64_t n, int dim, float* mean, float* sd, hipStream_t s) {
-  hipLaunchKernelGGL(k_column_stats, dim3(dim), dim3(256), 0, s, x, n, dim, mean, sd);
+// Row runs of k_column_partial: one unrolled pass or more each, and about four
+// blocks a compute unit in all.
+int column_stats_runs(int64_t n, int dim) {
+  int cus = 256;
+  int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t groups = (int64_t(dim) + 255) / 256;
+  const int64_t rows = int64_t(kStatsUnroll) * (dim < 256 ? 256 / dim : 1);
+  const int64_t need = (n + rows - 1) / rows, most = 4 * int64_t(cus) / groups > 1 ? 4 * int64_t(cus) / groups : 1;
+  return int(need < most ? need : most);
+}
+
+// Below this the one-block-per-column kernel is done sooner than scratch is
+// allocated (about 23 us a call with it): 4.7 us at 3000 x 36, 33 us at 30000 x 36,
+// 15 us at 30000 x 3, 44 us at 100000 x 3.
+bool column_stats_direct(int64_t n, int dim) { return n <= (dim < 16 ? 50000 : 20000); }
+
+hipError_t column_stats(const float* x, int64_t n, int dim, double* part, float* mean, float* sd, hipStream_t s) {
+  if (!part) {
+    hipLaunchKernelGGL(k_column_stats, dim3(dim), dim3(256), 0, s, x, n, dim, mean, sd);
+    return hipGetLastError();
+  }
+  const int runs = column_stats_runs(n, dim);
+  const int64_t rows = (n + runs - 1) / runs;
+  hipLaunchKernelGGL(k_column_partial, dim3(unsigned(runs) * unsigned((int64_t(dim) + 255) / 256)), dim3(256), 0, s, x, n,
+                     dim, rows, part);
+  hipLaunchKernelGGL(k_column_final, dim3(dim), dim3(256), 0, s, part, runs, n, dim, mean, sd);
   return hipGetLastError();
 }
 

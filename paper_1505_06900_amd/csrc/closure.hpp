@@ -24,10 +24,12 @@ hipError_t closure_coarsen(int dtype, const void* rho, const void* u, const void
 hipError_t mlp_pack(const float* params, uint16_t* packed, hipStream_t s);
 // packed weights (kMlpNPacked) followed by the fused step's register image (kMlpNRegImage)
 hipError_t mlp_pack_step(const float* params, uint16_t* packed_and_image, hipStream_t s);
-hipError_t mlp_infer(const float* x, int64_t n, const uint16_t* packed, const float* params, const float* norm,
-                     float* y, hipStream_t s);
+hipError_t mlp_infer(const float* x, int64_t n, const float* params, const float* norm, float* y, hipStream_t s);
 int mlp_train_blocks(int batch);
-hipError_t column_stats(const float* x, int64_t n, int dim, float* mean, float* sd, hipStream_t s);
+// part: 2 * dim * column_stats_runs(n, dim) doubles, or NULL (one block per column)
+int column_stats_runs(int64_t n, int dim);
+bool column_stats_direct(int64_t n, int dim);  // few rows: part = NULL is the faster form
+hipError_t column_stats(const float* x, int64_t n, int dim, double* part, float* mean, float* sd, hipStream_t s);
 hipError_t mlp_gradient(const float* x, const float* t, int64_t nrows, const int* idx, int batch, const uint16_t* packed,
                         const float* params, const float* norm, float* gpart, float* lpart, float* grad, float* loss,
                         hipStream_t s);
