@@ -52,7 +52,7 @@
  *                               moment-storage step, n >= 1 (read every step)
  *      LBRR_CLOSURE_WPR=1|2     waves per row of the fused closure step with
  *                               FP32 or FP16 storage (read every step)
- *      LBRR_PAIR_LZ=n           z-planes per block of the launches that take two
+ *      LBRR_PAIR_LZ=n           z-planes (2D: rows) per block of the launches that take two
  *                               population steps, n >= 1, 0 for single steps only
  *                               (read by every lb_step call)
  *      LBRR_PAIR_ROWS=n         rows per block of those launches, if built for n

@@ -26,7 +26,7 @@ LIB = os.path.join(PKG, "liblbrr.so")
 RESOURCES = os.path.join(PKG, "liblbrr_resources.json")
 
 SOURCES = ["api.hip", "diag.hip", "probe.hip", "closure.hip", "kernels_d2q9.hip", "kernels_d3q19.hip", "kernels_d3q27.hip",
-           "kernels_pair_d3q19.hip", "kernels_pair_d3q27.hip"]
+           "kernels_pair_d2q9.hip", "kernels_pair_d3q19.hip", "kernels_pair_d3q27.hip"]
 
 ARCH = "gfx950"
 FLAGS = [

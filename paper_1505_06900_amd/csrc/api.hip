@@ -89,10 +89,19 @@ int moment_lz(int nvalues, int q, int nx, int ny, int nz, size_t es) {
   return 6;
 }
 
-// Tile height and chunk length of the step pair (k_step_pair); lz = 0 where
-// lb_step takes single steps.
+// Tile height and chunk length of the step pair (k_step_pair, k_step_pair2);
+// lz = 0 where lb_step takes single steps.
 //
-// A compute unit holds one block, a block's time grows with the planes it
+// 2D: pairs at every size; short chunks while there are few blocks (a chunk is a
+// serial march), longer ones where their edge rows cost traffic.  us a step, order
+// 4, single / lz = 1 / 2 / 4 / 6 / 12:
+//   FP32   64^2  2.66 / 1.92 / 2.29 / 3.11 / 3.85 / 6.17    501^2  5.42 / 4.02 / 3.55 / 3.76 / 4.41 / 6.72
+//        1024^2 14.5 / 14.3 / 12.0 / 10.2 / 10.8 / 10.8    2048^2 49.9 / 43.8 / 36.1 / 33.8 / 33.8 / 34.3
+//   FP64  256^2  4.49 / 3.75 / 3.76 / 4.46 / 5.69 / 9.22    501^2  8.30 / 6.89 / 5.06 / 6.07 / 6.52 / 9.32
+//        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.1 / 62.3 / 60.9 / 62.7
+// (walled boxes within a few per cent of these: 501^2 FP64 8.51 / 7.16 / 5.22 / 5.86).
+//
+// 3D: a compute unit holds one block, a block's time grows with the planes it
 // rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are dealt
 // to the eight XCDs in turn, so the plan taken is the one with the smallest
 //   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
@@ -116,12 +125,29 @@ PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz) {
   int forced_lz = -1, forced_rows = 0;
   if (const char* e = std::getenv("LBRR_PAIR_LZ")) forced_lz = std::atoi(e);
   if (const char* e = std::getenv("LBRR_PAIR_ROWS")) forced_rows = std::atoi(e);
-  const int64_t gx = (nx + 63) / 64;
-  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
-  if (forced_lz == 0 || (forced_lz < 0 && state < 6.5e6)) return p;
   int cus = 256;
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (ops.d == 2) {
+    p.rows = ops.pair_rows(storage, 0);
+    if (p.rows == 0) return p;
+    if (forced_lz >= 0) {
+      p.lz = forced_lz;
+      return p;
+    }
+    const int64_t gx = (nx + 253) / 254;  // k_step_pair2: 254 columns a block
+    p.lz = 6;
+    for (int lz : {1, 2})
+      if (gx * ((ny + lz - 1) / lz) <= int64_t(3) * cus) {
+        p.lz = lz;
+        return p;
+      }
+    if (gx * ((ny + 3) / 4) <= int64_t(12) * cus) p.lz = 4;
+    return p;
+  }
+  const int64_t gx = (nx + 63) / 64;
+  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
+  if (forced_lz == 0 || (forced_lz < 0 && state < 6.5e6)) return p;
   const int64_t slots = cus / 8 > 0 ? cus / 8 : 1;
   int64_t cost = 0;
   bool listed = false;
@@ -537,10 +563,11 @@ int lb_step(lb_handle h, long long n) {
   // it started from, which replays of a captured run rely on).
   StepArgs ap = a;
   ap.lz = 0;
-  if (n >= 4 && !h->moment() && !h->closure_on && !h->walls) {
+  if (n >= 4 && !h->moment() && !h->closure_on && !(h->walls && h->d() == 3)) {
     const PairPlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz);
     ap.rows = p.rows;
     ap.lz = p.lz;
+    ap.walls = h->walls;
   }
   for (long long k = 0; k < n; ++k) {
     long long left = n - k;  // steps up to the end of the call or the next check

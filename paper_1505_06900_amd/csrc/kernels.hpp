@@ -145,10 +145,73 @@ constexpr bool opposite_is_reversed() {
   return true;
 }
 
+// Side of the box along one axis: -1 (first node), +1 (last node), 0.
+__device__ __forceinline__ int wall_side(int walls, int bit, int v, int n) {
+  return (walls >> bit & 1) ? (v == 0 ? -1 : (v == n - 1 ? 1 : 0)) : 0;
+}
+
+// Pulled populations f of a node -> post-collision populations, in place; the
+// node lies on sides sx, sy, sz of the box (0: not on a wall of that axis).  A
+// wall node completes its populations and replaces rho - rho0 and j among its
+// moments; the rest of the collision is the one of every node (with j = 0, a1^(2)
+// is the second moment minus (rho - rho0) c_s^2 I).  Which populations are unknown is
+// a lane mask per axis and side, so the completion is selects, not branches, and
+// the collision is there once (us a step, D2Q9 order 4 with walls on both axes,
+// against a branch per population and a second copy of the collision: FP32 64^2
+// 4.19 -> 3.85, 256^2 4.40 -> 3.32; FP64 501^2 8.90 -> 8.51).
+template <class L, int N, class R>
+__device__ __forceinline__ void collide_walls(R (&f)[L::Q], R rho0, R omega1, int sx, int sy, int sz) {
+  static_assert(opposite_is_reversed<L>(), "population order");
+  const bool wall = (sx | sy | sz) != 0;
+  R drho = R(0);
+  if (wall) {
+    const bool first[3] = {sx < 0, sy < 0, sz < 0}, last[3] = {sx > 0, sy > 0, sz > 0};
+    // does population I come from outside the box?
+    auto outside = [&](auto I) {
+      bool o = false;
+      if constexpr (L::cx(I) != 0) o |= L::cx(I) > 0 ? first[0] : last[0];
+      if constexpr (L::cy(I) != 0) o |= L::cy(I) > 0 ? first[1] : last[1];
+      if constexpr (L::cz(I) != 0) o |= L::cz(I) > 0 ? first[2] : last[2];
+      return o;
+    };
+    R sd = R(0), wb = R(0);
+    R g[L::Q];
+    bool buried[L::Q];
+    sfor<0, L::Q>([&](auto I) {
+      constexpr int O = L::Q - 1 - int(I);  // opposite velocity
+      const bool u = outside(I);
+      g[I] = u ? f[O] : f[I];
+      // only a velocity along two axes or more can be unknown both ways
+      constexpr bool edge = (L::cx(I) != 0) + (L::cy(I) != 0) + (L::cz(I) != 0) >= 2;
+      buried[I] = edge && u && outside(std::integral_constant<int, O>{});
+      if constexpr (edge) {
+        sd = sd + (buried[I] ? R(0) : g[I]);
+        wb = wb + (buried[I] ? R(L::w(I)) : R(0));
+      } else {
+        sd = sd + g[I];
+      }
+    });
+    drho = sd / (R(1) - wb);
+    sfor<0, L::Q>([&](auto I) {
+      R v = R(L::w(I)) * drho;
+      asm("" : "+v"(v));  // rounded before the moments add it
+      f[I] = buried[I] ? v : g[I];
+    });
+  }
+  Moments<R> m = raw_moments<L, R>(f);
+  if (wall) {
+    m.d0 = drho;
+    m.jx = m.jy = m.jz = R(0);
+  }
+  const Hydro<R> h = hydro<L, R>(m, rho0);
+  R C[3][3][3];
+  coefficients<L, N, R>(h, omega1, C);
+  reconstruct<L, N, R>(C, f);
+}
+
 template <class L, int N, class S>
 __global__ void __launch_bounds__(256) k_step_walls(const S* __restrict__ src, S* __restrict__ dst, StepArgs a,
                                                     int walls) {
-  static_assert(opposite_is_reversed<L>(), "population order");
   using R = typename Prec<S>::R;
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y), z = blockIdx.z;
@@ -168,54 +231,8 @@ __global__ void __launch_bounds__(256) k_step_walls(const S* __restrict__ src, S
     const S* row = src + int64_t(I) * a.si + int64_t(zs) * a.sz + int64_t(ys) * a.sy;
     f[I] = R(row[xs]);
   });
-  // sides of the box this node lies on: -1 (first node), +1 (last node), 0
-  const int sx = (walls & 1) ? (x == 0 ? -1 : (x == a.nx - 1 ? 1 : 0)) : 0;
-  const int sy = (walls & 2) ? (y == 0 ? -1 : (y == a.ny - 1 ? 1 : 0)) : 0;
-  const int sz = (L::D == 3 && (walls & 4)) ? (z == 0 ? -1 : (z == a.nz - 1 ? 1 : 0)) : 0;
-  if (sx == 0 && sy == 0 && sz == 0) {
-    collide<L, N, R>(f, R(a.rho0), R(a.omega1));
-  } else {
-    // population with velocity c comes from outside iff some side s != 0 has c = -s
-    auto from_outside = [&](int cx, int cy, int cz) {
-      return (sx != 0 && cx == -sx) || (sy != 0 && cy == -sy) || (sz != 0 && cz == -sz);
-    };
-    R sd = R(0), wb = R(0);
-    sfor<0, L::Q>([&](auto I) {
-      constexpr int cx = L::cx(I), cy = L::cy(I), cz = L::cz(I);
-      constexpr int O = L::Q - 1 - int(I);  // opposite velocity
-      if (!from_outside(cx, cy, cz)) sd = sd + f[I];
-      else if (!from_outside(-cx, -cy, -cz)) sd = sd + f[O];
-      else wb = wb + R(L::w(I));
-    });
-    const R drho = sd / (R(1) - wb);
-    R g[L::Q];
-    sfor<0, L::Q>([&](auto I) {
-      constexpr int cx = L::cx(I), cy = L::cy(I), cz = L::cz(I);
-      constexpr int O = L::Q - 1 - int(I);
-      if (!from_outside(cx, cy, cz)) g[I] = f[I];
-      else if (!from_outside(-cx, -cy, -cz)) g[I] = f[O];
-      else g[I] = R(L::w(I)) * drho;
-    });
-    const Moments<R> m = raw_moments<L, R>(g);
-    constexpr R cs2 = R(kCs2);
-    Hydro<R> h;
-    h.drho = drho;
-    h.rho = R(a.rho0) + drho;
-    h.ux = h.uy = h.uz = h.jx = h.jy = h.jz = R(0);
-    h.axx = fused(-drho, cs2, m.pxx);
-    h.ayy = fused(-drho, cs2, m.pyy);
-    h.axy = m.pxy;
-    if constexpr (L::D == 3) {
-      h.azz = fused(-drho, cs2, m.pzz);
-      h.axz = m.pxz;
-      h.ayz = m.pyz;
-    } else {
-      h.azz = h.axz = h.ayz = R(0);
-    }
-    R C[3][3][3];
-    coefficients<L, N, R>(h, R(a.omega1), C);
-    reconstruct<L, N, R>(C, f);
-  }
+  collide_walls<L, N, R>(f, R(a.rho0), R(a.omega1), wall_side(walls, 0, x, a.nx), wall_side(walls, 1, y, a.ny),
+                         L::D == 3 ? wall_side(walls, 2, z, a.nz) : 0);
   S* out = dst + int64_t(z) * a.sz + int64_t(y) * a.sy + x;
   sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(to_store<S, R>(f[I]), out + int64_t(I) * a.si); });
 }

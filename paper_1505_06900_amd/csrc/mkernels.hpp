@@ -237,11 +237,6 @@ __device__ __forceinline__ void add_row(Moments<R>& s, const R (*pop)[BX], int t
 // population whose opposite is unknown counts twice (at xi and at -xi: the
 // momentum cancels), and the buried ones enter when the node is finalised.
 
-// Side of the box along one axis: -1 (first node), +1 (last node), 0.
-__device__ __forceinline__ int wall_side(int walls, int bit, int v, int n) {
-  return (walls >> bit & 1) ? (v == 0 ? -1 : (v == n - 1 ? 1 : 0)) : 0;
-}
-
 // Does a population moving along (cx, cy, cz) arrive from outside the box?
 __device__ __forceinline__ bool from_outside(int sx, int sy, int sz, int cx, int cy, int cz) {
   return (sx != 0 && cx == -sx) || (sy != 0 && cy == -sy) || (sz != 0 && cz == -sz);

@@ -23,15 +23,15 @@ struct StepArgs {
   int64_t si, sy, sz;  // element strides of population, row and plane
   double rho0;         // reference density of the deviation storage
   double omega1;       // 1 - 1/tau
-  int lz;              // z-planes per block of the moment-state step and of the step pair (3D)
+  int lz;              // z-planes (2D: rows) per block of the moment-state step and of the step pair
   int rows;            // rows of a tile of the step pair
-  int walls;           // moment-state step: resting walls on the axes of this mask (bit 0 x, 1 y, 2 z)
+  int walls;           // moment-state step and step pair: resting walls on the axes of this mask (bit 0 x, 1 y, 2 z)
 };
 
 struct LatticeOps {
   int q, d, nmax;
   hipError_t (*step)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
-  // two steps in one launch (3D, population storage FP64 and FP32, no walls); pair_rows: the i-th tile height it is
+  // two steps in one launch (population storage FP64 and FP32; 2D with a.walls, 3D without walls); pair_rows: the i-th tile height it is
   // built for, 0 past the last and where the storage has no such kernel
   hipError_t (*step_pair)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
   int (*pair_rows)(int storage, int i);

@@ -63,17 +63,14 @@ struct OpsImpl {
     return hipErrorInvalidValue;
   }
   static hipError_t step_pair(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s) {
-    if constexpr (L::D == 3) {
-      switch (storage) {
-        case 0: return step_pair_by_order<L, double>(order, src, dst, a, s);
-        case 1: return step_pair_by_order<L, float>(order, src, dst, a, s);
-      }
+    switch (storage) {
+      case 0: return step_pair_by_order<L, double>(order, src, dst, a, s);
+      case 1: return step_pair_by_order<L, float>(order, src, dst, a, s);
     }
     return hipErrorInvalidValue;
   }
   static int pair_rows(int storage, int i) {
-    if constexpr (L::D == 3) return pair_rows_of<L>(storage, i);
-    return 0;
+    return pair_rows_of<L>(storage, i);
   }
   static hipError_t init(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1,
                          void* dst, const StepArgs& a, hipStream_t s) {

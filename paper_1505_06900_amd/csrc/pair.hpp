@@ -1,5 +1,5 @@
-// Two steps of the population update in one launch (FP32 and FP64 storage, 3D,
-// no walls).
+// Two steps of the population update in one launch (FP32 and FP64 storage; 3D
+// without walls, 2D with or without).
 //
 // k_step moves the state through HBM once per step and is held by that
 // traffic.  Here a block pulls and collides the nodes of a tile and of its
@@ -175,6 +175,102 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   if (inner) second(z1 - 1, layer_sums<L, -1, R>(arrived), mid2, up2);
 }
 
+// Two steps in 2D.  A block of kPairRowX threads runs the first step on a row of
+// kPairRowX nodes (x0 - 1 .. x0 + kPairRowX - 2) and marches along y through a chunk
+// of a.lz rows: the first step's populations on row p with c_y = +1, 0, -1
+// arrive on rows p + 1, p, p - 1, so an inner thread keeps the three arrivals of
+// each layer it is waiting for, and collides row p - 1 when row p is there.  The
+// populations moving along y stay in their thread; the six others pass through
+// LDS, in two buffers taken in turn (one barrier a row).  W: resting walls on the
+// axes of a.walls.  Measured (pair_plan, api.hip): 2048^2 FP32 49.9 -> 33.8 us a step
+// (124 GLUPS; 5.6 TB/s with the rows read twice), FP64 101 -> 61; small grids save
+// a launch: 64^2 FP32 2.66 -> 1.92.
+constexpr int kPairRowX = 256;
+
+template <class L, int N, class S, bool W>
+__global__ void __launch_bounds__(kPairRowX) k_step_pair2(const S* __restrict__ src, S* __restrict__ dst, StepArgs a) {
+  static_assert(L::D == 2, "2D lattices");
+  using R = S;
+  constexpr int BX = kPairRowX;
+  __shared__ R pop[2][6][BX];  // [c_y + 1 + (c_x > 0 ? 3 : 0)]
+  const int tx = int(threadIdx.x);
+  const int gx = (a.nx + BX - 3) / (BX - 2);
+  const int bx = int(blockIdx.x) % gx, by = int(blockIdx.x) / gx;
+  const int x0 = bx * (BX - 2);
+  const int px = wrap_axis(x0 - 1 + tx, a.nx);
+  const int xo = x0 + tx - 1;
+  const bool inner = tx >= 1 && tx <= BX - 2 && xo < a.nx;
+  const uint32_t xs[3] = {uint32_t(px == a.nx - 1 ? 0 : px + 1) * uint32_t(sizeof(S)), uint32_t(px) * uint32_t(sizeof(S)),
+                          uint32_t(px == 0 ? a.nx - 1 : px - 1) * uint32_t(sizeof(S))};
+  const uint32_t off_out = uint32_t(xo) * uint32_t(sizeof(S));
+  const R rho0 = R(a.rho0), om = R(a.omega1);
+  const int sx1 = W ? wall_side(a.walls, 0, px, a.nx) : 0, sx2 = W ? wall_side(a.walls, 0, xo, a.nx) : 0;
+  auto pull = [&](int y, R (&f)[L::Q]) __attribute__((always_inline)) {
+    const int ys[3] = {y == a.ny - 1 ? 0 : y + 1, y, y == 0 ? a.ny - 1 : y - 1};
+    sfor<0, L::Q>([&](auto I) {
+      constexpr int cx = L::cx(I), cy = L::cy(I);
+      f[I] = at_offset(src + int64_t(I) * a.si + int64_t(ys[cy + 1]) * a.sy, xs[cx + 1]);
+    });
+  };
+  auto update = [&](R (&f)[L::Q], int sx, int y) __attribute__((always_inline)) {
+    if constexpr (W) collide_walls<L, N, R>(f, rho0, om, sx, wall_side(a.walls, 1, y, a.ny), 0);
+    else collide<L, N, R>(f, rho0, om);
+  };
+  // rows y0 .. y1 - 1; first-step rows y0 - 1 .. y1, row y0 - 1 + k of the march
+  const int y0 = by * a.lz;
+  const int y1 = (y0 + a.lz < a.ny) ? y0 + a.lz : a.ny;
+  const int n = y1 - y0;
+  struct {  // a struct, as in k_step_pair
+    R v[L::Q];
+  } next;
+  struct {
+    R v[3];  // arrivals with c_x = -1, 0, 1
+  } up1, up2, mid2;
+  pull(wrap_axis(y0 - 1, a.ny), next.v);
+  for (int k = 0; k <= n + 1; ++k) {
+    const int y = wrap_axis(y0 - 1 + k, a.ny);
+    R f[L::Q];
+    sfor<0, L::Q>([&](auto I) { f[I] = next.v[I]; });
+    if (k <= n) pull(wrap_axis(y0 + k, a.ny), next.v);
+    update(f, sx1, y);
+    const int b = k & 1;
+    sfor<0, L::Q>([&](auto I) {
+      constexpr int cx = L::cx(I), cy = L::cy(I);
+      if constexpr (cx != 0) pop[b][cy + 1 + (cx > 0 ? 3 : 0)][tx] = f[I];
+    });
+    lds_barrier();
+    if (inner) {
+      // arrival from row y with velocity (c_x, c_y)
+      auto arrived = [&](auto X, auto Y) {
+        constexpr int cx = int(X) - 1, cy = int(Y) - 1;
+        if constexpr (cx == 0) return f[velocity_index<L>(0, cy, 0)];
+        else return pop[b][cy + 1 + (cx > 0 ? 3 : 0)][tx - cx];
+      };
+      using row_m = std::integral_constant<int, 0>;
+      using row_0 = std::integral_constant<int, 1>;
+      using row_p = std::integral_constant<int, 2>;
+      if (k >= 2) {
+        R g[L::Q];
+        sfor<0, 3>([&](auto X) {
+          constexpr int cx = int(X) - 1;
+          g[velocity_index<L>(cx, 1, 0)] = up2.v[X];
+          g[velocity_index<L>(cx, 0, 0)] = mid2.v[X];
+          g[velocity_index<L>(cx, -1, 0)] = arrived(X, row_m{});
+        });
+        const int yt = y0 + k - 2;
+        update(g, sx2, yt);
+        S* d = dst + int64_t(yt) * a.sy;
+        sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(g[I], ptr_at_offset(d + int64_t(I) * a.si, off_out)); });
+      }
+      up2 = up1;
+      sfor<0, 3>([&](auto X) {
+        mid2.v[X] = arrived(X, row_0{});
+        up1.v[X] = arrived(X, row_p{});
+      });
+    }
+  }
+}
+
 // Tile heights the host chooses from (pair_plan in api.hip).  GLUPS at 256^3,
 // order 4, by rows: D3Q27 FP32 5 / 7 / 8 / 9 / 10 rows 40.4 / 38.7 / 43.6 / 40.6 / 31.9 (10 and
 // more rows spill: 128 VGPRs), D3Q19 FP32 5 / 8 / 9 / 11 / 13 rows 57.1 / 56.7 / 56.5 /
@@ -182,6 +278,7 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
 // rows spill).  The second height serves boxes whose rows the first divides badly.
 template <class L, class S>
 constexpr int pair_rows_option(int i) {
+  if (L::D == 2) return i == 0 ? 1 : 0;
   if (sizeof(S) == 8) return i == 0 ? 4 : (i == 1 ? 3 : 0);
   if (L::Q == 19) return i == 0 ? 13 : (i == 1 ? 9 : 0);
   return i == 0 ? 8 : (i == 1 ? 9 : 0);
@@ -190,20 +287,36 @@ constexpr int pair_rows_option(int i) {
 template <class L, int N, class S, int TY>
 hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
   if (a.lz < 1) return hipErrorInvalidValue;
-  const int64_t plane = (int64_t(a.ny - 1) * a.sy + a.nx) * int64_t(sizeof(S));
-  if (plane >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // 32-bit lane byte offsets
-  const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
-  const int64_t blocks = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
-  if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_step_pair<L, N, S, TY>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
-                     static_cast<const S*>(src), static_cast<S*>(dst), a);
-  return hipGetLastError();
+  if constexpr (L::D == 2) {
+    if (uint64_t(a.nx) * sizeof(S) > 0xffffffffull) return hipErrorInvalidValue;  // 32-bit lane byte offsets
+    const int64_t nb = int64_t((a.nx + kPairRowX - 3) / (kPairRowX - 2)) * ((a.ny + a.lz - 1) / a.lz);
+    if (nb >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    if (a.walls)
+      hipLaunchKernelGGL((k_step_pair2<L, N, S, true>), dim3(unsigned(nb)), dim3(kPairRowX), 0, s,
+                         static_cast<const S*>(src), static_cast<S*>(dst), a);
+    else
+      hipLaunchKernelGGL((k_step_pair2<L, N, S, false>), dim3(unsigned(nb)), dim3(kPairRowX), 0, s,
+                         static_cast<const S*>(src), static_cast<S*>(dst), a);
+    return hipGetLastError();
+  } else {
+    const int64_t plane = (int64_t(a.ny - 1) * a.sy + a.nx) * int64_t(sizeof(S));
+    if (plane >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // 32-bit lane byte offsets
+    const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
+    const int64_t blocks = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
+    if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_step_pair<L, N, S, TY>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+                       static_cast<const S*>(src), static_cast<S*>(dst), a);
+    return hipGetLastError();
+  }
 }
 
 template <class L, int N, class S>
 hipError_t step_pair_by_rows(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
   if (a.rows == pair_rows_option<L, S>(0)) return launch_step_pair<L, N, S, pair_rows_option<L, S>(0)>(src, dst, a, s);
-  if (a.rows == pair_rows_option<L, S>(1)) return launch_step_pair<L, N, S, pair_rows_option<L, S>(1)>(src, dst, a, s);
+  if constexpr (L::D == 3) {
+    if (a.rows == pair_rows_option<L, S>(1))
+      return launch_step_pair<L, N, S, pair_rows_option<L, S>(1)>(src, dst, a, s);
+  }
   return hipErrorInvalidValue;
 }
 

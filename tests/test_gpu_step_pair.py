@@ -1,7 +1,7 @@
 """Launches of two population steps against single steps, bit for bit.
 
-lb_step may take steps two to a launch (3D, FP64 and FP32 population storage, no walls); the
-single steps are held to the oracle elsewhere.  Boxes at the edges of the launch's tiles: one
+lb_step may take steps two to a launch (FP64 and FP32 population storage; 3D without walls, 2D
+with or without); the single steps are held to the oracle elsewhere.  Boxes at the edges of the launch's tiles: one
 node, fewer rows or planes than a tile, rows of 64 +- 1 nodes, chunk lengths that leave one
 plane over, both tile heights; every order.  LBRR_PAIR_LZ=0 gives the single steps.
 """
@@ -13,12 +13,13 @@ ROWS = {("D3Q27", "fp32"): (8, 9), ("D3Q19", "fp32"): (13, 9), ("D3Q27", "fp64")
 SHAPES = [(1, 1, 1), (3, 2, 130), (7, 19, 65), (25, 37, 63), (20, 26, 64)]
 
 
-def _run(lbrr, torch, lattice, shape, order, storage, calls, check=0):
+def _run(lbrr, torch, lattice, shape, order, storage, calls, check=0, walls=(False,) * 3):
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
     rho = 1.0 + 0.01 * torch.randn(shape, generator=g, device="cuda", dtype=torch.float64)
-    u = 0.03 * torch.randn((3,) + shape, generator=g, device="cuda", dtype=torch.float64)
+    u = 0.03 * torch.randn((lbrr.DIM[lattice],) + shape, generator=g, device="cuda", dtype=torch.float64)
     sim = lbrr.Simulation(lattice, shape, 0.62, order, storage=storage)
+    sim.set_walls(*walls)
     sim.set_check_interval(check)
     sim.init_fields(rho, u)
     for n in calls:
@@ -55,3 +56,21 @@ def test_own_choice_splits_and_checks(lbrr, gpu, storage, monkeypatch):
         got, steps = _run(lbrr, gpu, "D3Q27", shape, 4, storage, calls, check)
         assert steps == 23
         assert gpu.equal(got, want), (calls, check)
+
+
+@pytest.mark.parametrize("order", [2, 3, 4])
+@pytest.mark.parametrize("storage", ["fp32", "fp64"])
+@pytest.mark.parametrize("walls", [(False, False), (True, False), (False, True), (True, True)])
+def test_pairs_equal_single_steps_2d(lbrr, gpu, order, storage, walls, monkeypatch):
+    """Rows around the 254 columns of a block, one to several blocks, chunks that divide the rows or not."""
+    for shape in [(1, 1, 1), (1, 3, 3), (1, 5, 254), (1, 20, 255), (1, 33, 600), (1, 4, 256)]:
+        if (walls[0] and shape[2] < 3) or (walls[1] and shape[1] < 3):
+            continue
+        monkeypatch.setenv("LBRR_PAIR_LZ", "0")
+        want, _ = _run(lbrr, gpu, "D2Q9", shape, order, storage, [9], walls=walls + (False,))
+        for lz in (1, 2, 6, 24):
+            monkeypatch.setenv("LBRR_PAIR_LZ", str(lz))
+            got, steps = _run(lbrr, gpu, "D2Q9", shape, order, storage, [9], walls=walls + (False,))
+            assert steps == 9
+            assert gpu.isfinite(got).all()
+            assert gpu.equal(got, want), (shape, lz)
