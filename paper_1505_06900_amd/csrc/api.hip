@@ -115,12 +115,14 @@ int moment_lz(int nvalues, int q, int nx, int ny, int nz, size_t es) {
 // along z is then longer than two single steps (D3Q27 FP32 48^3 13.7 -> 15.0, 36^3
 // 8.6 -> 8.0, 32^3 7.3 -> 5.9; D3Q19 FP32 48^3 18.2 -> 17.6, 24 x 24 x 330 20.3 -> 19.5):
 // pairs are taken where the state, weighted by the used share of a tile's 64
-// columns, has at least 6.5 MB.
+// columns, has at least 6.5 MB, 20 MB with walls (single -> pairs, walls along z / on
+// all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
+// / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
 // LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
 struct PairPlan {
   int rows = 0, lz = 0;
 };
-PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz) {
+PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls) {
   PairPlan p;
   int forced_lz = -1, forced_rows = 0;
   if (const char* e = std::getenv("LBRR_PAIR_LZ")) forced_lz = std::atoi(e);
@@ -129,7 +131,7 @@ PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz) {
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (ops.d == 2) {
-    p.rows = ops.pair_rows(storage, 0);
+    p.rows = ops.pair_rows(storage, 0, walls);
     if (p.rows == 0) return p;
     if (forced_lz >= 0) {
       p.lz = forced_lz;
@@ -147,12 +149,12 @@ PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz) {
   }
   const int64_t gx = (nx + 63) / 64;
   const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
-  if (forced_lz == 0 || (forced_lz < 0 && state < 6.5e6)) return p;
+  if (forced_lz == 0 || (forced_lz < 0 && state < (walls ? 2e7 : 6.5e6))) return p;
   const int64_t slots = cus / 8 > 0 ? cus / 8 : 1;
   int64_t cost = 0;
   bool listed = false;
-  for (int i = 0; const int rows = ops.pair_rows(storage, i); ++i) listed = listed || rows == forced_rows;
-  for (int i = 0; const int rows = ops.pair_rows(storage, i); ++i) {
+  for (int i = 0; const int rows = ops.pair_rows(storage, i, walls); ++i) listed = listed || rows == forced_rows;
+  for (int i = 0; const int rows = ops.pair_rows(storage, i, walls); ++i) {
     if (listed && rows != forced_rows) continue;
     const int64_t gy = (ny + rows - 1) / rows;
     for (int chunks = 1; chunks <= nz; ++chunks) {
@@ -563,8 +565,8 @@ int lb_step(lb_handle h, long long n) {
   // it started from, which replays of a captured run rely on).
   StepArgs ap = a;
   ap.lz = 0;
-  if (n >= 4 && !h->moment() && !h->closure_on && !(h->walls && h->d() == 3)) {
-    const PairPlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz);
+  if (n >= 4 && !h->moment() && !h->closure_on) {
+    const PairPlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz, h->walls != 0);
     ap.rows = p.rows;
     ap.lz = p.lz;
     ap.walls = h->walls;

@@ -150,21 +150,19 @@ __device__ __forceinline__ int wall_side(int walls, int bit, int v, int n) {
   return (walls >> bit & 1) ? (v == 0 ? -1 : (v == n - 1 ? 1 : 0)) : 0;
 }
 
-// Pulled populations f of a node -> post-collision populations, in place; the
-// node lies on sides sx, sy, sz of the box (0: not on a wall of that axis).  A
-// wall node completes its populations and replaces rho - rho0 and j among its
-// moments; the rest of the collision is the one of every node (with j = 0, a1^(2)
-// is the second moment minus (rho - rho0) c_s^2 I).  Which populations are unknown is
+// Wall nodes.  The node lies on sides sx, sy, sz of the box (0: not on a wall of
+// that axis); a node on none is left as it is.  Which populations are unknown is
 // a lane mask per axis and side, so the completion is selects, not branches, and
-// the collision is there once (us a step, D2Q9 order 4 with walls on both axes,
-// against a branch per population and a second copy of the collision: FP32 64^2
-// 4.19 -> 3.85, 256^2 4.40 -> 3.32; FP64 501^2 8.90 -> 8.51).
-template <class L, int N, class R>
-__device__ __forceinline__ void collide_walls(R (&f)[L::Q], R rho0, R omega1, int sx, int sy, int sz) {
+// the collision that follows is the one of every node (us a step, D2Q9 order 4 with
+// walls on both axes, against a branch per population and a second copy of the
+// collision: FP32 64^2 4.19 -> 3.85, 256^2 4.40 -> 3.32; FP64 501^2 8.90 -> 8.51).
+//
+// Completes the pulled populations f of a wall node; returns its rho - rho0.
+template <class L, class R>
+__device__ __forceinline__ R complete_walls(R (&f)[L::Q], int sx, int sy, int sz) {
   static_assert(opposite_is_reversed<L>(), "population order");
-  const bool wall = (sx | sy | sz) != 0;
   R drho = R(0);
-  if (wall) {
+  if ((sx | sy | sz) != 0) {
     const bool first[3] = {sx < 0, sy < 0, sz < 0}, last[3] = {sx > 0, sy > 0, sz > 0};
     // does population I come from outside the box?
     auto outside = [&](auto I) {
@@ -198,12 +196,26 @@ __device__ __forceinline__ void collide_walls(R (&f)[L::Q], R rho0, R omega1, in
       f[I] = buried[I] ? v : g[I];
     });
   }
+  return drho;
+}
+
+// Moments of completed populations; a wall node takes drho and j = 0 (with j = 0, the
+// a1^(2) that hydro forms is the second moment minus (rho - rho0) c_s^2 I).
+template <class L, class R>
+__device__ __forceinline__ Moments<R> moments_walls(const R (&f)[L::Q], R drho, int sx, int sy, int sz) {
   Moments<R> m = raw_moments<L, R>(f);
-  if (wall) {
+  if ((sx | sy | sz) != 0) {
     m.d0 = drho;
     m.jx = m.jy = m.jz = R(0);
   }
-  const Hydro<R> h = hydro<L, R>(m, rho0);
+  return m;
+}
+
+// Pulled populations f of a node -> post-collision populations, in place.
+template <class L, int N, class R>
+__device__ __forceinline__ void collide_walls(R (&f)[L::Q], R rho0, R omega1, int sx, int sy, int sz) {
+  const R drho = complete_walls<L, R>(f, sx, sy, sz);
+  const Hydro<R> h = hydro<L, R>(moments_walls<L, R>(f, drho, sx, sy, sz), rho0);
   R C[3][3][3];
   coefficients<L, N, R>(h, omega1, C);
   reconstruct<L, N, R>(C, f);

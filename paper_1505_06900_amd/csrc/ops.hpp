@@ -31,10 +31,10 @@ struct StepArgs {
 struct LatticeOps {
   int q, d, nmax;
   hipError_t (*step)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
-  // two steps in one launch (population storage FP64 and FP32; 2D with a.walls, 3D without walls); pair_rows: the i-th tile height it is
-  // built for, 0 past the last and where the storage has no such kernel
+  // two steps in one launch (population storage FP64 and FP32); pair_rows: the i-th tile height it is built for, 0
+  // past the last and where there is no such kernel
   hipError_t (*step_pair)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
-  int (*pair_rows)(int storage, int i);
+  int (*pair_rows)(int storage, int i, bool walls);
   hipError_t (*init)(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1, void* dst,
                      const StepArgs& a, hipStream_t s);
   hipError_t (*moments)(int storage, int dtype, const void* src, void* rho, void* u, void* pi1, const StepArgs& a,

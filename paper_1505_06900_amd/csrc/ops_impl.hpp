@@ -48,7 +48,7 @@ hipError_t step_walls_by_order(int order, const void* src, void* dst, const Step
 template <class L, class S>
 hipError_t step_pair_by_order(int order, const void* src, void* dst, const StepArgs& a, hipStream_t s);
 template <class L>
-int pair_rows_of(int storage, int i);
+int pair_rows_of(int storage, int i, bool walls);
 
 template <class L>
 struct OpsImpl {
@@ -69,8 +69,8 @@ struct OpsImpl {
     }
     return hipErrorInvalidValue;
   }
-  static int pair_rows(int storage, int i) {
-    return pair_rows_of<L>(storage, i);
+  static int pair_rows(int storage, int i, bool walls) {
+    return pair_rows_of<L>(storage, i, walls);
   }
   static hipError_t init(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1,
                          void* dst, const StepArgs& a, hipStream_t s) {

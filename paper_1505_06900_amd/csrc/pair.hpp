@@ -1,5 +1,5 @@
-// Two steps of the population update in one launch (FP32 and FP64 storage; 3D
-// without walls, 2D with or without).
+// Two steps of the population update in one launch (FP32 and FP64 storage,
+// with or without walls; no walls for D3Q27 FP64).
 //
 // k_step moves the state through HBM once per step and is held by that
 // traffic.  Here a block pulls and collides the nodes of a tile and of its
@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -37,7 +38,36 @@ namespace lbrr {
 // layer of plane p is there.  The pull of the next plane is issued as soon as
 // the moments of the present one are formed, and is in flight through both
 // collisions.
-template <class L, int N, class S, int TY>
+//
+// W: resting walls on the axes of a.walls.  A wall node is completed from its
+// populations one by one, so the thread then keeps the arrivals themselves
+// (LayerValues) in place of their sums.
+template <class L, int CZ, class R>
+struct LayerValues {
+  R v[9];  // [c_x + 1 + 3 (c_y + 1)], the velocities the lattice has
+  template <class G>
+  __device__ __forceinline__ void read(G&& get) {
+    sfor<0, 9>([&](auto K) {
+      constexpr int i = velocity_index<L>(int(K) % 3 - 1, int(K) / 3 - 1, CZ);
+      if constexpr (i >= 0) v[K] = get(std::integral_constant<int, i>{});
+    });
+  }
+  __device__ __forceinline__ void put(R (&f)[L::Q]) const {
+    sfor<0, 9>([&](auto K) {
+      constexpr int i = velocity_index<L>(int(K) % 3 - 1, int(K) / 3 - 1, CZ);
+      if constexpr (i >= 0) f[i] = v[K];
+    });
+  }
+};
+template <class L, int CZ, class R>
+struct LayerTotals : LayerSums<R> {
+  template <class G>
+  __device__ __forceinline__ void read(G&& get) {
+    static_cast<LayerSums<R>&>(*this) = layer_sums<L, CZ, R>(get);
+  }
+};
+
+template <class L, int N, class S, int TY, bool W>
 __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict__ src, S* __restrict__ dst,
                                                              StepArgs a) {
   static_assert(L::D == 3, "3D lattices");
@@ -87,6 +117,9 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   const uint32_t off_out =
       inner ? uint32_t((int64_t(y0 + r - 1) * a.sy + (x0 + lane)) * int64_t(sizeof(S))) : 0u;
   const R rho0 = R(a.rho0), om = R(a.omega1);
+  // sides of the box of the first and the second node
+  const int sx1 = W ? wall_side(a.walls, 0, px, a.nx) : 0, sy1 = W ? wall_side(a.walls, 1, py, a.ny) : 0;
+  const int sx2 = W ? wall_side(a.walls, 0, x0 + lane, a.nx) : 0, sy2 = W ? wall_side(a.walls, 1, y0 + r - 1, a.ny) : 0;
 
   auto pull = [&](int z, R (&f)[L::Q]) __attribute__((always_inline)) {
     const int zs[3] = {z == a.nz - 1 ? 0 : z + 1, z, z == 0 ? a.nz - 1 : z - 1};
@@ -109,12 +142,23 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   struct {  // a struct: a plain array carried around the loop ends in one 32-register tuple, copied whole
     R v[L::Q];
   } f;
-  LayerSums<R> up1, up2, mid2;  // c_z = +1 layers of targets k - 1 and k - 2, c_z = 0 layer of target k - 2
+  using Lo = std::conditional_t<W, LayerValues<L, -1, R>, LayerTotals<L, -1, R>>;
+  using Mid = std::conditional_t<W, LayerValues<L, 0, R>, LayerTotals<L, 0, R>>;
+  using Up = std::conditional_t<W, LayerValues<L, 1, R>, LayerTotals<L, 1, R>>;
+  Up up1, up2;  // c_z = +1 layers of targets k - 1 and k - 2
+  Mid mid2;     // c_z = 0 layer of target k - 2
   // First step of plane k into LDS; ZS selects all populations (2) or those
   // with c_z = ZS.  Next: pull plane k + 1 once the moments of plane k are formed.
   auto first = [&](int k, auto ZS, auto Next) __attribute__((always_inline)) {
     constexpr int Z = decltype(ZS)::value;
-    Moments<R> m = raw_moments<L, R>(f.v);
+    Moments<R> m;
+    if constexpr (W) {
+      const int sz = wall_side(a.walls, 2, wrap_axis(z0 - 1 + k, a.nz), a.nz);
+      const R drho = complete_walls<L, R>(f.v, sx1, sy1, sz);
+      m = moments_walls<L, R>(f.v, drho, sx1, sy1, sz);
+    } else {
+      m = raw_moments<L, R>(f.v);
+    }
     if constexpr (decltype(Next)::value) {
       // the moments are pinned here, so that the pull can take the registers of f
       asm volatile("" : "+v"(m.d0), "+v"(m.jx), "+v"(m.jy), "+v"(m.jz), "+v"(m.pxx), "+v"(m.pyy), "+v"(m.pzz),
@@ -133,10 +177,21 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   };
   // population I arriving at the inner node
   auto arrived = [&](auto I) { return pop[I][r - L::cy(I)][lane + 1 - L::cx(I)]; };
-  // second step of plane z from its layer sums
-  auto second = [&](int z, const LayerSums<R>& lo, const LayerSums<R>& mid, const LayerSums<R>& up)
-      __attribute__((always_inline)) {
-    const Hydro<R> h = hydro<L, R>(join_layers<L>(lo, mid, up), rho0);
+  // second step of plane z from its layers
+  auto second = [&](int z, const Lo& lo, const Mid& mid, const Up& up) __attribute__((always_inline)) {
+    Moments<R> m;
+    if constexpr (W) {
+      R g[L::Q];
+      lo.put(g);
+      mid.put(g);
+      up.put(g);
+      const int sz = wall_side(a.walls, 2, z, a.nz);
+      const R drho = complete_walls<L, R>(g, sx2, sy2, sz);
+      m = moments_walls<L, R>(g, drho, sx2, sy2, sz);
+    } else {
+      m = join_layers<L, R>(lo, mid, up);
+    }
+    const Hydro<R> h = hydro<L, R>(m, rho0);
     R C[3][3][3], out[L::Q];
     coefficients<L, N, R>(h, om, C);
     reconstruct<L, N, R>(C, out);
@@ -151,16 +206,18 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   pull(wrap_axis(z0 - 1, a.nz), f.v);
   first(0, layer_p{}, std::true_type{});
   lds_barrier();
-  if (inner) up1 = layer_sums<L, 1, R>(arrived);
+  if (inner) up1.read(arrived);
   lds_barrier();
   for (int k = 1; k <= n; ++k) {
     first(k, all{}, std::true_type{});
     lds_barrier();
-    LayerSums<R> lo, mid, up;
+    Lo lo;
+    Mid mid;
+    Up up;
     if (inner) {
-      lo = layer_sums<L, -1, R>(arrived);
-      mid = layer_sums<L, 0, R>(arrived);
-      up = layer_sums<L, 1, R>(arrived);
+      lo.read(arrived);
+      mid.read(arrived);
+      up.read(arrived);
     }
     lds_barrier();
     if (inner) {
@@ -172,7 +229,11 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   }
   first(n + 1, layer_m{}, std::false_type{});
   lds_barrier();
-  if (inner) second(z1 - 1, layer_sums<L, -1, R>(arrived), mid2, up2);
+  if (inner) {
+    Lo lo;
+    lo.read(arrived);
+    second(z1 - 1, lo, mid2, up2);
+  }
 }
 
 // Two steps in 2D.  A block of kPairRowX threads runs the first step on a row of
@@ -271,6 +332,13 @@ __global__ void __launch_bounds__(kPairRowX) k_step_pair2(const S* __restrict__ 
   }
 }
 
+// Walled boxes: D3Q27 FP64 would spill 25-69 registers and ran slower than single
+// steps (256^3, walls along z: 12.7 -> 11.7 GLUPS), so it has no such form.
+template <class L, class S>
+constexpr bool pair_has_walls() {
+  return !(L::Q == 27 && sizeof(S) == 8);
+}
+
 // Tile heights the host chooses from (pair_plan in api.hip).  GLUPS at 256^3,
 // order 4, by rows: D3Q27 FP32 5 / 7 / 8 / 9 / 10 rows 40.4 / 38.7 / 43.6 / 40.6 / 31.9 (10 and
 // more rows spill: 128 VGPRs), D3Q19 FP32 5 / 8 / 9 / 11 / 13 rows 57.1 / 56.7 / 56.5 /
@@ -304,7 +372,15 @@ hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipSt
     const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
     const int64_t blocks = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
     if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_step_pair<L, N, S, TY>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+    if (a.walls) {
+      if constexpr (pair_has_walls<L, S>()) {
+        hipLaunchKernelGGL((k_step_pair<L, N, S, TY, true>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+                           static_cast<const S*>(src), static_cast<S*>(dst), a);
+        return hipGetLastError();
+      }
+      return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL((k_step_pair<L, N, S, TY, false>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
                        static_cast<const S*>(src), static_cast<S*>(dst), a);
     return hipGetLastError();
   }
@@ -333,7 +409,8 @@ hipError_t step_pair_by_order(int order, const void* src, void* dst, const StepA
 }
 
 template <class L>
-int pair_rows_of(int storage, int i) {
+int pair_rows_of(int storage, int i, bool walls) {
+  if (walls && !(storage == 0 ? pair_has_walls<L, double>() : pair_has_walls<L, float>())) return 0;
   return storage == 0 ? pair_rows_option<L, double>(i) : (storage == 1 ? pair_rows_option<L, float>(i) : 0);
 }
 

@@ -1,7 +1,7 @@
 """Launches of two population steps against single steps, bit for bit.
 
-lb_step may take steps two to a launch (FP64 and FP32 population storage; 3D without walls, 2D
-with or without); the single steps are held to the oracle elsewhere.  Boxes at the edges of the launch's tiles: one
+lb_step may take steps two to a launch (FP64 and FP32 population storage, with or without walls;
+D3Q27 FP64 with walls keeps single steps); the single steps are held to the oracle elsewhere.  Boxes at the edges of the launch's tiles: one
 node, fewer rows or planes than a tile, rows of 64 +- 1 nodes, chunk lengths that leave one
 plane over, both tile heights; every order.  LBRR_PAIR_LZ=0 gives the single steps.
 """
@@ -56,6 +56,24 @@ def test_own_choice_splits_and_checks(lbrr, gpu, storage, monkeypatch):
         got, steps = _run(lbrr, gpu, "D3Q27", shape, 4, storage, calls, check)
         assert steps == 23
         assert gpu.equal(got, want), (calls, check)
+
+
+@pytest.mark.parametrize("lattice,order", [("D3Q27", 2), ("D3Q27", 4), ("D3Q27", 6), ("D3Q19", 3), ("D3Q19", 4)])
+@pytest.mark.parametrize("storage", ["fp32", "fp64"])
+@pytest.mark.parametrize("walls", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 1)])
+def test_pairs_equal_single_steps_walls(lbrr, gpu, lattice, order, storage, walls, monkeypatch):
+    """Wall nodes, edges and corners in both steps of a launch, in the tile and on its rim."""
+    for shape in [(3, 3, 3), (7, 19, 65), (20, 14, 64)]:
+        monkeypatch.setenv("LBRR_PAIR_LZ", "0")
+        want, _ = _run(lbrr, gpu, lattice, shape, order, storage, [9], walls=walls)
+        for rows in ROWS[lattice, storage]:
+            for lz in (1, 5):
+                monkeypatch.setenv("LBRR_PAIR_LZ", str(lz))
+                monkeypatch.setenv("LBRR_PAIR_ROWS", str(rows))
+                got, steps = _run(lbrr, gpu, lattice, shape, order, storage, [9], walls=walls)
+                assert steps == 9
+                assert gpu.isfinite(got).all()
+                assert gpu.equal(got, want), (shape, rows, lz)
 
 
 @pytest.mark.parametrize("order", [2, 3, 4])
