@@ -41,8 +41,8 @@ def log(msg):
 
 
 # Sources of the D3Q27 step kernels: the counters stay valid while these are unchanged.
-STEP_SOURCES = ("lattice.hpp", "collide.hpp", "ops.hpp", "kernels.hpp", "mkernels.hpp", "ops_impl.hpp",
-                "kernels_d3q27.hip")
+STEP_SOURCES = ("lattice.hpp", "collide.hpp", "ops.hpp", "kernels.hpp", "tile.hpp", "pair.hpp", "mkernels.hpp",
+                "ops_impl.hpp", "kernels_d3q27.hip", "kernels_pair_d3q27.hip")
 
 
 def kernel_source_hash():
@@ -158,20 +158,29 @@ def device_record(torch):
 
 
 def kernel_resources(B, storage):
-    """Registers, scratch, LDS and occupancy of the D3Q27 order-4 step kernel of ``storage``, as the
-    compiler reported them when the library was built."""
-    name = {"fp32": "k_step<lbrr::D3Q27, 4, float>", "fp16": "k_stepINS_5D3Q27ELi4EDF16_",
-            "fp64": "k_step<lbrr::D3Q27, 4, double>", "mom_fp32": "k_mstep_t<lbrr::D3Q27, 4, float, 9, false>",
-            "mom_fp64": "k_mstep<lbrr::D3Q27, 4, double, 8, 32, false>"}[storage]
+    """Registers, scratch, LDS and occupancy of the D3Q27 order-4 step kernel that ``storage`` runs at
+    256^3 (FP32 and FP64: the launch of two steps), as the compiler reported them when the library was built."""
+    names = {"fp32": ("k_step_pair<lbrr::D3Q27, 4, float, 8, false>", "k_step<lbrr::D3Q27, 4, float>"),
+             "fp16": ("k_stepINS_5D3Q27ELi4EDF16_",),
+             "fp64": ("k_step_pair<lbrr::D3Q27, 4, double, 4, false>", "k_step<lbrr::D3Q27, 4, double>"),
+             "mom_fp32": ("k_mstep_t<lbrr::D3Q27, 4, float, 13, false>",),
+             "mom_fp64": ("k_mstep_t<lbrr::D3Q27, 4, double, 5, false>",)}[storage]
     try:
         with open(B.RESOURCES) as fh:
             res = json.load(fh)
     except (OSError, ValueError):
         return None
-    for k, v in res.items():
-        if name in k:
-            return {"kernel": k, **v}
+    for name in names:
+        for k, v in res.items():
+            if name in k:
+                return {"kernel": k, **v}
     return None
+
+
+def state_passes(storage, steps):
+    """Times lb_step reads and writes the whole state in one call of ``steps`` steps at 256^3: FP32 and FP64
+    populations are stepped two to a launch, in groups of four steps."""
+    return steps - 2 * (steps // 4) if storage in ("fp32", "fp64") else steps
 
 
 def copy_probe(P, torch, nbytes=2 << 30, reps=10):
@@ -371,7 +380,7 @@ def write_traffic(fetch_dir, write_dir, out_path):
         ks = [k for k in fetch if kern in k and "D3Q27" in k and tag in k and "4" in k]
         if not ks:
             continue
-        k = ks[0]
+        k = min(ks, key=lambda name: "k_step_pair" not in name)
         b = (fetch[k] * ff + write[k] * fw) * 1024.0
         alg = {"fp32": 216, "fp16": 108, "fp64": 432, "mom_fp32": 80, "mom_fp64": 160}[st] * nodes
         out[st] = {"kernel": k, "fetch_kib": fetch[k], "write_kib": write[k], "bytes_per_launch": round(b),
@@ -507,7 +516,12 @@ def main(argv=None):
     main_st = storages[0]
     r = results[main_st]
     nodes = n**3
-    achieved = r["bytes_per_update"] * nodes / (r["kernel_ms"] * 1e-3) / 1e9
+
+    def rate(st):  # GB/s of state read and written, algorithmic
+        v = results[st]
+        return v["bytes_per_update"] * nodes * state_passes(st, a.steps) / (v["kernel_ms"] * 1e-3 * a.steps) / 1e9
+
+    achieved = rate(main_st)
     traffic = measured_traffic(main_st)
     out = {
         "metric": METRIC,
@@ -530,9 +544,9 @@ def main(argv=None):
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic},
         "storage_rates": {st: {"glups": round(v["glups"], 3), "kernel_ms": round(v["kernel_ms"], 4),
-                               "hbm_frac": round(v["bytes_per_update"] * nodes / (v["kernel_ms"] * 1e-3) / 1e12
-                                                 / (HBM_PEAK_GBS / 1000), 4),
-                               "bytes_per_update": v["bytes_per_update"]} for st, v in results.items()},
+                               "hbm_frac": round(rate(st) / HBM_PEAK_GBS, 4),
+                               "bytes_per_update": v["bytes_per_update"],
+                               "state_passes": state_passes(st, a.steps)} for st, v in results.items()},
         "l2_err_u_vs_fp64": errs,
         "repeats": r.get("repeats"),
         "kernel_resources": kernel_resources(B, main_st),

@@ -50,6 +50,8 @@
  *                               0 and 2, rounded up to 256 (read at allocation)
  *      LBRR_MOM_LZ=n            z-planes (3D) or rows (2D) per block of the
  *                               moment-storage step, n >= 1 (read every step)
+ *      LBRR_MOM_ROWS=n          rows per block of the 3D moment-storage step, if built
+ *                               for n (read every step)
  *      LBRR_CLOSURE_WPR=1|2     waves per row of the fused closure step with
  *                               FP32 or FP16 storage (read every step)
  *      LBRR_PAIR_LZ=n           z-planes (2D: rows) per block of the launches that take two

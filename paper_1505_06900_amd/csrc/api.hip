@@ -52,110 +52,38 @@ size_t elem_size(int storage) {
   return 2;
 }
 
-// Chunk length of the moment-state step: rows per block in 2D, z-planes per
-// block in 3D (each block rebuilds lz + 2/3 planes' worth: the two planes next
-// to the chunk rebuild one layer).  Measured on MI355X:
-//   2D, rows of 256 nodes: 4 rows best (see kRowX).
-//   3D FP32 (row-aligned tiles of 64 x 9 nodes, x-neighbouring tiles on one
-//   XCD), D3Q27 order 4, GLUPS at lz = 9 / 12 / 16 / 24 / 32 / 43 / 64:
-//     256^3 49.1 / 51.5 / 51.0 / 53.4 / 53.4 / 53.9 / 54.4
-//     512^3 50.9 / 52.6 / 53.9 / 55.0 / 55.9 / 56.1 / 55.7
-//     D3Q19 order 4 512^3 (lz 9 / 12 / 16 / 24): 51.0 / 53.0 / 54.6 / 55.8
-//   Longer chunks re-read fewer edge planes but give fewer blocks, so the host
-//   takes the longest of 24, 16, 12, 9, 6, 4 planes that still gives four
-//   blocks per compute unit (at 256^3: 24 planes, 1408 blocks).
-//   3D FP64 (64 x 8 / 32 x 8 patches, k_mstep), lz = 3 / 4 / 6:
-//     D3Q27 256^3 20.8 / 21.4 / 22.0, 512^3 19.8 / 20.3 / 21.7; D3Q19 on
-//     planes of 448^2 nodes and more prefers 4.  So lz = 6 there, except 4 for
-//     D3Q19 on large planes.
-// LBRR_MOM_LZ overrides the choice.
-int moment_lz(int nvalues, int q, int nx, int ny, int nz, size_t es) {
-  if (const char* e = std::getenv("LBRR_MOM_LZ")) {
-    const int v = std::atoi(e);
-    if (v >= 1) return v;
-  }
-  if (nvalues == 6) return 4;
-  if (es == 4) {  // row-aligned tiles of 64 x kTileRows nodes, tile rows in groups of eight
-    int cus = 256;
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    for (int lz : {24, 16, 12, 9, 6}) {
-      const int64_t rows = int64_t((ny + lbrr::kTileRows - 1) / lbrr::kTileRows) * ((nz + lz - 1) / lz);
-      if (int64_t((nx + 63) / 64) * 8 * ((rows + 7) / 8) >= int64_t(4) * cus) return lz;
-    }
-    return 4;
-  }
-  if (q == 19 && int64_t(nx) * ny >= 448 * 448) return 4;
-  return 6;
-}
-
-// Tile height and chunk length of the step pair (k_step_pair, k_step_pair2);
-// lz = 0 where lb_step takes single steps.
-//
-// 2D: pairs at every size; short chunks while there are few blocks (a chunk is a
-// serial march), longer ones where their edge rows cost traffic.  us a step, order
-// 4, single / lz = 1 / 2 / 4 / 6 / 12:
-//   FP32   64^2  2.66 / 1.92 / 2.29 / 3.11 / 3.85 / 6.17    501^2  5.42 / 4.02 / 3.55 / 3.76 / 4.41 / 6.72
-//        1024^2 14.5 / 14.3 / 12.0 / 10.2 / 10.8 / 10.8    2048^2 49.9 / 43.8 / 36.1 / 33.8 / 33.8 / 34.3
-//   FP64  256^2  4.49 / 3.75 / 3.76 / 4.46 / 5.69 / 9.22    501^2  8.30 / 6.89 / 5.06 / 6.07 / 6.52 / 9.32
-//        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.1 / 62.3 / 60.9 / 62.7
-// (walled boxes within a few per cent of these: 501^2 FP64 8.51 / 7.16 / 5.22 / 5.86).
-//
-// 3D: a compute unit holds one block, a block's time grows with the planes it
-// rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are dealt
-// to the eight XCDs in turn, so the plan taken is the one with the smallest
-//   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
-// Measured (GLUPS, order 4, single steps -> pairs), cubes of side n:
-//            n = 256         320         200         128          64
-//   D3Q27 FP32 27.3 -> 44.1  27.0 -> 41.7  22.9 -> 33.1  26.4 -> 37.5  22.3 -> 30.9
-//   D3Q19 FP32 40.0 -> 61.5  39.1 -> 61.2  33.1 -> 49.3  38.0 -> 49.2  30.8 -> 35.3
-//   D3Q27 FP64 12.5 -> 21.6  11.7 -> 21.0  12.9 -> 17.9  13.0 -> 20.5  12.2 -> 16.5
-//   D3Q19 FP64 18.3 -> 33.0  17.2 -> 31.6  18.9 -> 25.7  18.6 -> 29.5  16.5 -> 23.7
-// Smaller boxes leave most compute units without a block, and the pair's march
-// along z is then longer than two single steps (D3Q27 FP32 48^3 13.7 -> 15.0, 36^3
-// 8.6 -> 8.0, 32^3 7.3 -> 5.9; D3Q19 FP32 48^3 18.2 -> 17.6, 24 x 24 x 330 20.3 -> 19.5):
-// pairs are taken where the state, weighted by the used share of a tile's 64
-// columns, has at least 6.5 MB, 20 MB with walls (single -> pairs, walls along z / on
-// all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
-// / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
-// LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
-struct PairPlan {
-  int rows = 0, lz = 0;
-};
-PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls) {
-  PairPlan p;
-  int forced_lz = -1, forced_rows = 0;
-  if (const char* e = std::getenv("LBRR_PAIR_LZ")) forced_lz = std::atoi(e);
-  if (const char* e = std::getenv("LBRR_PAIR_ROWS")) forced_rows = std::atoi(e);
+int compute_units() {
   int cus = 256;
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (ops.d == 2) {
-    p.rows = ops.pair_rows(storage, 0, walls);
-    if (p.rows == 0) return p;
-    if (forced_lz >= 0) {
-      p.lz = forced_lz;
-      return p;
-    }
-    const int64_t gx = (nx + 253) / 254;  // k_step_pair2: 254 columns a block
-    p.lz = 6;
-    for (int lz : {1, 2})
-      if (gx * ((ny + lz - 1) / lz) <= int64_t(3) * cus) {
-        p.lz = lz;
-        return p;
-      }
-    if (gx * ((ny + 3) / 4) <= int64_t(12) * cus) p.lz = 4;
-    return p;
-  }
-  const int64_t gx = (nx + 63) / 64;
-  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
-  if (forced_lz == 0 || (forced_lz < 0 && state < (walls ? 2e7 : 6.5e6))) return p;
-  const int64_t slots = cus / 8 > 0 ? cus / 8 : 1;
+  return cus;
+}
+
+int env_int(const char* name, int none) {
+  const char* e = std::getenv(name);
+  return e ? std::atoi(e) : none;
+}
+
+// Tile height and chunk length of a launch that marches in chunks (rows of a 2D
+// lattice, tiles of planes of a 3D one).
+struct TilePlan {
+  int rows = 0, lz = 0;
+};
+
+// 3D (tile.hpp): a compute unit holds one block, a block's time grows with the
+// planes it rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are
+// dealt to the eight XCDs in turn, so the plan taken is the one with the smallest
+//   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
+// forced_lz, forced_rows: > 0 overrides the choice (forced_rows if built).
+TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls, int forced_lz,
+                   int forced_rows) {
+  TilePlan p;
+  const int64_t gx = (nx + 63) / 64, slots = compute_units() / 8 > 0 ? compute_units() / 8 : 1;
   int64_t cost = 0;
-  bool listed = false;
-  for (int i = 0; const int rows = ops.pair_rows(storage, i, walls); ++i) listed = listed || rows == forced_rows;
-  for (int i = 0; const int rows = ops.pair_rows(storage, i, walls); ++i) {
-    if (listed && rows != forced_rows) continue;
+  bool built = false;
+  for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) built = built || rows == forced_rows;
+  for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) {
+    if (built && rows != forced_rows) continue;
     const int64_t gy = (ny + rows - 1) / rows;
     for (int chunks = 1; chunks <= nz; ++chunks) {
       const int lz = forced_lz > 0 ? forced_lz : (nz + chunks - 1) / chunks;
@@ -171,6 +99,63 @@ PairPlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
     }
   }
   return p;
+}
+
+// The step pair (k_step_pair, k_step_pair2); lz = 0 where lb_step takes single steps.
+//
+// 2D: pairs at every size; short chunks while there are few blocks (a chunk is a
+// serial march), longer ones where their edge rows cost traffic.  us a step, order
+// 4, single / lz = 1 / 2 / 4 / 6 / 12:
+//   FP32   64^2  2.66 / 1.92 / 2.29 / 3.11 / 3.85 / 6.17    501^2  5.42 / 4.02 / 3.55 / 3.76 / 4.41 / 6.72
+//        1024^2 14.5 / 14.3 / 12.0 / 10.2 / 10.8 / 10.8    2048^2 49.9 / 43.8 / 36.1 / 33.8 / 33.8 / 34.3
+//   FP64  256^2  4.49 / 3.75 / 3.76 / 4.46 / 5.69 / 9.22    501^2  8.30 / 6.89 / 5.06 / 6.07 / 6.52 / 9.32
+//        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.1 / 62.3 / 60.9 / 62.7
+// (walled boxes within a few per cent of these: 501^2 FP64 8.51 / 7.16 / 5.22 / 5.86).
+//
+// 3D (GLUPS, order 4, single steps -> pairs), cubes of side n:
+//            n = 256         320         200         128          64
+//   D3Q27 FP32 27.3 -> 44.1  27.0 -> 41.7  22.9 -> 33.1  26.4 -> 37.5  22.3 -> 30.9
+//   D3Q19 FP32 40.0 -> 61.5  39.1 -> 61.2  33.1 -> 49.3  38.0 -> 49.2  30.8 -> 35.3
+//   D3Q27 FP64 12.5 -> 21.6  11.7 -> 21.0  12.9 -> 17.9  13.0 -> 20.5  12.2 -> 16.5
+//   D3Q19 FP64 18.3 -> 33.0  17.2 -> 31.6  18.9 -> 25.7  18.6 -> 29.5  16.5 -> 23.7
+// Smaller boxes leave most compute units without a block, and the pair's march
+// along z is then longer than two single steps (D3Q27 FP32 48^3 13.7 -> 15.0, 36^3
+// 8.6 -> 8.0, 32^3 7.3 -> 5.9; D3Q19 FP32 48^3 18.2 -> 17.6, 24 x 24 x 330 20.3 -> 19.5):
+// pairs are taken where the state, weighted by the used share of a tile's 64
+// columns, has at least 6.5 MB, 20 MB with walls (single -> pairs, walls along z / on
+// all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
+// / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
+// LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
+TilePlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls) {
+  TilePlan p;
+  const int forced_lz = env_int("LBRR_PAIR_LZ", -1);
+  if (forced_lz == 0) return p;
+  if (ops.d == 2) {
+    p.rows = ops.tile_rows(storage, 0, walls);
+    if (p.rows == 0) return p;
+    const int64_t gx = (nx + 253) / 254, cus = compute_units();  // k_step_pair2: 254 columns a block
+    p.lz = forced_lz > 0 ? forced_lz : 0;
+    for (int lz : {1, 2})
+      if (p.lz == 0 && gx * ((ny + lz - 1) / lz) <= 3 * cus) p.lz = lz;
+    if (p.lz == 0) p.lz = gx * ((ny + 3) / 4) <= 12 * cus ? 4 : 6;
+    return p;
+  }
+  const int64_t gx = (nx + 63) / 64;
+  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
+  if (forced_lz < 0 && state < (walls ? 2e7 : 6.5e6)) return p;
+  return tile_plan(ops, storage, nx, ny, nz, walls, forced_lz, env_int("LBRR_PAIR_ROWS", 0));
+}
+
+// The moment-state step: four rows per block in 2D (see kRowX in mkernels.hpp), the
+// tile plan in 3D.  LBRR_MOM_LZ and LBRR_MOM_ROWS override the choice.
+TilePlan moment_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls) {
+  const int forced_lz = env_int("LBRR_MOM_LZ", 0);
+  if (ops.d == 2) {
+    TilePlan p;
+    p.lz = forced_lz > 0 ? forced_lz : 4;
+    return p;
+  }
+  return tile_plan(ops, storage, nx, ny, nz, walls, forced_lz, env_int("LBRR_MOM_ROWS", 0));
 }
 
 // Extra bytes after each population plane (layouts 0 and 2).  Planes whose
@@ -267,7 +252,7 @@ struct lb_ctx {
     a.sz = sz;
     a.rho0 = rho0;
     a.omega1 = 1.0 - 1.0 / tau;
-    a.lz = moment() ? moment_lz(nvalues(), q(), nx, ny, nz, elem_size(storage)) : 1;
+    a.lz = 1;
     a.rows = 0;
     a.walls = moment() ? walls : 0;
     return a;
@@ -558,7 +543,12 @@ int lb_step(lb_handle h, long long n) {
   if (!h->ready) return fail(LB_ERR_STATE, "lb_step before lb_init_fields / lb_set_populations");
   if (h->closure_on && h->moment()) return fail(LB_ERR_UNSUPPORTED, "the learned closure needs population storage");
   if (h->walls && h->closure_on) return fail(LB_ERR_UNSUPPORTED, "walls and the learned closure exclude each other");
-  const StepArgs a = h->args();
+  StepArgs a = h->args();
+  if (h->moment()) {
+    const TilePlan p = moment_plan(*h->ops, h->storage, h->nx, h->ny, h->nz, h->walls != 0);
+    a.rows = p.rows;
+    a.lz = p.lz;
+  }
   // Two steps in one launch where the population step has that form, always two
   // such launches at a time: every call then swaps the state buffers as often,
   // modulo 2, as single steps would (an even number of steps ends in the buffer
@@ -566,7 +556,7 @@ int lb_step(lb_handle h, long long n) {
   StepArgs ap = a;
   ap.lz = 0;
   if (n >= 4 && !h->moment() && !h->closure_on) {
-    const PairPlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz, h->walls != 0);
+    const TilePlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz, h->walls != 0);
     ap.rows = p.rows;
     ap.lz = p.lz;
     ap.walls = h->walls;

@@ -16,19 +16,24 @@
 // 3D fields: drho, jx, jy, jz, axx, ayy, azz, axy, axz, ayz; 2D: drho, jx,
 // jy, axx, ayy, axy.  FP64 or FP32; the collision runs in the same precision.
 //
-// Step kernel (3D): a block rebuilds the populations of an MX x TY patch of
-// nodes of one z-plane (64 x 8 in FP32, 32 x 8 in FP64: 55 KiB of LDS),
-// exchanges them through LDS, and the inner (MX-2) x (TY-2) nodes pull
-// theirs.  The block marches along z through a chunk of planes: the
-// populations rebuilt on plane p with c_z = -1, 0, +1 arrive on planes p-1,
-// p, p+1, so each inner thread keeps running moment sums for three target
-// planes, and plane p-1 is complete once plane p has been rebuilt.  A chunk of
-// lz target planes rebuilds lz + 2 planes; a patch rebuilds its one-node halo
-// ring as well.  The halo and chunk overlaps are the price of the 2.7x smaller
-// state: about 2 rebuilds per node update and about twice the algorithmic
-// bytes read, so the kernel is held by the rebuild arithmetic and by that
-// traffic together, not by the stored bytes.  The 2D step (k_mstep2) does the
-// same one dimension lower: a row of kRowX nodes marching along y.
+// Step kernel (3D, k_mstep_t): a block rebuilds the populations of a tile and its
+// rim (tile.hpp) plane by plane into LDS and marches along z; the populations
+// rebuilt on plane p with c_z = -1, 0, +1 arrive on planes p-1, p, p+1, and plane p-1 is
+// complete once plane p has been rebuilt.  A chunk of lz target planes rebuilds
+// lz + 2 planes.  The rim and chunk overlaps are the price of the 2.7x smaller state.
+// Bound: the rebuild's arithmetic (VALU about 60% busy) and the latency of the
+// march behind one block per compute unit.  GLUPS, order 4, before (9 x 64 tiles of 12
+// waves in FP32, 32 x 8 patches in FP64, fixed chunk lengths) and now:
+//             n = 256          320          200          128           64
+//   D3Q27 FP32  54.7 -> 59.0  54.9 -> 59.1  41.6 -> 48.9  38.0 -> 46.4  19.0 -> 25.1
+//   D3Q19 FP32  56.6 -> 60.5  57.0 -> 61.3  43.7 -> 50.7  39.0 -> 48.5  19.7 -> 27.4
+//   D3Q27 FP64  21.8 -> 27.6  20.4 -> 28.4  21.0 -> 23.5  18.7 -> 23.5  10.3 -> 16.3
+//   D3Q19 FP64  22.4 -> 30.0  21.8 -> 30.9  22.4 -> 25.2  19.0 -> 26.6  10.4 -> 17.7
+// What gave it: layer sums in place of running sums of three planes and two
+// planes in flight in place of three buffers leave room for 16 waves (114 VGPRs);
+// tile height and chunk length chosen together (tile_plan, api.hip).
+// The 2D step (k_mstep2) does the same one dimension lower: a row of kRowX nodes
+// marching along y.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -36,26 +41,13 @@
 #include <cstdint>
 #include <type_traits>
 
-#include "kernels.hpp"
+#include "tile.hpp"
 
 namespace lbrr {
 
 template <class L>
 constexpr int kNM = (L::D == 3) ? 10 : 6;
 
-// Patch of rebuilt nodes per block of the 3D step: MX x TY.  A row of the
-// patch is read as MX consecutive values of each field starting one node
-// before a tile, so it spans one 128-byte line more than it needs; 64 wide,
-// that is 3 lines for 62 outputs (FP32) instead of 2 for 30.  Measured,
-// D3Q27 FP32 (GLUPS, best chunk length): 32 x 16 patches 36.5 / 33.3 / 30.5
-// at 256^3 / 384^3 / 512^3 (the larger boxes only with contiguous tile
-// ranges per XCD, otherwise falling to 21-27 past a plane-size threshold),
-// 64 x 8 patches 37.1 / 39.8 / 40.8 at 6 planes per chunk in plain block
-// order, 64 x 16 (1024 threads) spills registers and ran 33.6-39.1.
-template <class S>
-struct MPatch {
-  static constexpr int MX = sizeof(S) == 4 ? 64 : 32, TY = 8;
-};
 constexpr int kPrefetch = 2;  // planes of moments in flight ahead of the rebuild
 
 // 2D: nodes per rebuilt row of a block.  Measured, D2Q9 order 4 FP32, GLUPS at
@@ -120,70 +112,6 @@ __device__ __forceinline__ void finalize_state(const Moments<R>& s, R rho0, R (&
 template <class R>
 __device__ __forceinline__ void clear(Moments<R>& s) {
   s.d0 = s.jx = s.jy = s.jz = s.pxx = s.pyy = s.pzz = s.pxy = s.pxz = s.pyz = R(0);
-}
-
-// Add the populations of the layer c_z = CZ that arrive at inner node (tx, ty)
-// to its moment sums s: population (cx, cy, CZ) comes from patch node
-// (tx - cx, ty - cy).  Sums along x, then y, then the c_z factors.
-template <class L, int CZ, int TY, int MX, class R, bool Assign = false>
-__device__ __forceinline__ void add_layer(Moments<R>& s, const R (*pop)[TY][MX], int tx, int ty) {
-  R r0[3], r1[3], r2[3];  // per row cy: sum of v, cx v, cx^2 v
-  sfor<0, 3>([&](auto Y) {
-    constexpr int cy = int(Y) - 1;
-    R v[3];
-    sfor<0, 3>([&](auto X) {
-      constexpr int cx = int(X) - 1;
-      if constexpr (has_velocity<L>(cx, cy, CZ)) v[X] = pop[velocity_index<L>(cx, cy, CZ)][ty - cy][tx - cx];
-      else v[X] = R(0);
-    });
-    constexpr bool side = has_velocity<L>(-1, cy, CZ);  // the +-1 entries come in pairs
-    if constexpr (side) {
-      const R e = v[2] + v[0];
-      r0[Y] = e + v[1];
-      r1[Y] = v[2] - v[0];
-      r2[Y] = e;
-    } else {
-      r0[Y] = v[1];
-      r1[Y] = R(0);
-      r2[Y] = R(0);
-    }
-  });
-  const R e0 = r0[2] + r0[0];
-  const R s00 = e0 + r0[1], s01 = r0[2] - r0[0], s02 = e0;
-  const R s10 = (r1[2] + r1[0]) + r1[1], s11 = r1[2] - r1[0];
-  const R s20 = (r2[2] + r2[0]) + r2[1];
-  if constexpr (Assign) {  // the first layer a target receives (c_z = +1) sets every sum
-    static_assert(CZ > 0, "assign with the c_z = +1 layer");
-    s.d0 = s00;
-    s.jx = s10;
-    s.jy = s01;
-    s.pxx = s20;
-    s.pyy = s02;
-    s.pxy = s11;
-    s.pzz = s00;
-    s.jz = s00;
-    s.pxz = s10;
-    s.pyz = s01;
-    return;
-  }
-  s.d0 = s.d0 + s00;
-  s.jx = s.jx + s10;
-  s.jy = s.jy + s01;
-  s.pxx = s.pxx + s20;
-  s.pyy = s.pyy + s02;
-  s.pxy = s.pxy + s11;
-  if constexpr (CZ != 0) {
-    s.pzz = s.pzz + s00;
-    if constexpr (CZ > 0) {
-      s.jz = s.jz + s00;
-      s.pxz = s.pxz + s10;
-      s.pyz = s.pyz + s01;
-    } else {
-      s.jz = s.jz - s00;
-      s.pxz = s.pxz - s10;
-      s.pyz = s.pyz - s01;
-    }
-  }
 }
 
 // 2D: add the populations with c_y = CY rebuilt on one row that arrive at
@@ -262,21 +190,6 @@ __device__ __forceinline__ void add_known(Moments<R>& s, R v, int cx, int cy, in
   s.pyz = s.pyz + R(cy * cz) * k;
 }
 
-// Wall node: the populations of layer c_z = CZ arriving at inner node (tx, ty).
-template <class L, int CZ, int TY, int MX, class R>
-__device__ __forceinline__ void add_layer_walls(Moments<R>& s, const R (*pop)[TY][MX], int tx, int ty, int sx, int sy,
-                                                int sz) {
-  sfor<0, 3>([&](auto Y) {
-    sfor<0, 3>([&](auto X) {
-      constexpr int cx = int(X) - 1, cy = int(Y) - 1;
-      if constexpr (has_velocity<L>(cx, cy, CZ)) {
-        if (!from_outside(sx, sy, sz, cx, cy, CZ))
-          add_known(s, pop[velocity_index<L>(cx, cy, CZ)][ty - cy][tx - cx], cx, cy, CZ, sx, sy, sz);
-      }
-    });
-  });
-}
-
 // 2D wall node: the populations with c_y = CY rebuilt on one row arriving at inner node tx.
 template <class L, int CY, int BX, class R>
 __device__ __forceinline__ void add_row_walls(Moments<R>& s, const R (*pop)[BX], int tx, int sx, int sy) {
@@ -323,217 +236,45 @@ __device__ __forceinline__ void finalize_walls(const Moments<R>& s, int sx, int 
   }
 }
 
-// One step of the moment-state update (see the file comment).
-template <class L, int N, class S, int TY, int MX, bool W>
-__global__ void __launch_bounds__(MX * TY) k_mstep(const S* __restrict__ src, S* __restrict__ dst, StepArgs a) {
+// v in a register of its own.
+__device__ __forceinline__ float copy_of(float v) {
+  float c;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(c) : "v"(v));
+  return c;
+}
+__device__ __forceinline__ double copy_of(double v) {
+  double c;
+  asm volatile("v_mov_b64 %0, %1" : "=v"(c) : "v"(v));
+  return c;
+}
+
+// One step of the moment-state update in 3D on the tiles of tile.hpp: the tile's and
+// the rim's populations are rebuilt from their moments plane by plane, and an
+// inner thread that has the three layers of its plane forms and stores the new
+// moments.  The moments of the next plane are loaded as soon as the present
+// ones are in the collision's registers.  W: resting walls on the axes of a.walls.
+template <class L, int N, class S, int TY, bool W>
+__global__ void __launch_bounds__(Tile<TY>::threads()) k_mstep_t(const S* __restrict__ src, S* __restrict__ dst,
+                                                                 StepArgs a) {
   static_assert(L::D == 3, "3D lattices; 2D runs k_mstep2");
   using R = S;
   constexpr int NM = kNM<L>;
-  __shared__ R pop[L::Q][TY][MX];
-  const int tx = threadIdx.x % MX, ty = threadIdx.x / MX;
-  const int gx = (a.nx + MX - 3) / (MX - 2), gy = (a.ny + TY - 3) / (TY - 2);
-  // tiles in x, then y, then the z-chunk
-  const int t = int(blockIdx.x);
-  const int bxi = t % gx, byi = (t / gx) % gy, bz = t / (gx * gy);
-  const int x0 = bxi * (MX - 2), y0 = byi * (TY - 2);
-  // the patch node this thread rebuilds, and the node it updates if inner
-  const int px = wrap_axis(x0 - 1 + tx, a.nx), py = wrap_axis(y0 - 1 + ty, a.ny);
-  const bool inner = tx >= 1 && tx <= MX - 2 && ty >= 1 && ty <= TY - 2 && x0 + tx - 1 < a.nx && y0 + ty - 1 < a.ny;
-  // Byte offsets of the node within its plane of one field (32 bits: the host
-  // checks that a plane fits); the plane and field bases are block-uniform, so
-  // each access is a scalar base plus one per-lane 32-bit offset.
-  const uint32_t off_in = uint32_t((int64_t(py) * a.sy + px) * int64_t(sizeof(S)));
-  const uint32_t off_out = uint32_t((int64_t(y0 + ty - 1) * a.sy + (x0 + tx - 1)) * int64_t(sizeof(S)));
+  __shared__ R pop[L::Q][Tile<TY>::kRows][Tile<TY>::kCols];
+  const Tile<TY> t(a);
+  if (t.empty) return;
+  // Byte offsets of the nodes within a plane of one field (the host checks that
+  // they fit 32 bits); plane and field bases are block-uniform.
+  const uint32_t off_in = uint32_t((int64_t(t.py) * a.sy + t.px) * int64_t(sizeof(S)));
+  const uint32_t off_out = t.inner ? uint32_t((int64_t(t.y) * a.sy + t.x) * int64_t(sizeof(S))) : 0u;
   const R rho0 = R(a.rho0), om = R(a.omega1);
-
-  auto load = [&](int z, R (&m)[NM]) {
-    const S* s = src + int64_t(z) * a.sz;
-    uint32_t o = off_in;
-    asm volatile("" : "+v"(o));  // keeps the scalar-base form of the accesses (see k_mstep_t)
-    sfor<0, NM>([&](auto C) { m[C] = at_offset(s + int64_t(C) * a.si, o); });
+  const int sx = W ? wall_side(a.walls, 0, t.x, a.nx) : 0, sy = W ? wall_side(a.walls, 1, t.y, a.ny) : 0;
+  struct Plane {  // a struct, as in k_step_pair
+    R v[NM];
   };
-  // Rebuild the populations of this thread's patch node into LDS; ZS selects
-  // all of them (2) or only those with c_z = ZS (the planes next to a chunk).
-  auto rebuild = [&](const R (&m)[NM], auto ZS) __attribute__((always_inline)) {
-    constexpr int Z = decltype(ZS)::value;
-    const Hydro<R> h = state_hydro<L, R>(m, rho0);
-    R C[3][3][3];
-    coefficients<L, N, R>(h, om, C);
-    R f[L::Q];
-    reconstruct<L, N, R, Z>(C, f);
-    sfor<0, L::Q>([&](auto I) {
-      if constexpr (Z == 2 || L::cz(I) == Z) pop[I][ty][tx] = f[I];
-    });
-  };
-  auto put = [&](int z, const R (&m)[NM]) {
-    S* d = dst + int64_t(z) * a.sz;
-    uint32_t o = off_out;
-    asm volatile("" : "+v"(o));
-    sfor<0, NM>([&](auto C) { __builtin_nontemporal_store(m[C], ptr_at_offset(d + int64_t(C) * a.si, o)); });
-  };
-  // walls (W): sides of this thread's target column and row; the side along z
-  // depends on the target plane
-  const int wsx = W ? wall_side(a.walls, 0, x0 + tx - 1, a.nx) : 0;
-  const int wsy = W ? wall_side(a.walls, 1, y0 + ty - 1, a.ny) : 0;
-  // Add layer c_z = CZ to the sums of target plane `target`; the c_z = +1 layer
-  // is the first a target receives and sets the sums.
-  auto add = [&](Moments<R>& sums, auto CZS, int target) __attribute__((always_inline)) {
-    constexpr int CZ = decltype(CZS)::value;
-    if constexpr (W) {
-      const int wsz = wall_side(a.walls, 2, target, a.nz);
-      if (wsx != 0 || wsy != 0 || wsz != 0) {
-        if constexpr (CZ > 0) clear(sums);
-        add_layer_walls<L, CZ, TY, MX, R>(sums, pop, tx, ty, wsx, wsy, wsz);
-        return;
-      }
-    }
-    add_layer<L, CZ, TY, MX, R, (CZ > 0)>(sums, pop, tx, ty);
-  };
-  auto finish = [&](const Moments<R>& sums, int target, R (&m)[NM]) __attribute__((always_inline)) {
-    if constexpr (W) {
-      const int wsz = wall_side(a.walls, 2, target, a.nz);
-      if (wsx != 0 || wsy != 0 || wsz != 0) {
-        finalize_walls<L, R>(sums, wsx, wsy, wsz, m);
-        return;
-      }
-    }
-    finalize_state<L, R>(sums, rho0, m);
-  };
-  using layer_m = std::integral_constant<int, -1>;
-  using layer_0 = std::integral_constant<int, 0>;
-  using layer_p = std::integral_constant<int, 1>;
-
-  {
-    // Target planes z0 .. z1-1; planes z0-1 .. z1 are rebuilt, plane k of the
-    // march being z0 - 1 + k (k = 0 .. n + 1, n = z1 - z0).  Plane 0 reaches only
-    // target z0 (its c_z = +1 populations) and plane n + 1 only target z1 - 1
-    // (c_z = -1), so those two rebuild a third of the populations and add one
-    // layer.  Plane k adds its c_z = +1 layer to target k (first contribution),
-    // c_z = 0 to target k - 1 and c_z = -1 to target k - 2, which is then
-    // complete.  Roles rotate with period 3: the moments of plane k sit in
-    // buffer k mod 3 (plane k + 2 is loaded into buffer (k + 2) mod 3 while plane
-    // k is rebuilt) and the sums of target j in T[j mod 3]; the march is unrolled
-    // by 3, so no register is copied between iterations.  The moments of a
-    // completed target are kept in registers and stored at the start of the next
-    // iteration, next to the prefetch: loads and stores then have one or more
-    // whole rebuilds to complete before they are waited for.
-    static_assert(kPrefetch == 2, "two planes in flight ahead of the rebuild");
-    const int z0 = bz * a.lz;
-    const int z1 = (z0 + a.lz < a.nz) ? z0 + a.lz : a.nz;
-    const int n = z1 - z0;
-    Moments<R> T[3];  // sums of targets j = k, k - 1, k - 2 (mod 3) at plane k
-    R B[3][NM];       // moments of planes k, k + 1, k + 2 (mod 3)
-    load(wrap_axis(z0 - 1, a.nz), B[0]);
-    load(wrap_axis(z0, a.nz), B[1]);
-    R out[NM];  // moments of target k - 3, stored during plane k
-    // E = 2: plane inside the chunk; +1: plane 0; -1: plane n + 1.  PH = k mod 3.
-    auto iteration = [&](int k, auto PHS, auto ES) __attribute__((always_inline)) {
-      constexpr int PH = decltype(PHS)::value, E = decltype(ES)::value;
-      constexpr int P1 = (PH + 2) % 3, P2 = (PH + 1) % 3;  // (k - 1) mod 3, (k - 2) mod 3
-      const int pz = z0 - 1 + k;
-      if (k + kPrefetch <= n + 1) load(wrap_axis(pz + kPrefetch, a.nz), B[P1]);  // buffer (k + 2) mod 3
-      if (inner && k >= 3) put(z0 + k - 3, out);
-      rebuild(B[PH], ES);
-      lds_barrier();
-      if (inner) {
-        if constexpr (E == 1) {
-          add(T[PH], layer_p{}, z0);  // target z0 (k = 0)
-        } else if constexpr (E == -1) {
-          add(T[P2], layer_m{}, z1 - 1);  // target n - 1 = k - 2 is complete
-          finish(T[P2], z1 - 1, out);
-        } else {
-          if (k < n) add(T[PH], layer_p{}, pz + 1);
-          add(T[P1], layer_0{}, pz);
-          if (k >= 2) {
-            add(T[P2], layer_m{}, pz - 1);
-            finish(T[P2], pz - 1, out);  // target k - 2 is complete
-          }
-        }
-      }
-      lds_barrier();
-    };
-    using ph0 = std::integral_constant<int, 0>;
-    using ph1 = std::integral_constant<int, 1>;
-    using ph2 = std::integral_constant<int, 2>;
-    using first_plane = std::integral_constant<int, 1>;
-    using inner_plane = std::integral_constant<int, 2>;
-    using last_plane = std::integral_constant<int, -1>;
-    iteration(0, ph0{}, first_plane{});
-    int k = 1;
-    for (; k + 2 <= n; k += 3) {
-      iteration(k, ph1{}, inner_plane{});
-      iteration(k + 1, ph2{}, inner_plane{});
-      iteration(k + 2, ph0{}, inner_plane{});
-    }
-    if (k <= n) iteration(k++, ph1{}, inner_plane{});  // k = 1 mod 3 here
-    if (k <= n) iteration(k++, ph2{}, inner_plane{});
-    // k = n + 1: the last plane
-    switch (k % 3) {
-      case 0: iteration(k, ph0{}, last_plane{}); break;
-      case 1: iteration(k, ph1{}, last_plane{}); break;
-      default: iteration(k, ph2{}, last_plane{}); break;
-    }
-    if (inner) put(z1 - 1, out);
-  }
-}
-
-// One step of the moment-state update with row-aligned tiles (3D, FP32).  The
-// inner tile of a block is 64 nodes of a row, starting at a multiple of 64,
-// by TY rows.  TY + 2 waves rebuild the tile's 64 columns on rows y0 - 1 ..
-// y0 + TY (one wave per row), and one more wave rebuilds the two halo columns
-// (x0 - 1 and the column right after the tile) of those rows, so every field
-// row is read as two whole 128-byte lines, and the halo lines are the first and
-// last lines of the neighbouring tiles.  A 256-node row takes four tiles.  The
-// march along z is that of k_mstep.  LDS holds the patch as TY + 2 rows of 66
-// columns: column 0 is the left halo, 1 .. width the tile, width + 1 the right
-// halo.
-template <class L, int N, class S, int TY, bool W>
-__global__ void __launch_bounds__(64 * (TY + 3)) k_mstep_t(const S* __restrict__ src, S* __restrict__ dst,
-                                                           StepArgs a) {
-  static_assert(L::D == 3, "3D lattices");
-  static_assert(2 * (TY + 2) <= 64, "the halo wave holds both halo columns of every patch row");
-  using R = S;
-  constexpr int NM = kNM<L>, RW = TY + 2, MXL = 66;
-  __shared__ R pop[L::Q][RW][MXL];
-  const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
-  // Blocks reach the eight XCDs round-robin by id, and each XCD has its own
-  // L2.  Blocks b and b + 8 (the same XCD, dispatched one after the other) take
-  // x-neighbouring tiles of one tile row (rows y0 .. y0 + TY - 1 of a z-chunk),
-  // so the halo columns a block reads are lines its XCD's L2 holds for the
-  // neighbour.  Tile rows g >= gy * gz of the last group of eight are empty.
-  const int gx = (a.nx + 63) / 64, gy = (a.ny + TY - 1) / TY, gz = (a.nz + a.lz - 1) / a.lz;
-  const int b = int(blockIdx.x);
-  const int bxi = (b / 8) % gx, g = (b / (8 * gx)) * 8 + b % 8;
-  if (g >= gy * gz) return;
-  const int byi = g % gy, bz = g / gy;
-  const int x0 = bxi * 64, y0 = byi * TY;
-  const int width = (a.nx - x0 < 64) ? a.nx - x0 : 64;
-  // The node this thread rebuilds: patch row r, LDS column col, lattice node (px, py).
-  int r, col, px;
-  bool writes;
-  if (wave < RW) {
-    r = wave;
-    writes = lane < width;
-    col = lane + 1;
-    px = x0 + (writes ? lane : 0);
-  } else {
-    const bool left = lane < RW;
-    writes = lane < 2 * RW;
-    r = left ? lane : (writes ? lane - RW : 0);
-    col = left ? 0 : width + 1;
-    px = wrap_axis(left ? x0 - 1 : x0 + width, a.nx);
-  }
-  const int py = wrap_axis(y0 - 1 + r, a.ny);
-  // the node this thread updates, if inner: (x0 + lane, y0 + r - 1), LDS (lane + 1, r)
-  const bool inner = wave < RW && r >= 1 && r <= TY && lane < width && y0 + r - 1 < a.ny;
-  const int tc = lane + 1;
-  const uint32_t off_in = uint32_t((int64_t(py) * a.sy + px) * int64_t(sizeof(S)));
-  const uint32_t off_out =
-      inner ? uint32_t((int64_t(y0 + r - 1) * a.sy + (x0 + lane)) * int64_t(sizeof(S))) : 0u;
-  const R rho0 = R(a.rho0), om = R(a.omega1);
-
-  auto load = [&](int z, R (&m)[NM]) {
-    const S* s = src + int64_t(z) * a.sz;
+  const int z0 = t.z0, z1 = t.z1, n = z1 - z0;
+  // moments of plane k of the march, z0 - 1 + k (past the last plane: the last again)
+  auto load = [&](int k, Plane& m) __attribute__((always_inline)) {
+    const S* s = src + int64_t(wrap_axis(z0 - 1 + (k < n + 1 ? k : n + 1), a.nz)) * a.sz;
     // The empty asm hides that the lane offset is the same in every plane of
     // the march.  Without it the compiler hoists a 64-bit copy of the offset
     // out of the loop and adds it to every field's base with a 64-bit lane
@@ -541,117 +282,90 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_mstep_t(const S* __restrict__
     // 32-bit lane offset) and the adds go away.
     uint32_t o = off_in;
     asm volatile("" : "+v"(o));
-    sfor<0, NM>([&](auto C) { m[C] = at_offset(s + int64_t(C) * a.si, o); });
+    sfor<0, NM>([&](auto C) { m.v[C] = at_offset(s + int64_t(C) * a.si, o); });
   };
-  auto rebuild = [&](const R (&m)[NM], auto ZS) __attribute__((always_inline)) {
+  // Planes z0 - 1 .. z1 are rebuilt (plane z0 - 1 + k, k = 0 .. n + 1), targets z0 ..
+  // z1 - 1: plane k brings layer c_z = +1 to target k, 0 to target k - 1, -1 to target
+  // k - 2, which is then complete.  The first and the last plane rebuild the one
+  // layer that reaches the chunk.
+  using Lo = Layer<L, -1, R, W>;
+  using Mid = Layer<L, 0, R, W>;
+  using Up = Layer<L, 1, R, W>;
+  Up up1, up2;  // c_z = +1 layers of targets k - 1 and k - 2
+  Mid mid2;     // c_z = 0 layer of target k - 2
+  // Populations of plane k from its moments m into LDS; m then takes plane k + 2.
+  auto rebuild = [&](int k, Plane& m, auto ZS) __attribute__((always_inline)) {
     constexpr int Z = decltype(ZS)::value;
-    const Hydro<R> h = state_hydro<L, R>(m, rho0);
-    R C[3][3][3];
+    // The moments move to registers of their own before the load takes theirs.
+    // Left to itself the compiler loads into other registers and copies them back
+    // at the end of the loop, which waits for the load there.
+    R own[NM];
+    sfor<0, NM>([&](auto C) { own[C] = copy_of(m.v[C]); });
+    if constexpr (Z != -1) load(k + 2, m);
+    const Hydro<R> h = state_hydro<L, R>(own, rho0);
+    R C[3][3][3], out[L::Q];
     coefficients<L, N, R>(h, om, C);
-    R f[L::Q];
-    reconstruct<L, N, R, Z>(C, f);
-    if (writes) {
+    reconstruct<L, N, R, Z>(C, out);
+    if (t.writes) {
       sfor<0, L::Q>([&](auto I) {
-        if constexpr (Z == 2 || L::cz(I) == Z) pop[I][r][col] = f[I];
+        if constexpr (Z == 2 || L::cz(I) == Z) pop[I][t.r][t.col] = out[I];
       });
     }
   };
-  auto put = [&](int z, const R (&m)[NM]) {
+  auto arrived = [&](auto I) { return pop[I][t.r - L::cy(I)][t.lane + 1 - L::cx(I)]; };
+  auto finish = [&](int z, const Lo& lo, const Mid& mid, const Up& up) __attribute__((always_inline)) {
+    R m[NM];
+    finalize_state<L, R>(layer_moments<L, R, W>(lo, mid, up, sx, sy, W ? wall_side(a.walls, 2, z, a.nz) : 0), rho0, m);
     S* d = dst + int64_t(z) * a.sz;
     uint32_t o = off_out;
     asm volatile("" : "+v"(o));
     sfor<0, NM>([&](auto C) { __builtin_nontemporal_store(m[C], ptr_at_offset(d + int64_t(C) * a.si, o)); });
   };
-  const int wsx = W ? wall_side(a.walls, 0, x0 + lane, a.nx) : 0;
-  const int wsy = W ? wall_side(a.walls, 1, y0 + r - 1, a.ny) : 0;
-  auto add = [&](Moments<R>& sums, auto CZS, int target) __attribute__((always_inline)) {
-    constexpr int CZ = decltype(CZS)::value;
-    if constexpr (W) {
-      const int wsz = wall_side(a.walls, 2, target, a.nz);
-      if (wsx != 0 || wsy != 0 || wsz != 0) {
-        if constexpr (CZ > 0) clear(sums);
-        add_layer_walls<L, CZ, RW, MXL, R>(sums, pop, tc, r, wsx, wsy, wsz);
-        return;
-      }
-    }
-    add_layer<L, CZ, RW, MXL, R, (CZ > 0)>(sums, pop, tc, r);
-  };
-  auto finish = [&](const Moments<R>& sums, int target, R (&m)[NM]) __attribute__((always_inline)) {
-    if constexpr (W) {
-      const int wsz = wall_side(a.walls, 2, target, a.nz);
-      if (wsx != 0 || wsy != 0 || wsz != 0) {
-        finalize_walls<L, R>(sums, wsx, wsy, wsz, m);
-        return;
-      }
-    }
-    finalize_state<L, R>(sums, rho0, m);
-  };
+  using all = std::integral_constant<int, 2>;
   using layer_m = std::integral_constant<int, -1>;
-  using layer_0 = std::integral_constant<int, 0>;
   using layer_p = std::integral_constant<int, 1>;
-  {
-    // The march of k_mstep: targets z0 .. z1 - 1, planes z0 - 1 .. z1 rebuilt,
-    // register roles rotating with period 3, the two edge planes rebuilding
-    // only the layer that reaches the chunk.
-    static_assert(kPrefetch == 2, "two planes in flight ahead of the rebuild");
-    const int z0 = bz * a.lz;
-    const int z1 = (z0 + a.lz < a.nz) ? z0 + a.lz : a.nz;
-    const int n = z1 - z0;
-    Moments<R> T[3];
-    R B[3][NM];
-    load(wrap_axis(z0 - 1, a.nz), B[0]);
-    load(wrap_axis(z0, a.nz), B[1]);
-    // a completed target is stored at once (with 1024 threads a block has 128
-    // VGPRs per lane, and holding it for the next iteration spilled)
-    auto complete = [&](const Moments<R>& sums, int target) __attribute__((always_inline)) {
-      R out[NM];
-      finish(sums, target, out);
-      put(target, out);
-    };
-    auto iteration = [&](int k, auto PHS, auto ES) __attribute__((always_inline)) {
-      constexpr int PH = decltype(PHS)::value, E = decltype(ES)::value;
-      constexpr int P1 = (PH + 2) % 3, P2 = (PH + 1) % 3;
-      const int pz = z0 - 1 + k;
-      if (k + kPrefetch <= n + 1) load(wrap_axis(pz + kPrefetch, a.nz), B[P1]);
-      rebuild(B[PH], ES);
-      lds_barrier();
-      if (inner) {
-        if constexpr (E == 1) {
-          add(T[PH], layer_p{}, z0);
-        } else if constexpr (E == -1) {
-          add(T[P2], layer_m{}, z1 - 1);
-          complete(T[P2], z1 - 1);
-        } else {
-          if (k < n) add(T[PH], layer_p{}, pz + 1);
-          add(T[P1], layer_0{}, pz);
-          if (k >= 2) {
-            add(T[P2], layer_m{}, pz - 1);
-            complete(T[P2], pz - 1);
-          }
-        }
-      }
-      lds_barrier();
-    };
-    using ph0 = std::integral_constant<int, 0>;
-    using ph1 = std::integral_constant<int, 1>;
-    using ph2 = std::integral_constant<int, 2>;
-    using first_plane = std::integral_constant<int, 1>;
-    using inner_plane = std::integral_constant<int, 2>;
-    using last_plane = std::integral_constant<int, -1>;
-    iteration(0, ph0{}, first_plane{});
-    int k = 1;
-    for (; k + 2 <= n; k += 3) {
-      iteration(k, ph1{}, inner_plane{});
-      iteration(k + 1, ph2{}, inner_plane{});
-      iteration(k + 2, ph0{}, inner_plane{});
+  // A completed plane is stored before the barrier that frees the LDS (after it,
+  // as in k_step_pair: 53 -> 46 GLUPS with 9 rows, D3Q27 FP32 256^3).
+  auto inside = [&](int k, Plane& m) __attribute__((always_inline)) {
+    rebuild(k, m, all{});
+    lds_barrier();
+    if (t.inner) {
+      Lo lo;
+      Mid mid;
+      Up up;
+      lo.read(arrived);
+      mid.read(arrived);
+      up.read(arrived);
+      if (k >= 2) finish(z0 + k - 2, lo, mid2, up2);
+      up2 = up1;
+      mid2 = mid;
+      up1 = up;
     }
-    if (k <= n) iteration(k++, ph1{}, inner_plane{});
-    if (k <= n) iteration(k++, ph2{}, inner_plane{});
-    switch (k % 3) {
-      case 0: iteration(k, ph0{}, last_plane{}); break;
-      case 1: iteration(k, ph1{}, last_plane{}); break;
-      default: iteration(k, ph2{}, last_plane{}); break;
-    }
+    lds_barrier();
+  };
+  Plane even, odd;  // the planes in flight: two ahead of the rebuild
+  load(0, even);
+  load(1, odd);
+  rebuild(0, even, layer_p{});
+  lds_barrier();
+  if (t.inner) up1.read(arrived);
+  lds_barrier();
+  int k = 1;
+  for (; k + 1 <= n; k += 2) {
+    inside(k, odd);
+    inside(k + 1, even);
+  }
+  if (k <= n) {
+    inside(k, odd);
+    rebuild(n + 1, even, layer_m{});
+  } else {
+    rebuild(n + 1, odd, layer_m{});
+  }
+  lds_barrier();
+  if (t.inner) {
+    Lo lo;
+    lo.read(arrived);
+    finish(z1 - 1, lo, mid2, up2);
   }
 }
 
@@ -871,6 +585,30 @@ __global__ void __launch_bounds__(256) k_mpopulations(const S* __restrict__ src,
 // to 32; padding the z-planes off multiples of 64 KiB changed nothing;
 // contiguous tile ranges per XCD removed the fall-off at large planes but did
 // not beat the 64 x 8 patches in plain order.
+// Tile heights of the 3D step the host chooses from (tile_plan in api.hip).  GLUPS
+// at 256^3, order 4, by rows: D3Q27 FP32 5 / 8 / 9 / 11 / 13 rows 52.6 / 56.6 / 54.1 / 56.3 /
+// 58.8, D3Q19 FP32 51.9 / 58.8 / 56.1 / 61.6 / 59.7, D3Q27 FP64 3 / 4 / 5 rows 23.5 / 27.0 /
+// 27.5 (6 rows spill: 12.7), D3Q19 FP64 26.0 / 30.0 / 30.1.  The lower tiles serve boxes whose rows
+// the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).
+template <class S>
+constexpr int mom_rows_option(int i) {
+  constexpr int f32[] = {13, 11, 8}, f64[] = {5, 4};
+  return sizeof(S) == 8 ? (i < 2 ? f64[i] : 0) : (i < 3 ? f32[i] : 0);
+}
+
+template <class L, int N, class S, int TY>
+hipError_t launch_mstep_t(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
+  const int64_t blocks = Tile<TY>::blocks(a);
+  if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  if (a.walls)
+    hipLaunchKernelGGL((k_mstep_t<L, N, S, TY, true>), dim3(unsigned(blocks)), dim3(Tile<TY>::threads()), 0, s,
+                       static_cast<const S*>(src), static_cast<S*>(dst), a);
+  else
+    hipLaunchKernelGGL((k_mstep_t<L, N, S, TY, false>), dim3(unsigned(blocks)), dim3(Tile<TY>::threads()), 0, s,
+                       static_cast<const S*>(src), static_cast<S*>(dst), a);
+  return hipGetLastError();
+}
+
 template <class L, int N, class S>
 hipError_t launch_mstep(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
   if (a.lz < 1) return hipErrorInvalidValue;
@@ -886,30 +624,12 @@ hipError_t launch_mstep(const void* src, void* dst, const StepArgs& a, hipStream
     return hipGetLastError();
   } else {
     if (int64_t(a.ny) * a.sy * int64_t(sizeof(S)) >= (int64_t(1) << 32)) return hipErrorInvalidValue;
-    if constexpr (sizeof(S) == 4) {
-      constexpr int TY = kTileRows;
-      const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
-      const int64_t nbt = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
-      if (nbt >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-      if (a.walls)
-        hipLaunchKernelGGL((k_mstep_t<L, N, S, TY, true>), dim3(unsigned(nbt)), dim3(64 * (TY + 3)), 0, s,
-                           static_cast<const S*>(src), static_cast<S*>(dst), a);
-      else
-        hipLaunchKernelGGL((k_mstep_t<L, N, S, TY, false>), dim3(unsigned(nbt)), dim3(64 * (TY + 3)), 0, s,
-                           static_cast<const S*>(src), static_cast<S*>(dst), a);
-      return hipGetLastError();
+    if (a.rows == mom_rows_option<S>(0)) return launch_mstep_t<L, N, S, mom_rows_option<S>(0)>(src, dst, a, s);
+    if (a.rows == mom_rows_option<S>(1)) return launch_mstep_t<L, N, S, mom_rows_option<S>(1)>(src, dst, a, s);
+    if constexpr (mom_rows_option<S>(2) != 0) {
+      if (a.rows == mom_rows_option<S>(2)) return launch_mstep_t<L, N, S, mom_rows_option<S>(2)>(src, dst, a, s);
     }
-    constexpr int TY = MPatch<S>::TY, MX = MPatch<S>::MX;
-    const int64_t nb = int64_t((a.nx + MX - 3) / (MX - 2)) * ((a.ny + TY - 3) / (TY - 2)) *
-                       ((a.nz + a.lz - 1) / a.lz);
-    if (nb >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    if (a.walls)
-      hipLaunchKernelGGL((k_mstep<L, N, S, TY, MX, true>), dim3(unsigned(nb)), dim3(MX * TY), 0, s,
-                         static_cast<const S*>(src), static_cast<S*>(dst), a);
-    else
-      hipLaunchKernelGGL((k_mstep<L, N, S, TY, MX, false>), dim3(unsigned(nb)), dim3(MX * TY), 0, s,
-                         static_cast<const S*>(src), static_cast<S*>(dst), a);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
   }
 }
 

@@ -9,12 +9,6 @@
 namespace lbrr {
 
 constexpr int kReduceBlock = 256;
-// Inner rows of a row-aligned tile of the 3D FP32 moment step (k_mstep_t):
-// TY + 3 waves per block.  9 rows, 12 waves: no spills (D3Q27 order 4: 123
-// VGPRs, one block per CU); 13 rows, 16 waves (1024 threads, 128 VGPRs per
-// lane) spilled 11-18 VGPRs.
-constexpr int kTileRows = 9;
-
 // Launch parameters shared by the kernels.  Population (or moment field) i of node (x, y, z)
 // lives at element i*si + z*sz + y*sy + x of a buffer; the host picks the
 // strides (layout) and checks that every index stays inside the allocation.
@@ -24,17 +18,18 @@ struct StepArgs {
   double rho0;         // reference density of the deviation storage
   double omega1;       // 1 - 1/tau
   int lz;              // z-planes (2D: rows) per block of the moment-state step and of the step pair
-  int rows;            // rows of a tile of the step pair
+  int rows;            // rows of a tile of the 3D moment step and of the step pair
   int walls;           // moment-state step and step pair: resting walls on the axes of this mask (bit 0 x, 1 y, 2 z)
 };
 
 struct LatticeOps {
   int q, d, nmax;
   hipError_t (*step)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
-  // two steps in one launch (population storage FP64 and FP32); pair_rows: the i-th tile height it is built for, 0
-  // past the last and where there is no such kernel
+  // two steps in one launch (population storage FP64 and FP32)
   hipError_t (*step_pair)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);
-  int (*pair_rows)(int storage, int i, bool walls);
+  // the i-th tile height the step pair (moment storage: the 3D step) is built for, 0 past the last and where there
+  // is no such kernel
+  int (*tile_rows)(int storage, int i, bool walls);
   hipError_t (*init)(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1, void* dst,
                      const StepArgs& a, hipStream_t s);
   hipError_t (*moments)(int storage, int dtype, const void* src, void* rho, void* u, void* pi1, const StepArgs& a,

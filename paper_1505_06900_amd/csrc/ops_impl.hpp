@@ -69,7 +69,8 @@ struct OpsImpl {
     }
     return hipErrorInvalidValue;
   }
-  static int pair_rows(int storage, int i, bool walls) {
+  static int tile_rows(int storage, int i, bool walls) {
+    if (is_moment_storage(storage)) return L::D == 2 ? 0 : (storage == 3 ? mom_rows_option<double>(i) : mom_rows_option<float>(i));
     return pair_rows_of<L>(storage, i, walls);
   }
   static hipError_t init(int order, int storage, int dtype, const void* rho, const void* u, const void* pi1,
@@ -142,7 +143,7 @@ struct OpsImpl {
     return hipErrorInvalidValue;
   }
   static const LatticeOps& table() {
-    static const LatticeOps t = {L::Q, L::D, L::NMAX, &step, &step_pair, &pair_rows, &init, &moments, &totals, &velocity, &repack,
+    static const LatticeOps t = {L::Q, L::D, L::NMAX, &step, &step_pair, &tile_rows, &init, &moments, &totals, &velocity, &repack,
                                  &mpopulations, &step_walls};
     return t;
   }

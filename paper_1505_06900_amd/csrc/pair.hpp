@@ -24,102 +24,41 @@
 #include <cstdint>
 #include <type_traits>
 
-#include "kernels.hpp"
+#include "tile.hpp"
 
 namespace lbrr {
 
-// Tile of a block: 64 columns (a row segment starting at a multiple of 64) by
-// TY rows, marching along z through a chunk of a.lz planes.  TY + 2 waves run
-// the first step on the tile's 64 columns of rows y0 - 1 .. y0 + TY (a wave per
-// row) and one more wave on the two columns beside the tile.  The first step's
-// populations on plane p with c_z = +1, 0, -1 arrive on planes p + 1, p, p - 1:
-// an inner thread keeps the layer sums of the planes it is waiting for
-// (LayerSums, 6 values a layer) and collides plane p - 1 when the c_z = -1
-// layer of plane p is there.  The pull of the next plane is issued as soon as
-// the moments of the present one are formed, and is in flight through both
-// collisions.
-//
-// W: resting walls on the axes of a.walls.  A wall node is completed from its
-// populations one by one, so the thread then keeps the arrivals themselves
-// (LayerValues) in place of their sums.
-template <class L, int CZ, class R>
-struct LayerValues {
-  R v[9];  // [c_x + 1 + 3 (c_y + 1)], the velocities the lattice has
-  template <class G>
-  __device__ __forceinline__ void read(G&& get) {
-    sfor<0, 9>([&](auto K) {
-      constexpr int i = velocity_index<L>(int(K) % 3 - 1, int(K) / 3 - 1, CZ);
-      if constexpr (i >= 0) v[K] = get(std::integral_constant<int, i>{});
-    });
-  }
-  __device__ __forceinline__ void put(R (&f)[L::Q]) const {
-    sfor<0, 9>([&](auto K) {
-      constexpr int i = velocity_index<L>(int(K) % 3 - 1, int(K) / 3 - 1, CZ);
-      if constexpr (i >= 0) f[i] = v[K];
-    });
-  }
-};
-template <class L, int CZ, class R>
-struct LayerTotals : LayerSums<R> {
-  template <class G>
-  __device__ __forceinline__ void read(G&& get) {
-    static_cast<LayerSums<R>&>(*this) = layer_sums<L, CZ, R>(get);
-  }
-};
-
+// Two steps in 3D on the tiles of tile.hpp.  The first step runs on the tile and
+// its rim; its populations on plane p with c_z = +1, 0, -1 arrive on planes p + 1,
+// p, p - 1: an inner thread keeps the layers of the planes it is waiting for and
+// collides plane p - 1 when the c_z = -1 layer of plane p is there.  The pull of the
+// next plane is issued as soon as the moments of the present one are formed, and
+// is in flight through both collisions; the second collision follows the barrier
+// that frees the LDS (before it: 44.1 -> 42.3 GLUPS, D3Q27 FP32 256^3).  W: resting
+// walls on the axes of a.walls.
 template <class L, int N, class S, int TY, bool W>
-__global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict__ src, S* __restrict__ dst,
+__global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __restrict__ src, S* __restrict__ dst,
                                                              StepArgs a) {
   static_assert(L::D == 3, "3D lattices");
-  static_assert(2 * (TY + 2) <= 64, "one wave holds both rim columns of every patch row");
   using R = S;
-  constexpr int RW = TY + 2, MXL = 66;
-  __shared__ R pop[L::Q][RW][MXL];
-  const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  // Blocks reach the eight XCDs round-robin by id, and each XCD has its own
-  // L2: blocks b and b + 8 take x-neighbouring tiles of one tile row, so the rim
-  // columns a block reads are lines its XCD's L2 holds for the neighbour.  Tile
-  // rows past the last of a group of eight are empty.
-  const int gx = (a.nx + 63) / 64, gy = (a.ny + TY - 1) / TY, gz = (a.nz + a.lz - 1) / a.lz;
-  const int b = int(blockIdx.x);
-  const int bxi = (b / 8) % gx, g = (b / (8 * gx)) * 8 + b % 8;
-  if (g >= gy * gz) return;
-  const int byi = g % gy, bz = g / gy;
-  const int x0 = bxi * 64, y0 = byi * TY;
-  const int width = (a.nx - x0 < 64) ? a.nx - x0 : 64;
-  // the node of the first step: patch row r, LDS column col, lattice node (px, py)
-  int r, col, px;
-  bool writes;
-  if (wave < RW) {
-    r = wave;
-    writes = lane < width;
-    col = lane + 1;
-    px = x0 + (writes ? lane : 0);
-  } else {
-    const bool left = lane < RW;
-    writes = lane < 2 * RW;
-    r = left ? lane : (writes ? lane - RW : 0);
-    col = left ? 0 : width + 1;
-    px = wrap_axis(left ? x0 - 1 : x0 + width, a.nx);
-  }
-  const int py = wrap_axis(y0 - 1 + r, a.ny);
-  // the node of the second step: (x0 + lane, y0 + r - 1), LDS column lane + 1
-  const bool inner = wave < RW && r >= 1 && r <= TY && lane < width && y0 + r - 1 < a.ny;
+  __shared__ R pop[L::Q][Tile<TY>::kRows][Tile<TY>::kCols];
+  const Tile<TY> t(a);
+  if (t.empty) return;
   // Byte offsets of the nodes populations come from, within a plane of one
   // population (the host checks that it fits 32 bits); plane and population
   // bases are block-uniform.
+  const int px = t.px, py = t.py, r = t.r, lane = t.lane;
   const int xs[3] = {px == a.nx - 1 ? 0 : px + 1, px, px == 0 ? a.nx - 1 : px - 1};
   const int ys[3] = {py == a.ny - 1 ? 0 : py + 1, py, py == 0 ? a.ny - 1 : py - 1};
   uint32_t off[3][3];  // [c_y + 1][c_x + 1]
   sfor<0, 3>([&](auto Y) {
     sfor<0, 3>([&](auto X) { off[Y][X] = uint32_t((int64_t(ys[Y]) * a.sy + xs[X]) * int64_t(sizeof(S))); });
   });
-  const uint32_t off_out =
-      inner ? uint32_t((int64_t(y0 + r - 1) * a.sy + (x0 + lane)) * int64_t(sizeof(S))) : 0u;
+  const uint32_t off_out = t.inner ? uint32_t((int64_t(t.y) * a.sy + t.x) * int64_t(sizeof(S))) : 0u;
   const R rho0 = R(a.rho0), om = R(a.omega1);
   // sides of the box of the first and the second node
   const int sx1 = W ? wall_side(a.walls, 0, px, a.nx) : 0, sy1 = W ? wall_side(a.walls, 1, py, a.ny) : 0;
-  const int sx2 = W ? wall_side(a.walls, 0, x0 + lane, a.nx) : 0, sy2 = W ? wall_side(a.walls, 1, y0 + r - 1, a.ny) : 0;
+  const int sx2 = W ? wall_side(a.walls, 0, t.x, a.nx) : 0, sy2 = W ? wall_side(a.walls, 1, t.y, a.ny) : 0;
 
   auto pull = [&](int z, R (&f)[L::Q]) __attribute__((always_inline)) {
     const int zs[3] = {z == a.nz - 1 ? 0 : z + 1, z, z == 0 ? a.nz - 1 : z - 1};
@@ -133,18 +72,16 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
     });
   };
 
-  const int z0 = bz * a.lz;
-  const int z1 = (z0 + a.lz < a.nz) ? z0 + a.lz : a.nz;
-  const int n = z1 - z0;
+  const int z0 = t.z0, z1 = t.z1, n = z1 - z0;
   // First-step planes z0 - 1 .. z1 (plane z0 - 1 + k, k = 0 .. n + 1), targets
   // z0 .. z1 - 1: plane k brings layer c_z = +1 to target k, 0 to target k - 1,
   // -1 to target k - 2, which is then complete.
   struct {  // a struct: a plain array carried around the loop ends in one 32-register tuple, copied whole
     R v[L::Q];
   } f;
-  using Lo = std::conditional_t<W, LayerValues<L, -1, R>, LayerTotals<L, -1, R>>;
-  using Mid = std::conditional_t<W, LayerValues<L, 0, R>, LayerTotals<L, 0, R>>;
-  using Up = std::conditional_t<W, LayerValues<L, 1, R>, LayerTotals<L, 1, R>>;
+  using Lo = Layer<L, -1, R, W>;
+  using Mid = Layer<L, 0, R, W>;
+  using Up = Layer<L, 1, R, W>;
   Up up1, up2;  // c_z = +1 layers of targets k - 1 and k - 2
   Mid mid2;     // c_z = 0 layer of target k - 2
   // First step of plane k into LDS; ZS selects all populations (2) or those
@@ -169,9 +106,9 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
     R C[3][3][3], out[L::Q];
     coefficients<L, N, R>(h, om, C);
     reconstruct<L, N, R, Z>(C, out);
-    if (writes) {
+    if (t.writes) {
       sfor<0, L::Q>([&](auto I) {
-        if constexpr (Z == 2 || L::cz(I) == Z) pop[I][r][col] = out[I];
+        if constexpr (Z == 2 || L::cz(I) == Z) pop[I][r][t.col] = out[I];
       });
     }
   };
@@ -179,18 +116,8 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   auto arrived = [&](auto I) { return pop[I][r - L::cy(I)][lane + 1 - L::cx(I)]; };
   // second step of plane z from its layers
   auto second = [&](int z, const Lo& lo, const Mid& mid, const Up& up) __attribute__((always_inline)) {
-    Moments<R> m;
-    if constexpr (W) {
-      R g[L::Q];
-      lo.put(g);
-      mid.put(g);
-      up.put(g);
-      const int sz = wall_side(a.walls, 2, z, a.nz);
-      const R drho = complete_walls<L, R>(g, sx2, sy2, sz);
-      m = moments_walls<L, R>(g, drho, sx2, sy2, sz);
-    } else {
-      m = join_layers<L, R>(lo, mid, up);
-    }
+    const int sz2 = W ? wall_side(a.walls, 2, z, a.nz) : 0;
+    const Moments<R> m = layer_moments<L, R, W>(lo, mid, up, sx2, sy2, sz2);
     const Hydro<R> h = hydro<L, R>(m, rho0);
     R C[3][3][3], out[L::Q];
     coefficients<L, N, R>(h, om, C);
@@ -206,7 +133,7 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   pull(wrap_axis(z0 - 1, a.nz), f.v);
   first(0, layer_p{}, std::true_type{});
   lds_barrier();
-  if (inner) up1.read(arrived);
+  if (t.inner) up1.read(arrived);
   lds_barrier();
   for (int k = 1; k <= n; ++k) {
     first(k, all{}, std::true_type{});
@@ -214,13 +141,13 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
     Lo lo;
     Mid mid;
     Up up;
-    if (inner) {
+    if (t.inner) {
       lo.read(arrived);
       mid.read(arrived);
       up.read(arrived);
     }
     lds_barrier();
-    if (inner) {
+    if (t.inner) {
       if (k >= 2) second(z0 + k - 2, lo, mid2, up2);
       up2 = up1;
       mid2 = mid;
@@ -229,7 +156,7 @@ __global__ void __launch_bounds__(64 * (TY + 3)) k_step_pair(const S* __restrict
   }
   first(n + 1, layer_m{}, std::false_type{});
   lds_barrier();
-  if (inner) {
+  if (t.inner) {
     Lo lo;
     lo.read(arrived);
     second(z1 - 1, lo, mid2, up2);
@@ -369,18 +296,17 @@ hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipSt
   } else {
     const int64_t plane = (int64_t(a.ny - 1) * a.sy + a.nx) * int64_t(sizeof(S));
     if (plane >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // 32-bit lane byte offsets
-    const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
-    const int64_t blocks = int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
+    const int64_t blocks = Tile<TY>::blocks(a);
     if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     if (a.walls) {
       if constexpr (pair_has_walls<L, S>()) {
-        hipLaunchKernelGGL((k_step_pair<L, N, S, TY, true>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+        hipLaunchKernelGGL((k_step_pair<L, N, S, TY, true>), dim3(unsigned(blocks)), dim3(Tile<TY>::threads()), 0, s,
                            static_cast<const S*>(src), static_cast<S*>(dst), a);
         return hipGetLastError();
       }
       return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL((k_step_pair<L, N, S, TY, false>), dim3(unsigned(blocks)), dim3(64 * (TY + 3)), 0, s,
+    hipLaunchKernelGGL((k_step_pair<L, N, S, TY, false>), dim3(unsigned(blocks)), dim3(Tile<TY>::threads()), 0, s,
                        static_cast<const S*>(src), static_cast<S*>(dst), a);
     return hipGetLastError();
   }
