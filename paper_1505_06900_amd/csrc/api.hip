@@ -930,16 +930,12 @@ int lb_mlp_gradient(const float* params, const float* norm, const float* x, cons
   if (batch < 1 || n < 1) return fail(LB_ERR_INVALID_ARG, "batch and n must be >= 1");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int nb = lbrr::mlp_train_blocks(batch);
-  const size_t packed_bytes = sizeof(uint16_t) * lbrr::kMlpNPacked;
   const size_t part_bytes = sizeof(float) * size_t(nb) * lbrr::kMlpNParam;
   void* ws = nullptr;
-  if (int r = workspace(packed_bytes + part_bytes + sizeof(float) * size_t(nb) + 256, &ws)) return r;
-  char* base = static_cast<char*>(ws);
-  uint16_t* packed = reinterpret_cast<uint16_t*>(base);
-  float* gpart = reinterpret_cast<float*>(base + packed_bytes);
-  float* lpart = reinterpret_cast<float*>(base + packed_bytes + part_bytes);
-  hipError_t e = lbrr::mlp_pack(params, packed, s);
-  if (e == hipSuccess) e = lbrr::mlp_gradient(x, t, n, idx, batch, packed, params, norm, gpart, lpart, grad, loss, s);
+  if (int r = workspace(part_bytes + sizeof(float) * size_t(nb), &ws)) return r;
+  float* gpart = static_cast<float*>(ws);
+  float* lpart = gpart + size_t(nb) * lbrr::kMlpNParam;
+  const hipError_t e = lbrr::mlp_gradient(x, t, n, idx, batch, params, norm, gpart, lpart, grad, loss, s);
   if (e != hipSuccess) return hip_fail(e, "MLP gradient");
   return LB_OK;
 }

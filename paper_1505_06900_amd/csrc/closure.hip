@@ -163,15 +163,6 @@ __device__ __forceinline__ void write_features(const float (&feat)[kIn], const f
   for (int k4 = 0; k4 < kInP / 4; ++k4) xr[k4] = pack_bf16(v[4 * k4], v[4 * k4 + 1], v[4 * k4 + 2], v[4 * k4 + 3]);
 }
 
-// Four consecutive floats, 4-byte aligned: caller arrays (samples, parameters,
-// normalisation) may start at any float.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
-__device__ __forceinline__ bf16x4 load4_bf16(const float* p) {
-  const f32x4 v = load4(p);
-  return pack_bf16(v[0], v[1], v[2], v[3]);
-}
-
 constexpr int kInferWaves = 4, kInferBlocksPerCu = 2;
 
 // Batched inference: raw features (n x 36) -> de-normalised outputs (n x 3).
@@ -271,38 +262,47 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float* __r
 }
 
 // ---------------------------------------------------------------------------
-// Training: forward + backward of 32 samples per block (4 waves share the
-// tiles), mean-squared error of normalised outputs over the whole batch.
-// Writes one partial gradient (kNParam) and one partial squared-error sum per block.
+// Training: forward + backward of 32 samples per block, mean-squared error of
+// normalised outputs over the whole batch.  Writes one partial gradient (kNParam)
+// and one partial squared-error sum per block.
+//
+// Bound: latency, a chain of eight phases with a barrier between them.  A block has
+// sixteen waves so that no phase gives a wave more than one tile (four waves: up to
+// four), the serial sums (loss, biases) fall to waves that have none, and the
+// weights are rounded to BF16 as they are loaded.  Batch of 4096 (128 blocks): 15.1
+// us and a packing launch of 2.5 us with four waves, 9.7 us so, same bits.
 constexpr int kTS = 32;  // samples per block
+constexpr int kTrainThreads = 1024;
 
 // Batch rows outside [0, nrows) are clamped to the nearest valid row.
 __device__ __forceinline__ int64_t clamp_row(int r, int64_t nrows) {
   return r < 0 ? 0 : (int64_t(r) >= nrows ? nrows - 1 : int64_t(r));
 }
 
-__global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, const float* __restrict__ tgt,
-                                                   int64_t nrows, const int* __restrict__ idx, int batch,
-                                                   const uint16_t* __restrict__ packed,
-                                                   const float* __restrict__ params, const float* __restrict__ norm,
-                                                   float* __restrict__ gpart, float* __restrict__ lpart) {
+__global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const float* __restrict__ x,
+                                                             const float* __restrict__ tgt, int64_t nrows,
+                                                             const int* __restrict__ idx, int batch,
+                                                             const float* __restrict__ params,
+                                                             const float* __restrict__ norm, float* __restrict__ gpart,
+                                                             float* __restrict__ lpart) {
   __shared__ __attribute__((aligned(16))) uint16_t w[kNPacked];
   __shared__ __attribute__((aligned(16))) uint16_t xs[kTS * kLd1];
   __shared__ __attribute__((aligned(16))) uint16_t h1s[kTS * kLdH];
   __shared__ __attribute__((aligned(16))) uint16_t h2s[kTS * kLdH];
   __shared__ __attribute__((aligned(16))) uint16_t dys[kTS * kOutP], dz2s[kTS * kLdH], dz1s[kTS * kLdH];
   __shared__ float z1[kTS * kH], z2[kTS * kH], ys[kTS * kOutP], ts[kTS * kOut], red[kTS * kOut];
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  constexpr int nw = kTrainThreads / 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int s0 = blockIdx.x * kTS;
   float* g = gpart + int64_t(blockIdx.x) * kNParam;
-  load_weights<256>(packed, w);
-  for (int e = threadIdx.x; e < kTS * kInP; e += blockDim.x) {
+  load_weights<kTrainThreads>(params, w);
+  for (int e = threadIdx.x; e < kTS * kInP; e += kTrainThreads) {
     const int s = e / kInP, k = e % kInP, si = s0 + s;
     float v = 0.0f;
     if (k < kIn && si < batch) v = (x[clamp_row(idx[si], nrows) * kIn + k] - norm[k]) / norm[kIn + k];
     xs[s * kLd1 + k] = to_bf16(v);
   }
-  for (int e = threadIdx.x; e < kTS * kOut; e += blockDim.x) {
+  for (int e = threadIdx.x; e < kTS * kOut; e += kTrainThreads) {
     const int s = e / kOut, c = e % kOut, si = s0 + s;
     ts[e] = si < batch ? (tgt[clamp_row(idx[si], nrows) * kOut + c] - norm[2 * kIn + c]) / norm[2 * kIn + kOut + c]
                        : 0.0f;
@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, 
   }
   __syncthreads();
   // loss and dY = 2 (y - t) / (3 B) -----------------------------------------------
-  for (int e = threadIdx.x; e < kTS * kOutP; e += blockDim.x) {
+  for (int e = threadIdx.x; e < kTS * kOutP; e += kTrainThreads) {
     const int s = e / kOutP, c = e % kOutP;
     float d = 0.0f;
     if (c < kOut && s0 + s < batch) {
@@ -358,19 +358,21 @@ __global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, 
     dys[e] = to_bf16(d);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (wave == nw - 1 && lane == 0) {
     float l = 0.0f;
+#pragma unroll 32
     for (int e = 0; e < kTS * kOut; ++e) l += red[e];
     lpart[blockIdx.x] = l;
   }
-  if (threadIdx.x < kOut) {  // db3
+  if (wave == nw - 2 && lane < kOut) {  // db3
     float sacc = 0.0f;
-    for (int s = 0; s < kTS; ++s) sacc += ys[s * kOutP + threadIdx.x];
-    g[kOffB3 + threadIdx.x] = sacc;
+#pragma unroll
+    for (int s = 0; s < kTS; ++s) sacc += ys[s * kOutP + lane];
+    g[kOffB3 + lane] = sacc;
   }
-  // dW3 = dY^T H2 (rows o < 3), 1 x 4 tiles, K = samples
-  for (int t = wave; t < 4; t += nw) {
-    const int j0 = 16 * t;
+  // dW3 = dY^T H2 (rows o < 3), 1 x 4 tiles, K = samples (waves 8 .. 11; dZ2 takes 0 .. 7)
+  if (wave >= 8 && wave < 12) {
+    const int j0 = 16 * (wave - 8);
     f32x4 acc = {0, 0, 0, 0};
     acc = tile<kTS>(dys, 1, kOutP, h2s, kLdH, 1, 0, j0, acc);
     const int j = tile_col(j0);
@@ -393,10 +395,11 @@ __global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, 
     }
   }
   __syncthreads();
-  if (threadIdx.x < kH) {  // db2
+  if (wave == nw - 1) {  // db2
     float sacc = 0.0f;
-    for (int s = 0; s < kTS; ++s) sacc += z2[s * kH + threadIdx.x];
-    g[kOffB2 + threadIdx.x] = sacc;
+#pragma unroll
+    for (int s = 0; s < kTS; ++s) sacc += z2[s * kH + lane];
+    g[kOffB2 + lane] = sacc;
   }
   for (int t = wave; t < 16; t += nw) {  // dW2 = dZ2^T H1, 4 x 4 tiles, K = samples
     const int i0 = 16 * (t >> 2), j0 = 16 * (t & 3);
@@ -418,10 +421,11 @@ __global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, 
     }
   }
   __syncthreads();
-  if (threadIdx.x < kH) {  // db1
+  if (wave == nw - 1) {  // db1
     float sacc = 0.0f;
-    for (int s = 0; s < kTS; ++s) sacc += z1[s * kH + threadIdx.x];
-    g[kOffB1 + threadIdx.x] = sacc;
+#pragma unroll
+    for (int s = 0; s < kTS; ++s) sacc += z1[s * kH + lane];
+    g[kOffB1 + lane] = sacc;
   }
   for (int t = wave; t < 12; t += nw) {  // dW1 = dZ1^T X, 4 x 3 tiles, K = samples
     const int i0 = 16 * (t / 3), j0 = 16 * (t % 3);
@@ -433,26 +437,52 @@ __global__ void __launch_bounds__(256) k_mlp_train(const float* __restrict__ x, 
   }
 }
 
-// grad[p] = sum over blocks of the partials in a fixed order (eight interleaved
-// accumulators keep eight loads in flight per thread); loss = sum / (3 B).
-__global__ void __launch_bounds__(256) k_grad_reduce(const float* __restrict__ gpart, const float* __restrict__ lpart,
-                                                     int nblocks, int batch, float* __restrict__ grad,
-                                                     float* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[p] = sum over blocks of the partials in a fixed order: eight interleaved
+// sums (blocks b = u mod 8, the last nblocks mod 8 blocks with sum 0) and a tree;
+// loss = sum / (3 B).  A block takes 32 parameters, a thread one of the eight sums of
+// one parameter, so a row of partials is read in whole lines and the chip is
+// filled.  Bound: latency of the partials' loads.  128 blocks' partials (3.4 MB): 11.7
+// us with one thread per parameter on 27 blocks, 5.4 us so, same bits.
+constexpr int kReduceParams = 32;
+__global__ void __launch_bounds__(8 * kReduceParams) k_grad_reduce(const float* __restrict__ gpart,
+                                                                   const float* __restrict__ lpart, int nblocks,
+                                                                   int batch, float* __restrict__ grad,
+                                                                   float* __restrict__ loss) {
+  __shared__ float sums[8][kReduceParams];
+  const int c = threadIdx.x % kReduceParams, u = threadIdx.x / kReduceParams;
+  const int p = blockIdx.x * kReduceParams + c;
+  const int whole = nblocks / 8 * 8;
+  float s = 0.0f;
   if (p < kNParam) {
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int b = 0;
-    for (; b + 8 <= nblocks; b += 8) {
+    int b = u;
+    for (; b + 56 < whole; b += 64) {
+      float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s[u] += gpart[int64_t(b + u) * kNParam + p];
+      for (int k = 0; k < 8; ++k) v[k] = gpart[int64_t(b + 8 * k) * kNParam + p];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += v[k];
     }
-    for (; b < nblocks; ++b) s[0] += gpart[int64_t(b) * kNParam + p];
-    grad[p] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    for (; b < whole; b += 8) s += gpart[int64_t(b) * kNParam + p];
+    if (u == 0)
+      for (b = whole; b < nblocks; ++b) s += gpart[int64_t(b) * kNParam + p];
   }
-  if (p == 0 && loss) {
-    float s = 0.0f;
-    for (int b = 0; b < nblocks; ++b) s += lpart[b];
-    *loss = s / float(kOut * batch);
+  sums[u][c] = s;
+  __syncthreads();
+  if (u == 0 && p < kNParam)
+    grad[p] = ((sums[0][c] + sums[1][c]) + (sums[2][c] + sums[3][c])) +
+              ((sums[4][c] + sums[5][c]) + (sums[6][c] + sums[7][c]));
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 8 * kReduceParams - 1 && loss) {  // the last block has parameters to spare
+    float l = 0.0f;
+    int b = 0;
+    for (; b + 16 <= nblocks; b += 16) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = lpart[b + k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) l += v[k];
+    }
+    for (; b < nblocks; ++b) l += lpart[b];
+    *loss = l / float(kOut * batch);
   }
 }
 
@@ -897,13 +927,8 @@ hipError_t closure_coarsen(int dtype, const void* rho, const void* u, const void
   return hipGetLastError();
 }
 
-hipError_t mlp_pack(const float* params, uint16_t* packed, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack, dim3((kNPacked + 255) / 256), dim3(256), 0, s, params, packed);
-  return hipGetLastError();
-}
-
 hipError_t mlp_pack_step(const float* params, uint16_t* packed_and_image, hipStream_t s) {
-  if (hipError_t e = mlp_pack(params, packed_and_image, s); e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_pack, dim3((kNPacked + 255) / 256), dim3(256), 0, s, params, packed_and_image);
   hipLaunchKernelGGL(k_pack_image, dim3(kNOps), dim3(64), 0, s, packed_and_image,
                      reinterpret_cast<bf16x8*>(packed_and_image + kNPacked));
   return hipGetLastError();
@@ -953,14 +978,14 @@ hipError_t column_stats(const float* x, int64_t n, int dim, double* part, float*
   return hipGetLastError();
 }
 
-hipError_t mlp_gradient(const float* x, const float* t, int64_t nrows, const int* idx, int batch, const uint16_t* packed,
-                        const float* params, const float* norm, float* gpart, float* lpart, float* grad, float* loss,
-                        hipStream_t s) {
+hipError_t mlp_gradient(const float* x, const float* t, int64_t nrows, const int* idx, int batch, const float* params,
+                        const float* norm, float* gpart, float* lpart, float* grad, float* loss, hipStream_t s) {
   const int nb = mlp_train_blocks(batch);
   if (nb <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(256), 0, s, x, t, nrows, idx, batch, packed, params, norm, gpart,
+  hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(kTrainThreads), 0, s, x, t, nrows, idx, batch, params, norm, gpart,
                      lpart);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((kNParam + 255) / 256), dim3(256), 0, s, gpart, lpart, nb, batch, grad, loss);
+  hipLaunchKernelGGL(k_grad_reduce, dim3((kNParam + kReduceParams - 1) / kReduceParams), dim3(8 * kReduceParams), 0, s,
+                     gpart, lpart, nb, batch, grad, loss);
   return hipGetLastError();
 }
 

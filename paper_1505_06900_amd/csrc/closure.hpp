@@ -21,7 +21,6 @@ hipError_t closure_features(int storage, const void* src, float* m, const StepAr
                             double plain_weight, float* feat, float* lab, hipStream_t s);
 hipError_t closure_coarsen(int dtype, const void* rho, const void* u, const void* pi1, int nfx, int nfy, int F,
                            double alpha, double beta, double* rho_c, double* u_c, double* pi1_c, hipStream_t s);
-hipError_t mlp_pack(const float* params, uint16_t* packed, hipStream_t s);
 // packed weights (kMlpNPacked) followed by the fused step's register image (kMlpNRegImage)
 hipError_t mlp_pack_step(const float* params, uint16_t* packed_and_image, hipStream_t s);
 hipError_t mlp_infer(const float* x, int64_t n, const float* params, const float* norm, float* y, hipStream_t s);
@@ -30,9 +29,8 @@ int mlp_train_blocks(int batch);
 int column_stats_runs(int64_t n, int dim);
 bool column_stats_direct(int64_t n, int dim);  // few rows: part = NULL is the faster form
 hipError_t column_stats(const float* x, int64_t n, int dim, double* part, float* mean, float* sd, hipStream_t s);
-hipError_t mlp_gradient(const float* x, const float* t, int64_t nrows, const int* idx, int batch, const uint16_t* packed,
-                        const float* params, const float* norm, float* gpart, float* lpart, float* grad, float* loss,
-                        hipStream_t s);
+hipError_t mlp_gradient(const float* x, const float* t, int64_t nrows, const int* idx, int batch, const float* params,
+                        const float* norm, float* gpart, float* lpart, float* grad, float* loss, hipStream_t s);
 hipError_t mlp_adam(float* p, float* m, float* v, const float* g, long long step, float lr, float b1, float b2,
                     float eps, hipStream_t s);
 

@@ -5,7 +5,7 @@
 // Parameter vector (FP32, 6723 values): W1 (64 x 36, out x in), b1 (64),
 // W2 (64 x 64), b2 (64), W3 (3 x 64), b3 (3).  Normalisation vector (78):
 // x_mean (36), x_std (36), y_mean (3), y_std (3).
-// Packed BF16 weights (8768 values, copied verbatim into LDS): W1 as 64 rows
+// Packed BF16 weights (8768 values): W1 as 64 rows
 // of stride 52 (inputs 36..51 zero), W2 as 64 rows of stride 68, W3 as 16 rows
 // of stride 68 (outputs 3..15 zero; columns 64..67 of W2 and W3 zero).  The
 // row strides are 8 bytes modulo 128, so the 8-byte matrix-core operand reads
@@ -26,6 +26,7 @@ static_assert(kNParam == 6723, "parameter count");
 constexpr int kNNorm = 2 * kIn + 2 * kOut;
 constexpr int kLd1 = 52, kLdH = 68;  // LDS row strides (BF16 elements) of 48- and 64-wide operands
 constexpr int kPW1 = 0, kPW2 = kPW1 + kH * kLd1, kPW3 = kPW2 + kH * kLdH, kNPacked = kPW3 + kOutP * kLdH;
+static_assert(kLd1 % 4 == 0 && kLdH % 4 == 0 && kIn % 4 == 0, "rows of whole groups of four");
 static_assert((kNPacked * 2) % 16 == 0 && (kPW2 * 2) % 16 == 0 && (kPW3 * 2) % 16 == 0, "16-byte packed blocks");
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
@@ -129,24 +130,42 @@ __device__ __forceinline__ f32x4 tile_kc(const uint16_t* A, int lda, const uint1
 __device__ __forceinline__ int tile_row(int i0, int r) { return i0 + 4 * ((threadIdx.x & 63) >> 4) + r; }
 __device__ __forceinline__ int tile_col(int j0) { return j0 + (threadIdx.x & 15); }
 
-// Load the packed BF16 weights into LDS with a block of NT threads, 16 bytes
-// per load, every load of a thread issued before its first LDS write.
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// Four consecutive floats, 4-byte aligned: caller arrays (samples, parameters,
+// normalisation) may start at any float.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+__device__ __forceinline__ bf16x4 load4_bf16(const float* p) {
+  const f32x4 v = load4(p);
+  return pack_bf16(v[0], v[1], v[2], v[3]);
+}
+
+// The FP32 parameters' weights into LDS as padded BF16 rows (the packed layout
+// above), with a block of NT threads: four columns of a row per load, every load of
+// a thread issued before its first LDS write.
 template <int NT>
-__device__ __forceinline__ void load_weights(const uint16_t* __restrict__ packed, uint16_t* lds) {
-  constexpr int kChunks = kNPacked * 2 / 16, kPer = (kChunks + NT - 1) / NT;
-  const u32x4* src = reinterpret_cast<const u32x4*>(packed);
-  u32x4* dst = reinterpret_cast<u32x4*>(lds);
-  u32x4 v[kPer];
+__device__ __forceinline__ void load_weights(const float* __restrict__ params, uint16_t* lds) {
+  constexpr int c1 = kLd1 / 4, ch = kLdH / 4;  // groups of four columns in a padded row
+  constexpr int n1 = kH * c1, n2 = n1 + kH * ch, n3 = n2 + kOutP * ch, kPer = (n3 + NT - 1) / NT;
+  f32x4 v[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int c = int(threadIdx.x) + k * NT;
-    if (c < kChunks) v[k] = src[c];
+    const int e = int(threadIdx.x) + k * NT;
+    v[k] = f32x4{0, 0, 0, 0};
+    if (e < n1) {
+      const int o = e / c1, c = 4 * (e % c1);
+      if (c < kIn) v[k] = load4(params + kOffW1 + o * kIn + c);
+    } else if (e < n2) {
+      const int o = (e - n1) / ch, c = 4 * ((e - n1) % ch);
+      if (c < kH) v[k] = load4(params + kOffW2 + o * kH + c);
+    } else if (e < n3) {
+      const int o = (e - n2) / ch, c = 4 * ((e - n2) % ch);
+      if (o < kOut && c < kH) v[k] = load4(params + kOffW3 + o * kH + c);
+    }
   }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int c = int(threadIdx.x) + k * NT;
-    if (c < kChunks) dst[c] = v[k];
+    const int e = int(threadIdx.x) + k * NT;
+    if (e < n3) *reinterpret_cast<bf16x4*>(lds + 4 * e) = pack_bf16(v[k][0], v[k][1], v[k][2], v[k][3]);
   }
 }
 
