@@ -14,6 +14,7 @@
 #include "closure.hpp"
 #include "lbrr.h"
 #include "ops.hpp"
+#include "reduce.hpp"
 
 using lbrr::LatticeOps;
 using lbrr::StepArgs;
@@ -171,8 +172,8 @@ size_t plane_pad_bytes(size_t plane_bytes) {
 }
 
 // Scratch of lb_reduce_static: the per-block partial totals (5 doubles per
-// block, at most LB_REDUCE_STATIC_MAX_BLOCKS blocks) and nothing else.  A
-// file-scope device array: every GPU the library runs on holds its own copy
+// block, at most LB_REDUCE_STATIC_MAX_BLOCKS blocks) and nothing else (no ticket:
+// calls that overlap would leave it wrong for good).  A file-scope device array: every GPU the library runs on holds its own copy
 // (82 KB) until the process ends.  Host code never uses the name `scratch`
 // as an address; it uses the per-device address that hipGetSymbolAddress
 // returns (static_scratch below).
@@ -197,13 +198,86 @@ int static_scratch(double** out) {
   return LB_OK;
 }
 
-// Per-block partial count of the totals: one block per 2048 nodes, at most
-// LB_REDUCE_STATIC_MAX_BLOCKS (the handle path and lb_reduce_static use the
-// same partition, so their sums are the same bits).
+// Per-block partial count of the totals: one block per 256 nodes (a node per
+// thread), at most LB_REDUCE_STATIC_MAX_BLOCKS (the handle path and
+// lb_reduce_static use the same partition, so their sums are the same bits).
+// With 2048 nodes a block a 64^2 grid ran on two blocks, eight nodes in turn.
 int totals_blocks(int64_t nodes) {
-  const int64_t nb = (nodes + 2047) / 2048;
+  const int64_t nb = (nodes + 255) / 256;
   return int(nb < 1 ? 1 : (nb > LB_REDUCE_STATIC_MAX_BLOCKS ? LB_REDUCE_STATIC_MAX_BLOCKS : nb));
 }
+
+// Where a handle's reductions leave their few results.  The kernels write them to
+// pinned host memory, so the host reads them as soon as the stream is done; a
+// copy from device memory took 10 us and more of each lb_reduce and
+// lb_enstrophy.  One pinned page per process holds 64-byte slots; a handle that
+// finds none free (or no pinned memory) keeps its results in device memory and
+// copies them.
+struct ResultSlot {
+  static constexpr int kSlots = 256, kDoubles = 8;
+  double* device = nullptr;  // the kernels' address
+  volatile double* host = nullptr;
+
+  hipError_t acquire() {
+    if (device) return hipSuccess;
+    std::lock_guard<std::mutex> lock(mu());
+    Page& p = page();
+    if (!p.tried) {
+      p.tried = true;
+      void* m = nullptr;
+      if (hipHostMalloc(&m, sizeof(double) * kDoubles * kSlots, hipHostMallocPortable | hipHostMallocMapped) ==
+          hipSuccess)
+        p.host = static_cast<double*>(m);
+      else
+        (void)hipGetLastError();
+    }
+    for (int i = 0; p.host && i < kSlots; ++i) {
+      if (p.used[i]) continue;
+      void* d = nullptr;
+      if (hipHostGetDevicePointer(&d, p.host + i * kDoubles, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        break;
+      }
+      p.used[i] = true;
+      host = p.host + i * kDoubles;
+      device = static_cast<double*>(d);
+      return hipSuccess;
+    }
+    return hipMalloc(&device, sizeof(double) * kDoubles);
+  }
+  hipError_t read(double* out, int n, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (!host) e = hipMemcpyAsync(out, device, sizeof(double) * n, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    for (int c = 0; host && c < n; ++c) out[c] = host[c];
+    return e;
+  }
+  void release() {
+    if (host) {
+      std::lock_guard<std::mutex> lock(mu());
+      page().used[(const_cast<double*>(host) - page().host) / kDoubles] = false;
+    } else if (device) {
+      (void)hipFree(device);
+    }
+    device = nullptr;
+    host = nullptr;
+  }
+
+ private:
+  struct Page {
+    bool tried = false;
+    double* host = nullptr;
+    bool used[kSlots] = {};
+  };
+  static std::mutex& mu() {
+    static std::mutex m;
+    return m;
+  }
+  static Page& page() {
+    static Page p;
+    return p;
+  }
+};
 
 }  // namespace
 
@@ -228,7 +302,8 @@ struct lb_ctx {
   int walls = 0;  // bit 0 x, bit 1 y, bit 2 z: resting no-slip walls on the first and last node
   double* partials = nullptr;
   int nblocks = 0;
-  double* dev_out = nullptr;
+  unsigned* ticket = nullptr;  // of the reductions' blocks, behind the partials; NULL for large grids (reduce.hpp)
+  ResultSlot slot;             // where they write their results
   double* vel = nullptr;
   // learned closure (D2Q9)
   bool closure_on = false;
@@ -263,10 +338,10 @@ struct lb_ctx {
       b = nullptr;
     }
     if (partials) (void)hipFree(partials);
-    if (dev_out) (void)hipFree(dev_out);
     if (vel) (void)hipFree(vel);
     partials = nullptr;
-    dev_out = nullptr;
+    ticket = nullptr;
+    slot.release();
     vel = nullptr;
     ready = false;
   }
@@ -369,8 +444,12 @@ int ensure_buffers(lb_ctx* h) {
   }
   h->nblocks = totals_blocks(h->nodes());
   // a failure here frees the population buffers too: buf[0] marks a complete set
-  hipError_t e = hipMalloc(&h->partials, sizeof(double) * 5 * h->nblocks);
-  if (e == hipSuccess) e = hipMalloc(&h->dev_out, sizeof(double) * 8);
+  hipError_t e = hipMalloc(&h->partials, sizeof(double) * (5 * size_t(h->nblocks) + 1));
+  if (e == hipSuccess && h->nblocks <= lbrr::kTicketBlocks) {
+    h->ticket = reinterpret_cast<unsigned*>(h->partials + 5 * size_t(h->nblocks));
+    e = lbrr::launch_zero(h->ticket, 1, h->stream);
+  }
+  if (e == hipSuccess) e = h->slot.acquire();
   if (e != hipSuccess) {
     h->release();
     (void)hipGetLastError();
@@ -386,10 +465,10 @@ int check_handle(lb_ctx* h) {
 }
 
 int totals(lb_ctx* h, double out[5]) {
-  hipError_t e = h->ops->totals(h->storage, h->buf[h->cur], h->partials, h->nblocks, h->dev_out, h->args(), h->stream);
+  hipError_t e = h->ops->totals(h->storage, h->buf[h->cur], h->partials, h->ticket, h->nblocks, h->slot.device,
+                                h->args(), h->stream);
   if (e != hipSuccess) return hip_fail(e, "totals kernel launch");
-  HIP_TRY(hipMemcpyAsync(out, h->dev_out, sizeof(double) * 5, hipMemcpyDeviceToHost, h->stream), "copy totals");
-  HIP_TRY(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+  HIP_TRY(h->slot.read(out, 5, h->stream), "read totals");
   for (int c = 0; c < 5; ++c)
     if (!std::isfinite(out[c])) return fail(LB_ERR_UNSTABLE, "non-finite total after step %lld", h->steps);
   return LB_OK;
@@ -678,7 +757,7 @@ int lb_reduce_static(int lattice, int storage, int nx, int ny, int nz, double rh
   a.lz = 1;
   a.walls = 0;
   const hipError_t e =
-      ops->totals(storage, populations, partials, nblocks, out, a, static_cast<hipStream_t>(hip_stream));
+      ops->totals(storage, populations, partials, nullptr, nblocks, out, a, static_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return hip_fail(e, "totals kernel launch");
   return LB_OK;
 }
@@ -690,12 +769,11 @@ int lb_enstrophy(lb_handle h, double* out) {
   if (!h->vel) HIP_TRY(hipMalloc(&h->vel, sizeof(double) * size_t(h->nodes()) * h->d()), "hipMalloc velocity");
   hipError_t e = h->ops->velocity(h->storage, h->buf[h->cur], h->vel, h->args(), h->stream);
   if (e == hipSuccess)
-    e = lbrr::launch_enstrophy(h->vel, h->d(), h->nx, h->ny, h->nz, h->walls, h->partials, h->nblocks, h->dev_out,
-                               h->stream);
+    e = lbrr::launch_enstrophy(h->vel, h->d(), h->nx, h->ny, h->nz, h->walls, h->partials, h->ticket, h->nblocks,
+                               h->slot.device, h->stream);
   if (e != hipSuccess) return hip_fail(e, "enstrophy kernels");
   double s = 0.0;
-  HIP_TRY(hipMemcpyAsync(&s, h->dev_out, sizeof(double), hipMemcpyDeviceToHost, h->stream), "copy enstrophy");
-  HIP_TRY(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+  HIP_TRY(h->slot.read(&s, 1, h->stream), "read enstrophy");
   // trapezoid volume: a walled axis of n nodes spans n - 1 cells, a periodic one n
   double vol = 1.0;
   const int dims[3] = {h->nx, h->ny, h->nz};

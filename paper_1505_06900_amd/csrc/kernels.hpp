@@ -11,6 +11,7 @@
 
 #include "collide.hpp"
 #include "ops.hpp"
+#include "reduce.hpp"
 
 namespace lbrr {
 
@@ -342,35 +343,12 @@ __global__ void __launch_bounds__(256) k_moments(const S* __restrict__ src, T* _
 }
 
 // ---------------------------------------------------------------------------
-// FP64 reductions: wave butterfly (64 lanes) -> LDS across waves -> one
-// partial per block; the final sum over blocks runs in a fixed order.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <int NV>
-__device__ __forceinline__ void block_sum_store(double (&v)[NV], double* __restrict__ out) {
-  __shared__ double lds[NV][kReduceBlock / 64];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int c = 0; c < NV; ++c) {
-    const double s = wave_sum(v[c]);
-    if (lane == 0) lds[c][wid] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < NV) {
-    double s = 0.0;
-    for (int w = 0; w < kReduceBlock / 64; ++w) s += lds[threadIdx.x][w];
-    out[int64_t(blockIdx.x) * NV + threadIdx.x] = s;
-  }
-}
-
-// Per-block partial totals {rho, rho u_x, rho u_y, rho u_z, rho |u|^2 / 2}.
+// Per-block partial totals {rho, rho u_x, rho u_y, rho u_z, rho |u|^2 / 2}, added up by
+// the last block to finish (reduce.hpp).
 template <class L, class S>
 __global__ void __launch_bounds__(kReduceBlock) k_totals(const S* __restrict__ src, double* __restrict__ partials,
-                                                         StepArgs a, int64_t per_block) {
+                                                         unsigned* __restrict__ ticket, StepArgs a, int64_t per_block,
+                                                         double* __restrict__ out) {
   const int64_t nodes = int64_t(a.nx) * a.ny * a.nz;
   const int64_t begin = int64_t(blockIdx.x) * per_block;
   const int64_t end = begin + per_block < nodes ? begin + per_block : nodes;
@@ -387,22 +365,7 @@ __global__ void __launch_bounds__(kReduceBlock) k_totals(const S* __restrict__ s
     acc[3] += m.jz;
     acc[4] += 0.5 * (m.jx * m.jx + m.jy * m.jy + m.jz * m.jz) / rho;
   }
-  block_sum_store<5>(acc, partials);
-}
-
-// Sum of per-block partials in a fixed order: thread t adds blocks t, t+B, ...
-// then a fixed tree over the threads.
-template <int NV>
-__global__ void __launch_bounds__(kReduceBlock) k_final(const double* __restrict__ partials, int nblocks,
-                                                        double* __restrict__ out) {
-  double acc[NV];
-#pragma unroll
-  for (int c = 0; c < NV; ++c) acc[c] = 0.0;
-  for (int b = threadIdx.x; b < nblocks; b += kReduceBlock) {
-#pragma unroll
-    for (int c = 0; c < NV; ++c) acc[c] += partials[int64_t(b) * NV + c];
-  }
-  block_sum_store<NV>(acc, out);
+  reduce_blocks<5>(acc, partials, ticket, out);
 }
 
 // Velocity field (FP64) of the stored state, for the vorticity diagnostic.
@@ -525,13 +488,13 @@ hipError_t launch_moments(int dtype, const void* src, void* rho, void* u, void* 
 }
 
 template <class L, class S>
-hipError_t launch_totals(const void* src, double* partials, int nblocks, double* out, const StepArgs& a,
-                         hipStream_t s) {
+hipError_t launch_totals(const void* src, double* partials, unsigned* ticket, int nblocks, double* out,
+                         const StepArgs& a, hipStream_t s) {
   const int64_t nodes = int64_t(a.nx) * a.ny * a.nz;
   const int64_t per_block = (nodes + nblocks - 1) / nblocks;
   hipLaunchKernelGGL((k_totals<L, S>), dim3(nblocks), dim3(kReduceBlock), 0, s, static_cast<const S*>(src), partials,
-                     a, per_block);
-  hipLaunchKernelGGL((k_final<5>), dim3(1), dim3(kReduceBlock), 0, s, partials, nblocks, out);
+                     ticket, a, per_block, out);
+  if (!ticket) hipLaunchKernelGGL((k_final<5>), dim3(1), dim3(kReduceBlock), 0, s, partials, nblocks, out);
   return hipGetLastError();
 }
 

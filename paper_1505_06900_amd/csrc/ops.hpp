@@ -34,8 +34,9 @@ struct LatticeOps {
                      const StepArgs& a, hipStream_t s);
   hipError_t (*moments)(int storage, int dtype, const void* src, void* rho, void* u, void* pi1, const StepArgs& a,
                         double inv_omega1, hipStream_t s);
-  hipError_t (*totals)(int storage, const void* src, double* partials, int nblocks, double* out, const StepArgs& a,
-                       hipStream_t s);
+  // ticket: 0 before the launch and after it, or NULL: the partials are added in a launch of their own (reduce.hpp)
+  hipError_t (*totals)(int storage, const void* src, double* partials, unsigned* ticket, int nblocks, double* out,
+                       const StepArgs& a, hipStream_t s);
   hipError_t (*velocity)(int storage, const void* src, double* u, const StepArgs& a, hipStream_t s);
   // copy between the internal layout and compact SoA [q][nz][ny][nx] (to_compact: internal -> compact)
   hipError_t (*repack)(int storage, const void* src, void* dst, bool to_compact, const StepArgs& a, hipStream_t s);
@@ -57,8 +58,9 @@ const LatticeOps& ops_d3q27();
 // diagnostics kernels (diag.hip)
 hipError_t launch_probe(int kind, int vec_bytes, int blocks_per_cu, int nontemporal, int streams, const void* src,
                         void* dst, size_t nbytes, int cus, hipStream_t s);
-hipError_t launch_enstrophy(const double* u, int d, int nx, int ny, int nz, int walls, double* partials, int nblocks,
-                            double* out, hipStream_t s);
+hipError_t launch_enstrophy(const double* u, int d, int nx, int ny, int nz, int walls, double* partials,
+                            unsigned* ticket, int nblocks, double* out, hipStream_t s);
+hipError_t launch_zero(unsigned* p, int n, hipStream_t s);
 hipError_t launch_copy(const void* src, void* dst, size_t n, hipStream_t s);
 
 }  // namespace lbrr

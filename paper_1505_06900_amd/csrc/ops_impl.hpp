@@ -95,14 +95,14 @@ struct OpsImpl {
     }
     return hipErrorInvalidValue;
   }
-  static hipError_t totals(int storage, const void* src, double* partials, int nblocks, double* out,
+  static hipError_t totals(int storage, const void* src, double* partials, unsigned* ticket, int nblocks, double* out,
                            const StepArgs& a, hipStream_t s) {
     switch (storage) {
-      case 0: return launch_totals<L, double>(src, partials, nblocks, out, a, s);
-      case 1: return launch_totals<L, float>(src, partials, nblocks, out, a, s);
-      case 2: return launch_totals<L, _Float16>(src, partials, nblocks, out, a, s);
-      case 3: return launch_mtotals<L, double>(src, partials, nblocks, out, a, s);
-      case 4: return launch_mtotals<L, float>(src, partials, nblocks, out, a, s);
+      case 0: return launch_totals<L, double>(src, partials, ticket, nblocks, out, a, s);
+      case 1: return launch_totals<L, float>(src, partials, ticket, nblocks, out, a, s);
+      case 2: return launch_totals<L, _Float16>(src, partials, ticket, nblocks, out, a, s);
+      case 3: return launch_mtotals<L, double>(src, partials, ticket, nblocks, out, a, s);
+      case 4: return launch_mtotals<L, float>(src, partials, ticket, nblocks, out, a, s);
     }
     return hipErrorInvalidValue;
   }
