@@ -84,6 +84,22 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
   using Up = Layer<L, 1, R, W>;
   Up up1, up2;  // c_z = +1 layers of targets k - 1 and k - 2
   Mid mid2;     // c_z = 0 layer of target k - 2
+  // Loads and stores complete in order under one counter: populations stored at
+  // once are waited for with the pulled plane.  Stored late, they wait in registers
+  // for the next iteration and go between the wait for its plane and the next pull.
+  // Only where the registers hold them too: D3Q27 FP32 256^3 44.1 -> 44.6 GLUPS,
+  // D3Q19 FP32 65 x 130 x 301 44.6 -> 45.8, walled 41.4 -> 43.6; FP64 D3Q19 +-1 %;
+  // with spills (13 rows or walled D3Q27 FP32, D3Q27 FP64) 35 to 55 % are lost.
+  constexpr bool kStoreLate = sizeof(S) == 4 && (L::Q == 27 ? !W : TY < 13);
+  struct {
+    R v[L::Q];
+  } done;
+  auto put = [&](int z, const R (&v)[L::Q]) __attribute__((always_inline)) {
+    S* d = dst + int64_t(z) * a.sz;
+    uint32_t o = off_out;
+    asm volatile("" : "+v"(o));
+    sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(v[I], ptr_at_offset(d + int64_t(I) * a.si, o)); });
+  };
   // First step of plane k into LDS; ZS selects all populations (2) or those
   // with c_z = ZS.  Next: pull plane k + 1 once the moments of plane k are formed.
   auto first = [&](int k, auto ZS, auto Next) __attribute__((always_inline)) {
@@ -96,12 +112,12 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
     } else {
       m = raw_moments<L, R>(f.v);
     }
-    if constexpr (decltype(Next)::value) {
-      // the moments are pinned here, so that the pull can take the registers of f
-      asm volatile("" : "+v"(m.d0), "+v"(m.jx), "+v"(m.jy), "+v"(m.jz), "+v"(m.pxx), "+v"(m.pyy), "+v"(m.pzz),
-                   "+v"(m.pxy), "+v"(m.pxz), "+v"(m.pyz));
-      pull(wrap_axis(z0 + k, a.nz), f.v);
-    }
+    // the moments are pinned here, so that the pull can take the registers of f
+    asm volatile("" : "+v"(m.d0), "+v"(m.jx), "+v"(m.jy), "+v"(m.jz), "+v"(m.pxx), "+v"(m.pyy), "+v"(m.pzz),
+                 "+v"(m.pxy), "+v"(m.pxz), "+v"(m.pyz));
+    if constexpr (kStoreLate)
+      if (t.inner && k >= 3) put(z0 + k - 3, done.v);
+    if constexpr (decltype(Next)::value) pull(wrap_axis(z0 + k, a.nz), f.v);
     const Hydro<R> h = hydro<L, R>(m, rho0);
     R C[3][3][3], out[L::Q];
     coefficients<L, N, R>(h, om, C);
@@ -115,17 +131,13 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
   // population I arriving at the inner node
   auto arrived = [&](auto I) { return pop[I][r - L::cy(I)][lane + 1 - L::cx(I)]; };
   // second step of plane z from its layers
-  auto second = [&](int z, const Lo& lo, const Mid& mid, const Up& up) __attribute__((always_inline)) {
+  auto second = [&](int z, const Lo& lo, const Mid& mid, const Up& up, R (&out)[L::Q]) __attribute__((always_inline)) {
     const int sz2 = W ? wall_side(a.walls, 2, z, a.nz) : 0;
     const Moments<R> m = layer_moments<L, R, W>(lo, mid, up, sx2, sy2, sz2);
     const Hydro<R> h = hydro<L, R>(m, rho0);
-    R C[3][3][3], out[L::Q];
+    R C[3][3][3];
     coefficients<L, N, R>(h, om, C);
     reconstruct<L, N, R>(C, out);
-    S* d = dst + int64_t(z) * a.sz;
-    uint32_t o = off_out;
-    asm volatile("" : "+v"(o));
-    sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(out[I], ptr_at_offset(d + int64_t(I) * a.si, o)); });
   };
   using all = std::integral_constant<int, 2>;
   using layer_m = std::integral_constant<int, -1>;
@@ -148,7 +160,10 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
     }
     lds_barrier();
     if (t.inner) {
-      if (k >= 2) second(z0 + k - 2, lo, mid2, up2);
+      if (k >= 2) {
+        second(z0 + k - 2, lo, mid2, up2, done.v);
+        if constexpr (!kStoreLate) put(z0 + k - 2, done.v);
+      }
       up2 = up1;
       mid2 = mid;
       up1 = up;
@@ -159,7 +174,9 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
   if (t.inner) {
     Lo lo;
     lo.read(arrived);
-    second(z1 - 1, lo, mid2, up2);
+    R out[L::Q];
+    second(z1 - 1, lo, mid2, up2, out);
+    put(z1 - 1, out);
   }
 }
 
@@ -170,8 +187,11 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
 // each layer it is waiting for, and collides row p - 1 when row p is there.  The
 // populations moving along y stay in their thread; the six others pass through
 // LDS, in two buffers taken in turn (one barrier a row).  W: resting walls on the
-// axes of a.walls.  Measured (pair_plan, api.hip): 2048^2 FP32 49.9 -> 33.8 us a step
-// (124 GLUPS; 5.6 TB/s with the rows read twice), FP64 101 -> 61; small grids save
+// axes of a.walls.  The next row is pulled into the registers of the present one
+// once its moments are formed (copied from a second set at the end of the loop, it
+// was waited for there: 33.8 us); storing late as in k_step_pair loses 2 to 6 % on
+// large grids.  Measured (pair_plan, api.hip): 2048^2 FP32 49.9 -> 32.5 us a step
+// (129 GLUPS; 5.8 TB/s with the rows read twice), FP64 101 -> 61; small grids save
 // a launch: 64^2 FP32 2.66 -> 1.92.
 constexpr int kPairRowX = 256;
 
@@ -188,50 +208,58 @@ __global__ void __launch_bounds__(kPairRowX) k_step_pair2(const S* __restrict__ 
   const int px = wrap_axis(x0 - 1 + tx, a.nx);
   const int xo = x0 + tx - 1;
   const bool inner = tx >= 1 && tx <= BX - 2 && xo < a.nx;
-  const uint32_t xs[3] = {uint32_t(px == a.nx - 1 ? 0 : px + 1) * uint32_t(sizeof(S)), uint32_t(px) * uint32_t(sizeof(S)),
-                          uint32_t(px == 0 ? a.nx - 1 : px - 1) * uint32_t(sizeof(S))};
+  uint32_t xs[3] = {uint32_t(px == a.nx - 1 ? 0 : px + 1) * uint32_t(sizeof(S)), uint32_t(px) * uint32_t(sizeof(S)),
+                    uint32_t(px == 0 ? a.nx - 1 : px - 1) * uint32_t(sizeof(S))};
   const uint32_t off_out = uint32_t(xo) * uint32_t(sizeof(S));
   const R rho0 = R(a.rho0), om = R(a.omega1);
   const int sx1 = W ? wall_side(a.walls, 0, px, a.nx) : 0, sx2 = W ? wall_side(a.walls, 0, xo, a.nx) : 0;
   auto pull = [&](int y, R (&f)[L::Q]) __attribute__((always_inline)) {
     const int ys[3] = {y == a.ny - 1 ? 0 : y + 1, y, y == 0 ? a.ny - 1 : y - 1};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) asm volatile("" : "+v"(xs[i]));  // keeps the scalar-base form (see k_step_pair)
     sfor<0, L::Q>([&](auto I) {
       constexpr int cx = L::cx(I), cy = L::cy(I);
       f[I] = at_offset(src + int64_t(I) * a.si + int64_t(ys[cy + 1]) * a.sy, xs[cx + 1]);
     });
   };
-  auto update = [&](R (&f)[L::Q], int sx, int y) __attribute__((always_inline)) {
-    if constexpr (W) collide_walls<L, N, R>(f, rho0, om, sx, wall_side(a.walls, 1, y, a.ny), 0);
-    else collide<L, N, R>(f, rho0, om);
-  };
   // rows y0 .. y1 - 1; first-step rows y0 - 1 .. y1, row y0 - 1 + k of the march
   const int y0 = by * a.lz;
   const int y1 = (y0 + a.lz < a.ny) ? y0 + a.lz : a.ny;
   const int n = y1 - y0;
-  struct {  // a struct, as in k_step_pair
+  struct {  // structs, as in k_step_pair
     R v[L::Q];
-  } next;
+  } f;  // the pulled row
   struct {
     R v[3];  // arrivals with c_x = -1, 0, 1
   } up1, up2, mid2;
-  pull(wrap_axis(y0 - 1, a.ny), next.v);
-  for (int k = 0; k <= n + 1; ++k) {
-    const int y = wrap_axis(y0 - 1 + k, a.ny);
-    R f[L::Q];
-    sfor<0, L::Q>([&](auto I) { f[I] = next.v[I]; });
-    if (k <= n) pull(wrap_axis(y0 + k, a.ny), next.v);
-    update(f, sx1, y);
+  // Moments of populations v of a node on row y, side sx of the box.
+  auto moments = [&](R (&v)[L::Q], int sx, int y) __attribute__((always_inline)) {
+    if constexpr (W) {
+      const int sy = wall_side(a.walls, 1, y, a.ny);
+      const R drho = complete_walls<L, R>(v, sx, sy, 0);
+      return moments_walls<L, R>(v, drho, sx, sy, 0);
+    } else {
+      return raw_moments<L, R>(v);
+    }
+  };
+  auto row = [&](int k, auto Next) __attribute__((always_inline)) {
+    Moments<R> m = moments(f.v, sx1, wrap_axis(y0 - 1 + k, a.ny));
+    asm volatile("" : "+v"(m.d0), "+v"(m.jx), "+v"(m.jy), "+v"(m.pxx), "+v"(m.pyy), "+v"(m.pxy));
+    if constexpr (decltype(Next)::value) pull(wrap_axis(y0 + k, a.ny), f.v);
+    R C[3][3][3], out[L::Q];
+    coefficients<L, N, R>(hydro<L, R>(m, rho0), om, C);
+    reconstruct<L, N, R>(C, out);
     const int b = k & 1;
     sfor<0, L::Q>([&](auto I) {
       constexpr int cx = L::cx(I), cy = L::cy(I);
-      if constexpr (cx != 0) pop[b][cy + 1 + (cx > 0 ? 3 : 0)][tx] = f[I];
+      if constexpr (cx != 0) pop[b][cy + 1 + (cx > 0 ? 3 : 0)][tx] = out[I];
     });
     lds_barrier();
     if (inner) {
-      // arrival from row y with velocity (c_x, c_y)
+      // arrival from this row with velocity (c_x, c_y)
       auto arrived = [&](auto X, auto Y) {
         constexpr int cx = int(X) - 1, cy = int(Y) - 1;
-        if constexpr (cx == 0) return f[velocity_index<L>(0, cy, 0)];
+        if constexpr (cx == 0) return out[velocity_index<L>(0, cy, 0)];
         else return pop[b][cy + 1 + (cx > 0 ? 3 : 0)][tx - cx];
       };
       using row_m = std::integral_constant<int, 0>;
@@ -245,10 +273,13 @@ __global__ void __launch_bounds__(kPairRowX) k_step_pair2(const S* __restrict__ 
           g[velocity_index<L>(cx, 0, 0)] = mid2.v[X];
           g[velocity_index<L>(cx, -1, 0)] = arrived(X, row_m{});
         });
-        const int yt = y0 + k - 2;
-        update(g, sx2, yt);
-        S* d = dst + int64_t(yt) * a.sy;
-        sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(g[I], ptr_at_offset(d + int64_t(I) * a.si, off_out)); });
+        R D[3][3][3];
+        coefficients<L, N, R>(hydro<L, R>(moments(g, sx2, y0 + k - 2), rho0), om, D);
+        reconstruct<L, N, R>(D, g);
+        S* d = dst + int64_t(y0 + k - 2) * a.sy;
+        uint32_t o = off_out;
+        asm volatile("" : "+v"(o));
+        sfor<0, L::Q>([&](auto I) { __builtin_nontemporal_store(g[I], ptr_at_offset(d + int64_t(I) * a.si, o)); });
       }
       up2 = up1;
       sfor<0, 3>([&](auto X) {
@@ -256,7 +287,10 @@ __global__ void __launch_bounds__(kPairRowX) k_step_pair2(const S* __restrict__ 
         up1.v[X] = arrived(X, row_p{});
       });
     }
-  }
+  };
+  pull(wrap_axis(y0 - 1, a.ny), f.v);
+  for (int k = 0; k <= n; ++k) row(k, std::true_type{});
+  row(n + 1, std::false_type{});
 }
 
 // Walled boxes: D3Q27 FP64 would spill 25-69 registers and ran slower than single
