@@ -972,10 +972,8 @@ int lb_closure_features(lb_handle h, const double* a_target, double plain_weight
   if (!features || !labels) return fail(LB_ERR_INVALID_ARG, "features and labels must not be NULL");
   if (h->moment()) return fail(LB_ERR_UNSUPPORTED, "closure features need population storage");
   if (!h->ready) return fail(LB_ERR_STATE, "no state");
-  void* m = nullptr;
-  if (int r = workspace(sizeof(float) * 3 * size_t(h->nodes()), &m)) return r;
-  hipError_t e = lbrr::closure_features(h->storage, h->buf[h->cur], static_cast<float*>(m), h->args(), a_target,
-                                        plain_weight, features, labels, h->stream);
+  hipError_t e = lbrr::closure_features(h->storage, h->buf[h->cur], h->args(), a_target, plain_weight, features, labels,
+                                        h->stream);
   if (e != hipSuccess) return hip_fail(e, "closure features");
   return LB_OK;
 }

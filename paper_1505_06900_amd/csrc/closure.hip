@@ -27,6 +27,12 @@ static_assert(kMlpNPacked == kNPacked && kMlpNParam == kNParam && kMlpNNorm == k
 //   rho_c = box(rho), j_c = box(rho u), u_c = j_c / rho_c,
 //   T = box(rho u u) - rho_c u_c u_c          (sub-filter stress),
 //   pi1_c = alpha box(pi1) + beta T.
+//
+// Small boxes (F <= kCoarsenNarrow), one thread per box: its few rows of F values
+// share their cache lines with the neighbours'.  Bound: HBM (6 values a fine node);
+// 1024^2 FP64 by 2: 12.3 us (through LDS 16.9), by 4: 11.9 (12.2).
+constexpr int kCoarsenNarrow = 4;
+
 template <class T>
 __global__ void __launch_bounds__(256) k_coarsen(const T* __restrict__ rho, const T* __restrict__ u,
                                                  const T* __restrict__ pi1, int nfx, int nfy, int F, double alpha,
@@ -64,6 +70,76 @@ __global__ void __launch_bounds__(256) k_coarsen(const T* __restrict__ rho, cons
   pi1_c[2 * nc + c] = alpha * vyy * inv + beta * tyy;
 }
 
+// Wider boxes: a block takes 256 / F of them beside each other (one if F > 256), a
+// thread a column of the box (every 256th): it adds its F rows, the lanes of a wave
+// reading side by side; the columns are then added through LDS, one thread per sum
+// and box.  Bound: HBM.  FP64, against a thread per box: 1024^2 by 8 30.2 -> 11.2 us
+// (4.5 TB/s), 2048^2 by 16 206 -> 30.4, 1024^2 by 64 2834 -> 18.4, 1000^2 by 5
+// 14.3 -> 11.8.  (Columns added between the lanes of a wave: 15.1, 32.9, 78.6 us.)
+constexpr int kCoarsenThreads = 256;
+
+template <class T>
+__global__ void __launch_bounds__(kCoarsenThreads) k_coarsen_wide(const T* __restrict__ rho, const T* __restrict__ u,
+                                                                  const T* __restrict__ pi1, int nfx, int nfy, int F,
+                                                                  double alpha, double beta, double* __restrict__ rho_c,
+                                                                  double* __restrict__ u_c,
+                                                                  double* __restrict__ pi1_c) {
+  __shared__ double part[9][kCoarsenThreads], total[9][kCoarsenThreads];
+  const int ncx = nfx / F, ncy = nfy / F;
+  const int64_t nc = int64_t(ncx) * ncy, nfine = int64_t(nfx) * nfy;
+  const int width = F < kCoarsenThreads ? F : kCoarsenThreads;  // threads of a box
+  const int boxes = kCoarsenThreads / width;
+  const int t = int(threadIdx.x), box = t / width, col = t - box * width;
+  const int gx = (ncx + boxes - 1) / boxes;
+  const int64_t groups = int64_t(gx) * ncy;
+  const double inv = 1.0 / (double(F) * double(F));
+  for (int64_t group = blockIdx.x; group < groups; group += gridDim.x) {
+    const int cy = int(group / gx), cx0 = int(group - int64_t(cy) * gx) * boxes;
+    const int here = boxes < ncx - cx0 ? boxes : ncx - cx0;
+    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (box < here) {
+      for (int dx = col; dx < F; dx += width) {
+        int64_t n = int64_t(cy) * F * nfx + (int64_t(cx0) + box) * F + dx;
+#pragma unroll 4
+        for (int dy = 0; dy < F; ++dy, n += nfx) {
+          const double r = double(rho[n]), ux = double(u[n]), uy = double(u[nfine + n]);
+          v[0] += r;
+          v[1] += r * ux;
+          v[2] += r * uy;
+          v[3] += r * ux * ux;
+          v[4] += r * ux * uy;
+          v[5] += r * uy * uy;
+          v[6] += double(pi1[n]);
+          v[7] += double(pi1[nfine + n]);
+          v[8] += double(pi1[2 * nfine + n]);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) part[k][t] = v[k];
+    __syncthreads();
+    for (int i = t; i < 9 * here; i += kCoarsenThreads) {
+      const int k = i / here, b = i - k * here;
+      double sum = 0;
+      for (int j = 0; j < width; ++j) sum += part[k][b * width + j];
+      total[k][b] = sum;
+    }
+    __syncthreads();  // total is written again only after the next group's first barrier
+    if (t < here) {
+      const int64_t c = int64_t(cy) * ncx + cx0 + t;
+      const double rc = total[0][t] * inv, ux = total[1][t] * inv / rc, uy = total[2][t] * inv / rc;
+      const double txx = total[3][t] * inv - rc * ux * ux, txy = total[4][t] * inv - rc * ux * uy,
+                   tyy = total[5][t] * inv - rc * uy * uy;
+      rho_c[c] = rc;
+      u_c[c] = ux;
+      u_c[nc + c] = uy;
+      pi1_c[c] = alpha * total[6][t] * inv + beta * txx;
+      pi1_c[nc + c] = alpha * total[7][t] * inv + beta * txy;
+      pi1_c[2 * nc + c] = alpha * total[8][t] * inv + beta * tyy;
+    }
+  }
+}
+
 // (rho - rho0, u_x, u_y) of the stored D2Q9 state at element offset off.
 template <class S>
 __device__ __forceinline__ void node_moments3(const S* __restrict__ src, const StepArgs& a, int64_t off,
@@ -76,19 +152,6 @@ __device__ __forceinline__ void node_moments3(const S* __restrict__ src, const S
   v[0] = float(h.drho);
   v[1] = float(h.ux);
   v[2] = float(h.uy);
-}
-
-// (rho - rho0, u_x, u_y) of every node of a stored D2Q9 state (compact [3][ny][nx]).
-template <class S>
-__global__ void __launch_bounds__(256) k_node_moments(const S* __restrict__ src, StepArgs a, float* __restrict__ m) {
-  const int64_t nodes = int64_t(a.nx) * a.ny;
-  const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (n >= nodes) return;
-  float v[3];
-  node_moments3<S>(src, a, node_offset(a, uint32_t(n)), v);
-  m[n] = v[0];
-  m[nodes + n] = v[1];
-  m[2 * nodes + n] = v[2];
 }
 
 // Pull the 9 pre-collision deviations of node (x, y) from a stored state.
@@ -104,50 +167,64 @@ __device__ __forceinline__ void pull9(const S* __restrict__ src, const StepArgs&
   });
 }
 
-// The 36 raw features of node (x, y): pulled deviations, then the 3 x 3
-// neighbourhood (dy outer, dx inner) of (rho - rho0, u_x, u_y) of the stored state.
-template <class R>
-__device__ __forceinline__ void features36(const R (&f)[9], const float* __restrict__ m, const StepArgs& a, int x,
-                                           int y, float (&feat)[kIn]) {
+// Features of the next step and labels a_target - plain_weight * (plain a1^(2) of
+// the pulled populations) (a_target NULL reads as 0), one thread per node of a tile.
+// The 36 features: pulled deviations, then the 3 x 3 neighbourhood (dy outer, dx
+// inner) of (rho - rho0, u_x, u_y) of the stored state, which the block forms once
+// for its tile and rim.  Rows of features go through LDS, so that a wave writes side
+// by side (stride kIn + 1: no bank conflicts).  Bound on the grids it is used on
+// (256^2: 256 blocks): latency.  256^2 FP64: 3.4 + 7.5 us with the moments from a launch
+// of their own and each thread writing its 144 bytes, 9.4 us so.
+constexpr int kFeatX = 64, kFeatY = 4;
+
+template <class S>
+__global__ void __launch_bounds__(kFeatX * kFeatY) k_features(const S* __restrict__ src, StepArgs a,
+                                                              const double* __restrict__ a_target, double plain_weight,
+                                                              float* __restrict__ feat_out,
+                                                              float* __restrict__ lab_out) {
+  using R = typename Prec<S>::R;
+  constexpr int BX = kFeatX, BY = kFeatY, RX = BX + 2, RY = BY + 2;
+  __shared__ float mom[3][RY][RX];
+  __shared__ float rows[BX * BY * (kIn + 1)];
   const int64_t nodes = int64_t(a.nx) * a.ny;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) feat[i] = float(f[i]);
-  int k = 9;
-#pragma unroll
-  for (int dy = -1; dy <= 1; ++dy) {
-    const int yy = (y + dy + a.ny) % a.ny;
-#pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) {
-      const int xx = (x + dx + a.nx) % a.nx;
-      const int64_t n = int64_t(yy) * a.nx + xx;
-      feat[k++] = m[n];
-      feat[k++] = m[nodes + n];
-      feat[k++] = m[2 * nodes + n];
+  const int64_t gx = (a.nx + BX - 1) / BX, tiles = gx * ((a.ny + BY - 1) / BY);
+  const int t = int(threadIdx.x), tx = t % BX, ty = t / BX;
+  const unsigned nx = unsigned(a.nx), ny = unsigned(a.ny);
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int x0 = int(tile % gx) * BX, y0 = int(tile / gx) * BY;
+    for (int i = t; i < RX * RY; i += BX * BY) {
+      const int c = i % RX, r = i / RX;
+      const unsigned x = (unsigned(x0 + c) + nx - 1) % nx, y = (unsigned(y0 + r) + ny - 1) % ny;
+      float v[3];
+      node_moments3<S>(src, a, int64_t(y) * a.sy + x, v);
+      mom[0][r][c] = v[0];
+      mom[1][r][c] = v[1];
+      mom[2][r][c] = v[2];
+    }
+    __syncthreads();
+    const int x = x0 + tx, y = y0 + ty;
+    if (x < a.nx && y < a.ny) {
+      const int64_t n = int64_t(y) * a.nx + x;
+      R f[9];
+      pull9<S, R>(src, a, x, y, f);
+      float* row = rows + t * (kIn + 1);
+      sfor<0, 9>([&](auto I) { row[I] = float(f[I]); });
+      sfor<0, 9>([&](auto J) {
+        sfor<0, 3>([&](auto C) { row[9 + 3 * J + C] = mom[C][ty + J / 3][tx + J % 3]; });
+      });
+      const Moments<R> mo = raw_moments<D2Q9, R>(f);
+      const Hydro<R> h = hydro<D2Q9, R>(mo, R(a.rho0));
+      const double ap[3] = {double(h.axx), double(h.axy), double(h.ayy)};
+      for (int c = 0; c < 3; ++c)
+        lab_out[n * 3 + c] = float((a_target ? a_target[int64_t(c) * nodes + n] : 0.0) - plain_weight * ap[c]);
+    }
+    __syncthreads();  // rows are written again only after the next tile's first barrier
+    const int width = (BX < a.nx - x0 ? BX : a.nx - x0) * kIn;
+    for (int r = 0; r < BY && y0 + r < a.ny; ++r) {
+      float* out = feat_out + (int64_t(y0 + r) * a.nx + x0) * kIn;
+      for (int i = t; i < width; i += BX * BY) out[i] = rows[(r * BX + i / kIn) * (kIn + 1) + i % kIn];
     }
   }
-}
-
-// Features of the next step and labels a_target - plain_weight * (plain
-// a1^(2) of the pulled populations) (a_target NULL reads as 0), one thread per node.
-template <class S>
-__global__ void __launch_bounds__(256) k_features(const S* __restrict__ src, const float* __restrict__ m, StepArgs a,
-                                                  const double* __restrict__ a_target, double plain_weight,
-                                                  float* __restrict__ feat_out, float* __restrict__ lab_out) {
-  using R = typename Prec<S>::R;
-  const int64_t nodes = int64_t(a.nx) * a.ny;
-  const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (n >= nodes) return;
-  const int x = int(n % a.nx), y = int(n / a.nx);
-  R f[9];
-  pull9<S, R>(src, a, x, y, f);
-  float feat[kIn];
-  features36<R>(f, m, a, x, y, feat);
-  for (int k = 0; k < kIn; ++k) feat_out[n * kIn + k] = feat[k];
-  const Moments<R> mo = raw_moments<D2Q9, R>(f);
-  const Hydro<R> h = hydro<D2Q9, R>(mo, R(a.rho0));
-  const double ap[3] = {double(h.axx), double(h.axy), double(h.ayy)};
-  for (int c = 0; c < 3; ++c)
-    lab_out[n * 3 + c] = float((a_target ? a_target[int64_t(c) * nodes + n] : 0.0) - plain_weight * ap[c]);
 }
 
 // ---------------------------------------------------------------------------
@@ -880,13 +957,12 @@ hipError_t step_closure_s(int order, const void* src, void* dst, const StepArgs&
 }
 
 template <class S>
-hipError_t features_s(const void* src, float* m, const StepArgs& a, const double* a_target, double plain_weight,
-                      float* feat, float* lab, hipStream_t s) {
-  const int64_t nodes = int64_t(a.nx) * a.ny;
-  const unsigned g = unsigned((nodes + 255) / 256);
-  hipLaunchKernelGGL((k_node_moments<S>), dim3(g), dim3(256), 0, s, static_cast<const S*>(src), a, m);
-  hipLaunchKernelGGL((k_features<S>), dim3(g), dim3(256), 0, s, static_cast<const S*>(src), m, a, a_target,
-                     plain_weight, feat, lab);
+hipError_t features_s(const void* src, const StepArgs& a, const double* a_target, double plain_weight, float* feat,
+                      float* lab, hipStream_t s) {
+  const int64_t tiles = int64_t((a.nx + kFeatX - 1) / kFeatX) * ((a.ny + kFeatY - 1) / kFeatY);
+  const int64_t g = tiles < (1 << 20) ? tiles : (1 << 20);  // blocks stride over the rest
+  hipLaunchKernelGGL((k_features<S>), dim3(unsigned(g)), dim3(kFeatX * kFeatY), 0, s, static_cast<const S*>(src), a,
+                     a_target, plain_weight, feat, lab);
   return hipGetLastError();
 }
 
@@ -902,28 +978,35 @@ hipError_t closure_step(int order, int storage, const void* src, void* dst, cons
   return hipErrorInvalidValue;
 }
 
-hipError_t closure_features(int storage, const void* src, float* m, const StepArgs& a, const double* a_target,
+hipError_t closure_features(int storage, const void* src, const StepArgs& a, const double* a_target,
                             double plain_weight, float* feat, float* lab, hipStream_t s) {
   switch (storage) {
-    case 0: return features_s<double>(src, m, a, a_target, plain_weight, feat, lab, s);
-    case 1: return features_s<float>(src, m, a, a_target, plain_weight, feat, lab, s);
-    case 2: return features_s<_Float16>(src, m, a, a_target, plain_weight, feat, lab, s);
+    case 0: return features_s<double>(src, a, a_target, plain_weight, feat, lab, s);
+    case 1: return features_s<float>(src, a, a_target, plain_weight, feat, lab, s);
+    case 2: return features_s<_Float16>(src, a, a_target, plain_weight, feat, lab, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t closure_coarsen(int dtype, const void* rho, const void* u, const void* pi1, int nfx, int nfy, int F,
                            double alpha, double beta, double* rho_c, double* u_c, double* pi1_c, hipStream_t s) {
-  const int64_t nc = int64_t(nfx / F) * (nfy / F);
-  const unsigned g = unsigned((nc + 255) / 256);
-  if (dtype == 0)
-    hipLaunchKernelGGL((k_coarsen<double>), dim3(g), dim3(256), 0, s, static_cast<const double*>(rho),
-                       static_cast<const double*>(u), static_cast<const double*>(pi1), nfx, nfy, F, alpha, beta, rho_c, u_c,
-                       pi1_c);
-  else
-    hipLaunchKernelGGL((k_coarsen<float>), dim3(g), dim3(256), 0, s, static_cast<const float*>(rho),
-                       static_cast<const float*>(u), static_cast<const float*>(pi1), nfx, nfy, F, alpha, beta, rho_c, u_c,
-                       pi1_c);
+  auto launch = [&](auto type) {
+    using T = decltype(type);
+    const T *r = static_cast<const T*>(rho), *v = static_cast<const T*>(u), *p = static_cast<const T*>(pi1);
+    if (F <= kCoarsenNarrow) {
+      const int64_t nc = int64_t(nfx / F) * (nfy / F);
+      hipLaunchKernelGGL((k_coarsen<T>), dim3(unsigned((nc + 255) / 256)), dim3(256), 0, s, r, v, p, nfx, nfy, F, alpha,
+                         beta, rho_c, u_c, pi1_c);
+    } else {
+      const int boxes = F < kCoarsenThreads ? kCoarsenThreads / F : 1;
+      const int64_t groups = int64_t((nfx / F + boxes - 1) / boxes) * (nfy / F);
+      const int64_t g = groups < (1 << 20) ? groups : (1 << 20);  // blocks stride over the rest
+      hipLaunchKernelGGL((k_coarsen_wide<T>), dim3(unsigned(g)), dim3(kCoarsenThreads), 0, s, r, v, p, nfx, nfy, F,
+                         alpha, beta, rho_c, u_c, pi1_c);
+    }
+  };
+  if (dtype == 0) launch(double{});
+  else launch(float{});
   return hipGetLastError();
 }
 

@@ -17,7 +17,7 @@ constexpr int kMlpIn = 36;
 
 hipError_t closure_step(int order, int storage, const void* src, void* dst, const StepArgs& a,
                         const uint16_t* packed, const float* params, const float* norm, hipStream_t s);
-hipError_t closure_features(int storage, const void* src, float* m, const StepArgs& a, const double* a_target,
+hipError_t closure_features(int storage, const void* src, const StepArgs& a, const double* a_target,
                             double plain_weight, float* feat, float* lab, hipStream_t s);
 hipError_t closure_coarsen(int dtype, const void* rho, const void* u, const void* pi1, int nfx, int nfy, int F,
                            double alpha, double beta, double* rho_c, double* u_c, double* pi1_c, hipStream_t s);
