@@ -108,14 +108,14 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // serial march), longer ones where their edge rows cost traffic.  us a step, order
 // 4, single / lz = 1 / 2 / 4 / 6 / 12:
 //   FP32   64^2  2.66 / 1.92 / 2.29 / 3.11 / 3.85 / 6.17    501^2  5.42 / 4.02 / 3.55 / 3.76 / 4.41 / 6.72
-//        1024^2 14.5 / 14.3 / 12.0 / 10.2 / 10.8 / 10.8    2048^2 49.9 / 43.8 / 36.1 / 33.8 / 33.8 / 34.3
+//        1024^2 14.5 / 14.3 / 11.9 / 10.1 / 10.8 / 10.4    2048^2 49.9 / 43.8 / 35.9 / 32.8 / 32.5 / 33.2
 //   FP64  256^2  4.49 / 3.75 / 3.76 / 4.46 / 5.69 / 9.22    501^2  8.30 / 6.89 / 5.06 / 6.07 / 6.52 / 9.32
-//        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.1 / 62.3 / 60.9 / 62.7
+//        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.4 / 62.1 / 61.0 / 61.3
 // (walled boxes within a few per cent of these: 501^2 FP64 8.51 / 7.16 / 5.22 / 5.86).
 //
 // 3D (GLUPS, order 4, single steps -> pairs), cubes of side n:
 //            n = 256         320         200         128          64
-//   D3Q27 FP32 27.3 -> 44.1  27.0 -> 41.7  22.9 -> 33.1  26.4 -> 37.5  22.3 -> 30.9
+//   D3Q27 FP32 27.3 -> 44.6  27.0 -> 41.7  22.9 -> 33.1  26.4 -> 37.5  22.3 -> 30.9
 //   D3Q19 FP32 40.0 -> 61.5  39.1 -> 61.2  33.1 -> 49.3  38.0 -> 49.2  30.8 -> 35.3
 //   D3Q27 FP64 12.5 -> 21.6  11.7 -> 21.0  12.9 -> 17.9  13.0 -> 20.5  12.2 -> 16.5
 //   D3Q19 FP64 18.3 -> 33.0  17.2 -> 31.6  18.9 -> 25.7  18.6 -> 29.5  16.5 -> 23.7

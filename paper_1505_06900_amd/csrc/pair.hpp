@@ -9,11 +9,11 @@
 // the same operations and order, on values of the storage type: two steps here
 // give the bits of two launches of k_step.
 //
-// D3Q27 order 4 FP32 at 256^3: 0.762 ms for two steps (44.1 GLUPS) against
-// 2 x 0.614 ms (27.3).  rocprofv3 at 8 rows and 16 planes a block: reads 1.34x the state
-// (rim rows and chunk edges), writes 1.00x, 4.24 GB at 5.1 TB/s; VALU busy 40%.
-// FP64: 1.56 ms against 2 x 1.34 ms, reads 1.61x, 6.1 TB/s.  So it is held by its
-// traffic again, at 0.54 of the traffic of two single steps.
+// D3Q27 order 4 FP32 at 256^3: 0.749 ms for two steps (44.8 GLUPS) against
+// 2 x 0.614 ms (27.3).  rocprofv3 at 8 rows a block: reads 1.27x the state (rim rows and
+// chunk edges), writes 1.00x, 4.11 GB at 5.5 TB/s; VALU busy 51%.  FP64: 1.54 ms against
+// 2 x 1.34 ms, reads 1.55x, 6.0 TB/s.  So it is held by its traffic again, at 0.57 of
+// the traffic of two single steps.
 //
 // FP16 storage keeps single steps: they are near their VALU bound (D3Q19) or
 // would have to round the first step's populations to keep the bits.
