@@ -72,7 +72,8 @@ struct TilePlan {
 };
 
 // 3D (tile.hpp): a compute unit holds one block, a block's time grows with the
-// planes it rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are
+// planes it rebuilds (lz + 2) and with its waves (rows + 3; narrow tiles, taken for at
+// most their 32 columns, rows / 2 + 2), and the tile rows are
 // dealt to the eight XCDs in turn, so the plan taken is the one with the smallest
 //   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
 // forced_lz, forced_rows: > 0 overrides the choice (forced_rows if built).
@@ -84,13 +85,13 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
   bool built = false;
   for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) built = built || rows == forced_rows;
   for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) {
-    if (built && rows != forced_rows) continue;
+    if (built ? rows != forced_rows : rows == lbrr::kNarrowRows && nx > 32) continue;
     const int64_t gy = (ny + rows - 1) / rows;
     for (int chunks = 1; chunks <= nz; ++chunks) {
       const int lz = forced_lz > 0 ? forced_lz : (nz + chunks - 1) / chunks;
       const int64_t g = gy * ((nz + lz - 1) / lz);
       const int64_t rounds = (gx * ((g + 7) / 8) + slots - 1) / slots;
-      const int64_t c = rounds * (lz + 2) * (rows + 3);
+      const int64_t c = rounds * (lz + 2) * (rows == lbrr::kNarrowRows ? rows / 2 + 2 : rows + 3);
       if (p.lz == 0 || c < cost) {
         p.rows = rows;
         p.lz = lz;

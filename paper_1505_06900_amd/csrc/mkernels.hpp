@@ -581,21 +581,19 @@ __global__ void __launch_bounds__(256) k_mpopulations(const S* __restrict__ src,
 
 // ---------------------------------------------------------------------------
 // Launchers.  a.lz = z-planes per block of the 3D step (each chunk rebuilds
-// lz + 2 planes); the host picks it.  Measured with 32 x 16 patches, 256^3
-// D3Q27 FP32: patches of 8, 16 and 32 rows within 6%; dispatching the z-chunks
-// of a tile next to each other gave 24-27 GLUPS at 256^3 and 512^3 for lz = 2
-// to 32; padding the z-planes off multiples of 64 KiB changed nothing;
-// contiguous tile ranges per XCD removed the fall-off at large planes but did
-// not beat the 64 x 8 patches in plain order.
+// lz + 2 planes) and a.rows = its tile height; the host picks both.
 // Tile heights of the 3D step the host chooses from (tile_plan in api.hip).  GLUPS
 // at 256^3, order 4, by rows: D3Q27 FP32 5 / 8 / 9 / 11 / 13 rows 52.6 / 56.6 / 54.1 / 56.3 /
 // 58.8, D3Q19 FP32 51.9 / 58.8 / 56.1 / 61.6 / 59.7, D3Q27 FP64 3 / 4 / 5 rows 23.5 / 27.0 /
 // 27.5 (6 rows spill: 12.7), D3Q19 FP64 26.0 / 30.0 / 30.1.  The lower tiles serve boxes whose rows
-// the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).
+// the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).  FP64 boxes
+// of at most 32 columns leave half of a 64-column tile idle: 32 columns by 12 rows in
+// the same eight waves (us a step, D3Q19 273 x 67 x 25 41.8 -> 30.9, 200 x 200 x 32 79.8 -> 52.9;
+// at 40 columns 64-column tiles 83.1, 32-column ones 88.1).
 template <class S>
 constexpr int mom_rows_option(int i) {
-  constexpr int f32[] = {13, 11, 8}, f64[] = {5, 4};
-  return sizeof(S) == 8 ? (i < 2 ? f64[i] : 0) : (i < 3 ? f32[i] : 0);
+  constexpr int f32[] = {13, 11, 8}, f64[] = {5, 4, kNarrowRows};
+  return i > 2 ? 0 : (sizeof(S) == 8 ? f64[i] : f32[i]);
 }
 
 template <class L, int N, class S, int TY>
@@ -628,9 +626,7 @@ hipError_t launch_mstep(const void* src, void* dst, const StepArgs& a, hipStream
     if (int64_t(a.ny) * a.sy * int64_t(sizeof(S)) >= (int64_t(1) << 32)) return hipErrorInvalidValue;
     if (a.rows == mom_rows_option<S>(0)) return launch_mstep_t<L, N, S, mom_rows_option<S>(0)>(src, dst, a, s);
     if (a.rows == mom_rows_option<S>(1)) return launch_mstep_t<L, N, S, mom_rows_option<S>(1)>(src, dst, a, s);
-    if constexpr (mom_rows_option<S>(2) != 0) {
-      if (a.rows == mom_rows_option<S>(2)) return launch_mstep_t<L, N, S, mom_rows_option<S>(2)>(src, dst, a, s);
-    }
+    if (a.rows == mom_rows_option<S>(2)) return launch_mstep_t<L, N, S, mom_rows_option<S>(2)>(src, dst, a, s);
     return hipErrorInvalidValue;
   }
 }

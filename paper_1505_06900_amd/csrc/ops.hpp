@@ -8,6 +8,8 @@
 
 namespace lbrr {
 
+constexpr int kNarrowRows = 12;  // tile height that stands for tiles of 32 columns (tile.hpp)
+
 constexpr int kReduceBlock = 256;
 // Launch parameters shared by the kernels.  Population (or moment field) i of node (x, y, z)
 // lives at element i*si + z*sz + y*sy + x of a buffer; the host picks the

@@ -2,7 +2,8 @@
 // segment starting at a multiple of 64) by TY rows through a chunk of a.lz planes,
 // and brings the populations of the tile and of its one-node rim into LDS plane by
 // plane.  TY + 2 waves hold the tile's columns of rows y0 - 1 .. y0 + TY (a wave per
-// row) and one more wave the two columns beside the tile.
+// row) and one more wave the two columns beside the tile.  TY = kNarrowRows is the
+// tile of narrow boxes: 32 columns, two rows a wave.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,10 +17,14 @@ namespace lbrr {
 
 template <int TY>
 struct Tile {
-  static constexpr int kRows = TY + 2, kCols = 66;  // patch in LDS: the tile and its rim
+  static constexpr int kWidth = TY == kNarrowRows ? 32 : 64;  // columns of the tile
+  static constexpr int kPerWave = 64 / kWidth;                // rows a wave holds
+  static constexpr int kRows = TY + 2, kCols = kWidth + 2;    // patch in LDS: the tile and its rim
+  static constexpr int kRowWaves = kRows / kPerWave;
+  static_assert(kRows % kPerWave == 0, "whole waves of rows");
   static_assert(2 * kRows <= 64, "one wave holds both rim columns of every patch row");
   bool empty;       // block past the last tile row
-  int lane;
+  int lane;         // column of the tile this thread holds
   int r, col;       // the node this thread brings: patch row, LDS column,
   int px, py;       //   lattice node
   bool writes;      //   inside the patch
@@ -32,40 +37,41 @@ struct Tile {
   // columns a block reads are lines its XCD's L2 holds for the neighbour.  Tile
   // rows past the last of a group of eight are empty.
   __device__ __forceinline__ explicit Tile(const StepArgs& a) {
-    lane = int(threadIdx.x) & 63;
+    const int thread = int(threadIdx.x) & 63;  // of its wave
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int gx = (a.nx + 63) / 64, gy = (a.ny + TY - 1) / TY, gz = (a.nz + a.lz - 1) / a.lz;
+    lane = thread & (kWidth - 1);
+    const int gx = (a.nx + kWidth - 1) / kWidth, gy = (a.ny + TY - 1) / TY, gz = (a.nz + a.lz - 1) / a.lz;
     const int b = int(blockIdx.x);
     const int bxi = (b / 8) % gx, g = (b / (8 * gx)) * 8 + b % 8;
     empty = g >= gy * gz;
     const int byi = g % gy, bz = g / gy;
-    const int x0 = bxi * 64, y0 = byi * TY;
-    const int width = (a.nx - x0 < 64) ? a.nx - x0 : 64;
-    if (wave < kRows) {
-      r = wave;
+    const int x0 = bxi * kWidth, y0 = byi * TY;
+    const int width = (a.nx - x0 < kWidth) ? a.nx - x0 : kWidth;
+    if (wave < kRowWaves) {
+      r = kPerWave == 1 ? wave : wave * kPerWave + thread / kWidth;
       writes = lane < width;
       col = lane + 1;
       px = x0 + (writes ? lane : 0);
     } else {
-      const bool left = lane < kRows;
-      writes = lane < 2 * kRows;
-      r = left ? lane : (writes ? lane - kRows : 0);
+      const bool left = thread < kRows;
+      writes = thread < 2 * kRows;
+      r = left ? thread : (writes ? thread - kRows : 0);
       col = left ? 0 : width + 1;
       px = wrap_axis(left ? x0 - 1 : x0 + width, a.nx);
     }
     py = wrap_axis(y0 - 1 + r, a.ny);
     x = x0 + lane;
     y = y0 + r - 1;
-    inner = wave < kRows && r >= 1 && r <= TY && lane < width && y < a.ny;
+    inner = wave < kRowWaves && r >= 1 && r <= TY && lane < width && y < a.ny;
     z0 = bz * a.lz;
     z1 = (z0 + a.lz < a.nz) ? z0 + a.lz : a.nz;
   }
   // blocks of a launch, all tiles dealt to the XCDs in groups of eight tile rows
   static int64_t blocks(const StepArgs& a) {
     const int64_t rows = int64_t((a.ny + TY - 1) / TY) * ((a.nz + a.lz - 1) / a.lz);
-    return int64_t((a.nx + 63) / 64) * 8 * ((rows + 7) / 8);
+    return int64_t((a.nx + kWidth - 1) / kWidth) * 8 * ((rows + 7) / 8);
   }
-  static constexpr int threads() { return 64 * (TY + 3); }
+  static constexpr int threads() { return 64 * (kRowWaves + 1); }
 };
 
 // What an inner thread keeps of the layer c_z = CZ that arrived at its node: the
