@@ -145,10 +145,11 @@ template <class S>
 __device__ __forceinline__ void node_moments3(const S* __restrict__ src, const StepArgs& a, int64_t off,
                                               float (&v)[3]) {
   using R = typename Prec<S>::R;
+  using L = Stored<D2Q9, S>;
   R f[9];
   sfor<0, 9>([&](auto I) { f[I] = R(src[int64_t(I) * a.si + off]); });
-  const Moments<R> mo = raw_moments<D2Q9, R>(f);
-  const Hydro<R> h = hydro<D2Q9, R>(mo, R(a.rho0));
+  const Moments<R> mo = raw_moments<L, R>(f);
+  const Hydro<R> h = hydro<L, R>(mo, R(a.rho0));
   v[0] = float(h.drho);
   v[1] = float(h.ux);
   v[2] = float(h.uy);
@@ -183,6 +184,7 @@ __global__ void __launch_bounds__(kFeatX * kFeatY) k_features(const S* __restric
                                                               float* __restrict__ feat_out,
                                                               float* __restrict__ lab_out) {
   using R = typename Prec<S>::R;
+  using L = Stored<D2Q9, S>;
   constexpr int BX = kFeatX, BY = kFeatY, RX = BX + 2, RY = BY + 2;
   __shared__ float mom[3][RY][RX];
   __shared__ float rows[BX * BY * (kIn + 1)];
@@ -212,8 +214,8 @@ __global__ void __launch_bounds__(kFeatX * kFeatY) k_features(const S* __restric
       sfor<0, 9>([&](auto J) {
         sfor<0, 3>([&](auto C) { row[9 + 3 * J + C] = mom[C][ty + J / 3][tx + J % 3]; });
       });
-      const Moments<R> mo = raw_moments<D2Q9, R>(f);
-      const Hydro<R> h = hydro<D2Q9, R>(mo, R(a.rho0));
+      const Moments<R> mo = raw_moments<L, R>(f);
+      const Hydro<R> h = hydro<L, R>(mo, R(a.rho0));
       const double ap[3] = {double(h.axx), double(h.axy), double(h.ayy)};
       for (int c = 0; c < 3; ++c)
         lab_out[n * 3 + c] = float((a_target ? a_target[int64_t(c) * nodes + n] : 0.0) - plain_weight * ap[c]);
@@ -785,6 +787,7 @@ __global__ void __launch_bounds__(kClosureSamples * WPR)
     k_step_closure(const S* __restrict__ src, S* __restrict__ dst, StepArgs a, const uint16_t* __restrict__ packed,
                    const float* __restrict__ params, const float* __restrict__ norm) {
   using R = typename Prec<S>::R;
+  using L = Stored<D2Q9, S>;
   constexpr int kThreads = kClosureSamples * WPR, kTiles = 4 / WPR;  // sample tiles of 16 per wave
   // standardised BF16 inputs; the padding keeps the operand reads of k 48 .. 63 (set to zero) of the last row inside
   __shared__ __attribute__((aligned(16))) uint16_t xs[kClosureSamples * kLd1 + 16];
@@ -841,8 +844,8 @@ __global__ void __launch_bounds__(kClosureSamples * WPR)
   for (int h = 0; h < kPer; ++h) {
     const int k = int(threadIdx.x) + h * kThreads;
     if (k < kClosureHalo) {
-      const Moments<R> mo = raw_moments<D2Q9, R>(p[h]);
-      const Hydro<R> hh = hydro<D2Q9, R>(mo, R(a.rho0));
+      const Moments<R> mo = raw_moments<L, R>(p[h]);
+      const Hydro<R> hh = hydro<L, R>(mo, R(a.rho0));
       *reinterpret_cast<f32x4*>(&nb[k / 66][k % 66][0]) = f32x4{float(hh.drho), float(hh.ux), float(hh.uy), 0.0f};
     }
   }
@@ -894,16 +897,16 @@ __global__ void __launch_bounds__(kClosureSamples * WPR)
   lds_barrier();
   if (!owner) return;
   const f32x4 yv = *reinterpret_cast<const f32x4*>(&ys[64 * row + lane][0]);
-  const Moments<R> mo = raw_moments<D2Q9, R>(f);
-  Hydro<R> h = hydro<D2Q9, R>(mo, R(a.rho0));
+  const Moments<R> mo = raw_moments<L, R>(f);
+  Hydro<R> h = hydro<L, R>(mo, R(a.rho0));
   const float* ym = cst + 2 * kIn;
   const float* ysd = ym + kOut;
   h.axx += R(yv[0] * ysd[0] + ym[0]);
   h.axy += R(yv[1] * ysd[1] + ym[1]);
   h.ayy += R(yv[2] * ysd[2] + ym[2]);
   R C[3][3][3];
-  coefficients<D2Q9, N, R>(h, R(a.omega1), C);
-  reconstruct<D2Q9, N, R>(C, f);
+  coefficients<L, N, R>(h, R(a.omega1), C);
+  reconstruct<L, N, R>(C, f);
   if (active) {
     S* out = dst + int64_t(y) * a.sy + x;
     sfor<0, 9>([&](auto I) { __builtin_nontemporal_store(to_store<S, R>(f[I]), out + int64_t(I) * a.si); });

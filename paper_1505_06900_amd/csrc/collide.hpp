@@ -42,6 +42,20 @@ __device__ __forceinline__ void sfor(F&& f) {
   }
 }
 
+// The lattice of a collision whose results are stored in FP16.  It keeps plain sums and
+// products, contracted by the compiler, where the collision of the other storages
+// writes out its multiply-adds and sums layer by layer: no step pair needs the bits of
+// FP16 single steps, and a last bit of FP32 that falls the other way moves a stored
+// value by 2^-11 of it, which ten steps at 512^3 (D3Q19) spread over a state's
+// populations.  So FP16 runs and saved FP16 states reproduce from one version of the
+// library to the next.
+template <class L>
+struct Fp16State : L {};
+template <class L>
+constexpr bool kPlainSums = false;
+template <class L>
+constexpr bool kPlainSums<Fp16State<L>> = true;
+
 // Raw moments of the deviations: 0th, 1st and 2nd order.
 template <class R>
 struct Moments {
@@ -137,9 +151,40 @@ __device__ __forceinline__ Moments<R> join_layers(const LayerSums<R>& m, const L
   return r;
 }
 
+// Sum over the q velocities of cx^A cy^B cz^C f_i in lattice order (zero terms dropped at compile time).
+template <class L, int A, int B, int C, class R>
+__device__ __forceinline__ R moment_direct(const R* f) {
+  R s = R(-0.0);  // -0 + x == x exactly, so the first add folds away
+  sfor<0, L::Q>([&](auto I) {
+    constexpr int p = (A == 0 ? 1 : (A == 1 ? L::cx(I) : L::cx(I) * L::cx(I))) *
+                      (B == 0 ? 1 : (B == 1 ? L::cy(I) : L::cy(I) * L::cy(I))) *
+                      (C == 0 ? 1 : (C == 1 ? L::cz(I) : L::cz(I) * L::cz(I)));
+    if constexpr (p == 1) s = s + f[I];
+    if constexpr (p == -1) s = s - f[I];
+  });
+  return s;
+}
+
+template <class L, class R>
+__device__ __forceinline__ Moments<R> moments_direct(const R* f) {
+  Moments<R> r;
+  r.d0 = moment_direct<L, 0, 0, 0>(f);
+  r.jx = moment_direct<L, 1, 0, 0>(f);
+  r.jy = moment_direct<L, 0, 1, 0>(f);
+  r.jz = moment_direct<L, 0, 0, 1>(f);
+  r.pxx = moment_direct<L, 2, 0, 0>(f);
+  r.pyy = moment_direct<L, 0, 2, 0>(f);
+  r.pzz = moment_direct<L, 0, 0, 2>(f);
+  r.pxy = moment_direct<L, 1, 1, 0>(f);
+  r.pxz = moment_direct<L, 1, 0, 1>(f);
+  r.pyz = moment_direct<L, 0, 1, 1>(f);
+  return r;
+}
+
 // f holds the lattice's q populations in lattice order.
 template <class L, class R>
 __device__ __forceinline__ Moments<R> raw_moments(const R* f) {
+  if constexpr (kPlainSums<L> && !L::kProduct) return moments_direct<L, R>(f);
   auto get = [&](auto I) { return f[int(I)]; };
   const LayerSums<R> z = layer_sums<L, 0, R>(get);
   if constexpr (L::D == 3) {
@@ -161,30 +206,47 @@ __device__ __forceinline__ Moments<R> raw_moments(const R* f) {
 // Fused multiply-adds, written out: every product of the collision that meets a
 // sum does so in one of these, and no other product feeds a sum.  A contraction
 // left to the compiler can depend on what else a kernel does with the operands;
-// written out, every kernel that collides a node gives the same bits.
+// written out, every kernel that collides a node gives the same bits.  (FP16 states:
+// mul_add, add_mul and sub_mul leave it to the compiler, see Fp16State.)
 __device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <class L, class R>
+__device__ __forceinline__ R mul_add(R a, R b, R c) {
+  if constexpr (kPlainSums<L>) return a * b + c;
+  else return fused(a, b, c);
+}
+template <class L, class R>
+__device__ __forceinline__ R add_mul(R c, R a, R b) {
+  if constexpr (kPlainSums<L>) return c + a * b;
+  else return fused(a, b, c);
+}
+template <class L, class R>
+__device__ __forceinline__ R sub_mul(R c, R a, R b) {
+  if constexpr (kPlainSums<L>) return c - a * b;
+  else return fused(-a, b, c);
+}
 
 // 1/rho for rho = rho0 + drho rounded: the exact rounding error of the sum
 // (two-sum) corrects the reciprocal to first order.  Rounding rho to the
 // working precision would otherwise bias u = j/rho by up to half an ulp of
 // rho0 at every step, an error that accumulates in time.
-template <class R>
+template <class L, class R>
 __device__ __forceinline__ R inv_density(R rho0, R drho, R rho) {
   const R bb = rho - rho0;
   const R err = (rho0 - (rho - bb)) + (drho - bb);
   const R inv = R(1) / rho;
-  return fused(-(inv * inv), err, inv);
+  return sub_mul<L>(inv, inv * inv, err);
 }
 // FP32: the hardware reciprocal (within 1 ulp) and one Newton step
 // r (2 - rho r) in place of the IEEE division sequence; rho is near rho0, far
 // from zero, infinity and the denormals.
+template <class L>
 __device__ __forceinline__ float inv_density(float rho0, float drho, float rho) {
   const float bb = rho - rho0;
   const float err = (rho0 - (rho - bb)) + (drho - bb);
   float inv = __builtin_amdgcn_rcpf(rho);
   inv = __builtin_fmaf(inv, __builtin_fmaf(-rho, inv, 1.0f), inv);
-  return fused(-(inv * inv), err, inv);
+  return sub_mul<L>(inv, inv * inv, err);
 }
 
 // rho, u and a1^(2) = Pi - rho cs2 I - rho u u, written with deviations:
@@ -195,20 +257,20 @@ __device__ __forceinline__ Hydro<R> hydro(const Moments<R>& m, R rho0) {
   Hydro<R> h;
   h.drho = m.d0;
   h.rho = rho0 + m.d0;
-  const R inv = inv_density(rho0, m.d0, h.rho);
+  const R inv = inv_density<L>(rho0, m.d0, h.rho);
   h.jx = m.jx;
   h.jy = m.jy;
   h.ux = m.jx * inv;
   h.uy = m.jy * inv;
-  h.axx = fused(-m.jx, h.ux, fused(-m.d0, cs2, m.pxx));
-  h.ayy = fused(-m.jy, h.uy, fused(-m.d0, cs2, m.pyy));
-  h.axy = fused(-m.jx, h.uy, m.pxy);
+  h.axx = sub_mul<L>(sub_mul<L>(m.pxx, m.d0, cs2), m.jx, h.ux);
+  h.ayy = sub_mul<L>(sub_mul<L>(m.pyy, m.d0, cs2), m.jy, h.uy);
+  h.axy = sub_mul<L>(m.pxy, m.jx, h.uy);
   if constexpr (L::D == 3) {
     h.jz = m.jz;
     h.uz = m.jz * inv;
-    h.azz = fused(-m.jz, h.uz, fused(-m.d0, cs2, m.pzz));
-    h.axz = fused(-m.jx, h.uz, m.pxz);
-    h.ayz = fused(-m.jy, h.uz, m.pyz);
+    h.azz = sub_mul<L>(sub_mul<L>(m.pzz, m.d0, cs2), m.jz, h.uz);
+    h.axz = sub_mul<L>(m.pxz, m.jx, h.uz);
+    h.ayz = sub_mul<L>(m.pyz, m.jy, h.uz);
   } else {
     h.jz = h.uz = h.azz = h.axz = h.ayz = R(0);
   }
@@ -249,12 +311,12 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
             // a0: rho u^k, written as j_d times the remaining velocities; a1: pair
             // sum of the recursion
             if constexpr (n == 2) {
-              if constexpr (a == 2) C[a][b][c] = fused(h.jx, h.ux, sxx);
-              else if constexpr (b == 2) C[a][b][c] = fused(h.jy, h.uy, syy);
-              else if constexpr (c == 2) C[a][b][c] = fused(h.jz, h.uz, szz);
-              else if constexpr (c == 0) C[a][b][c] = fused(h.jx, h.uy, sxy);
-              else if constexpr (b == 0) C[a][b][c] = fused(h.jx, h.uz, sxz);
-              else C[a][b][c] = fused(h.jy, h.uz, syz);
+              if constexpr (a == 2) C[a][b][c] = mul_add<L>(h.jx, h.ux, sxx);
+              else if constexpr (b == 2) C[a][b][c] = mul_add<L>(h.jy, h.uy, syy);
+              else if constexpr (c == 2) C[a][b][c] = mul_add<L>(h.jz, h.uz, szz);
+              else if constexpr (c == 0) C[a][b][c] = mul_add<L>(h.jx, h.uy, sxy);
+              else if constexpr (b == 0) C[a][b][c] = mul_add<L>(h.jx, h.uz, sxz);
+              else C[a][b][c] = mul_add<L>(h.jy, h.uz, syz);
             } else {
               R s;
               if constexpr (!L::kProduct && n == 4) {
@@ -272,9 +334,9 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
                 auto term = [&](R v, auto I, auto J, auto K) __attribute__((always_inline)) {
                   constexpr int i = I, j = J, k = K;
                   static_assert(i + j + k >= 1, "a velocity factor per term");
-                  if constexpr (k > 0) s = fused(v * px[i] * py[j], pz[k], s);
-                  else if constexpr (j > 0) s = fused(v * px[i], py[j], s);
-                  else s = fused(v, px[i], s);
+                  if constexpr (k > 0) s = add_mul<L>(s, v * px[i] * py[j], pz[k]);
+                  else if constexpr (j > 0) s = add_mul<L>(s, v * px[i], py[j]);
+                  else s = add_mul<L>(s, v, px[i]);
                 };
                 using std::integral_constant;
                 if constexpr (a == 2) term(sxx, integral_constant<int, 0>{}, B, Cc);
@@ -290,9 +352,9 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
               // + rho u^k, the last velocity in the multiply-add
               const R e = a > 0 ? h.jx * px[a > 0 ? a - 1 : 0] : h.jy;
               constexpr int eb = a > 0 ? b : b - 1;
-              if constexpr (c > 0) s = fused(e * py[eb], pz[c], s);
-              else if constexpr (eb > 0) s = fused(e, py[eb], s);
-              else s = fused(h.jx, px[a - 1], s);
+              if constexpr (c > 0) s = mul_add<L>(e * py[eb], pz[c], s);
+              else if constexpr (eb > 0) s = mul_add<L>(e, py[eb], s);
+              else s = mul_add<L>(h.jx, px[a - 1], s);
               C[a][b][c] = s;
             }
           }
@@ -318,11 +380,11 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
 // rounded constants give 2 fl(1/6) + fl(2/3) = 1 + 2^-25 in FP32, so that every
 // weighted transform would scale the zeroth moment of its input by that
 // factor: a systematic growth of the momentum of 2^-24 per step in 3D.
-template <bool Weighted, bool Has1, bool Has2, class R>
+template <class L, bool Has1, bool Has2, class R>
 __device__ __forceinline__ void axis3(R c0, R c1, R c2, R& gm, R& g0, R& gp) {
-  if constexpr (Weighted) {
+  if constexpr (L::kProduct) {  // weighted
     g0 = Has2 ? fused(R(2.0 / 3.0), c0, -c2) : R(2.0 / 3.0) * c0;
-    const R t = R(0.5) * (Has2 ? c0 - g0 : fused(R(-2.0 / 3.0), c0, c0));
+    const R t = R(0.5) * (Has2 ? c0 - g0 : sub_mul<L>(c0, R(2.0 / 3.0), c0));
     if constexpr (Has1) {
       gm = fused(R(-0.5), c1, t);
       gp = fused(R(0.5), c1, t);
@@ -565,7 +627,7 @@ __device__ __forceinline__ void reconstruct(R (&C)[3][3][3], R* out) {
             if constexpr (g != 0.0) s = fused(R(g), C[a2][b2][c2], s);
           }
         });
-        asm("" : "+v"(s));  // a sum of one term is a product: rounded before the transforms add it
+        if constexpr (!kPlainSums<L>) asm("" : "+v"(s));  // a sum of one term is a product: rounded before the transforms add it
         B[a][b][c] = s;
       }
     });
@@ -593,7 +655,7 @@ __device__ __forceinline__ void reconstruct(R (&C)[3][3][3], R* out) {
       if constexpr (kept<L, N>(a, b, 0)) {
         if constexpr (L::D == 3) {
           constexpr bool h1 = kept<L, N>(a, b, 1), h2 = kept<L, N>(a, b, 2);
-          axis3<W, h1, h2>(B[a][b][0], h1 ? B[a][b][1] : R(0), h2 ? B[a][b][2] : R(0),
+          axis3<L, h1, h2>(B[a][b][0], h1 ? B[a][b][1] : R(0), h2 ? B[a][b][2] : R(0),
                            G1[a][b][0], G1[a][b][1], G1[a][b][2]);
         } else {
           G1[a][b][0] = B[a][b][0];
@@ -609,7 +671,7 @@ __device__ __forceinline__ void reconstruct(R (&C)[3][3][3], R* out) {
       constexpr int a = A;
       if constexpr (kept<L, N>(a, 0, 0) && layer_needed<kConserve, ZSel>(int(Z))) {
         constexpr bool h1 = kept<L, N>(a, 1, 0), h2 = kept<L, N>(a, 2, 0);
-        axis3<W, h1, h2>(G1[a][0][Z], h1 ? G1[a][1][Z] : R(0), h2 ? G1[a][2][Z] : R(0),
+        axis3<L, h1, h2>(G1[a][0][Z], h1 ? G1[a][1][Z] : R(0), h2 ? G1[a][2][Z] : R(0),
                          G2[a][0][Z], G2[a][1][Z], G2[a][2][Z]);
       }
     });
@@ -618,7 +680,7 @@ __device__ __forceinline__ void reconstruct(R (&C)[3][3][3], R* out) {
   sfor<0, NZ>([&](auto Z) {
     if constexpr (layer_needed<kConserve, ZSel>(int(Z))) sfor<0, 3>([&](auto Y) {
       R gm, g0, gp;
-      axis3<W, true, true>(G2[0][Y][Z], G2[1][Y][Z], G2[2][Y][Z], gm, g0, gp);
+      axis3<L, true, true>(G2[0][Y][Z], G2[1][Y][Z], G2[2][Y][Z], gm, g0, gp);
       sfor<0, L::Q>([&](auto I) {
         if constexpr (L::cy(I) + 1 == Y && L::cz(I) + 1 == (L::D == 3 ? int(Z) : 1)) {
           const R v = (L::cx(I) == -1) ? gm : ((L::cx(I) == 0) ? g0 : gp);

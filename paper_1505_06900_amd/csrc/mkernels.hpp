@@ -63,7 +63,7 @@ __device__ __forceinline__ Hydro<R> state_hydro(const R (&m)[kNM<L>], R rho0) {
   Hydro<R> h;
   h.drho = m[0];
   h.rho = rho0 + m[0];
-  const R inv = inv_density(rho0, m[0], h.rho);
+  const R inv = inv_density<L>(rho0, m[0], h.rho);
   h.jx = m[1];
   h.jy = m[2];
   h.ux = m[1] * inv;
