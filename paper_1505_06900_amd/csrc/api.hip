@@ -128,10 +128,11 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
 // / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
 // LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
-TilePlan pair_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls) {
+TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, bool walls) {
   TilePlan p;
+  const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int forced_lz = env_int("LBRR_PAIR_LZ", -1);
-  if (forced_lz == 0) return p;
+  if (forced_lz == 0 || !lbrr::pair_offsets_fit(ops.d, a, int(elem_size(storage)))) return p;
   if (ops.d == 2) {
     p.rows = ops.tile_rows(storage, 0, walls);
     if (p.rows == 0) return p;
@@ -636,7 +637,7 @@ int lb_step(lb_handle h, long long n) {
   StepArgs ap = a;
   ap.lz = 0;
   if (n >= 4 && !h->moment() && !h->closure_on) {
-    const TilePlan p = pair_plan(*h->ops, h->storage, h->nx, h->ny, h->nz, h->walls != 0);
+    const TilePlan p = pair_plan(*h->ops, h->storage, a, h->walls != 0);
     ap.rows = p.rows;
     ap.lz = p.lz;
     ap.walls = h->walls;

@@ -24,6 +24,15 @@ struct StepArgs {
   int walls;           // moment-state step and step pair: resting walls on the axes of this mask (bit 0 x, 1 y, 2 z)
 };
 
+// A step pair's lanes address a plane of one population (2D: a row) by 32-bit byte
+// offsets.  With the rows of all populations together (layout 1) a D3Q27 FP32 plane
+// passes that at 39.8 million nodes; larger boxes keep single steps, whose addresses are
+// 64-bit in 3D.
+inline bool pair_offsets_fit(int d, const StepArgs& a, int elem_bytes) {
+  const int64_t span = (d == 2 ? int64_t(a.nx) : int64_t(a.ny - 1) * a.sy + a.nx) * elem_bytes;
+  return span < (int64_t(1) << 32);
+}
+
 struct LatticeOps {
   int q, d, nmax;
   hipError_t (*step)(int order, int storage, const void* src, void* dst, const StepArgs& a, hipStream_t s);

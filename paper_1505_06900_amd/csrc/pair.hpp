@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_step_pair(const S* __re
   const Tile<TY> t(a);
   if (t.empty) return;
   // Byte offsets of the nodes populations come from, within a plane of one
-  // population (the host checks that it fits 32 bits); plane and population
+  // population (pair_offsets_fit); plane and population
   // bases are block-uniform.
   const int px = t.px, py = t.py, r = t.r, lane = t.lane;
   const int xs[3] = {px == a.nx - 1 ? 0 : px + 1, px, px == 0 ? a.nx - 1 : px - 1};
@@ -316,8 +316,8 @@ constexpr int pair_rows_option(int i) {
 template <class L, int N, class S, int TY>
 hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipStream_t s) {
   if (a.lz < 1) return hipErrorInvalidValue;
+  if (!pair_offsets_fit(L::D, a, int(sizeof(S)))) return hipErrorInvalidValue;
   if constexpr (L::D == 2) {
-    if (uint64_t(a.nx) * sizeof(S) > 0xffffffffull) return hipErrorInvalidValue;  // 32-bit lane byte offsets
     const int64_t nb = int64_t((a.nx + kPairRowX - 3) / (kPairRowX - 2)) * ((a.ny + a.lz - 1) / a.lz);
     if (nb >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     if (a.walls)
@@ -328,8 +328,6 @@ hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, hipSt
                          static_cast<const S*>(src), static_cast<S*>(dst), a);
     return hipGetLastError();
   } else {
-    const int64_t plane = (int64_t(a.ny - 1) * a.sy + a.nx) * int64_t(sizeof(S));
-    if (plane >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // 32-bit lane byte offsets
     const int64_t blocks = Tile<TY>::blocks(a);
     if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     if (a.walls) {
