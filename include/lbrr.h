@@ -299,7 +299,10 @@ int lb_mlp_gradient(const float* params, const float* norm, const float* x, cons
 
 /* Column mean and standard deviation (population form, FP64 accumulation in a
  * fixed order) of x (n x dim, row-major), e.g. for the normalisation vector;
- * a zero deviation is reported as 1. */
+ * a zero deviation is reported as 1.  Large x is summed in parts kept in scratch
+ * that the call allocates and frees in stream order; on a capturing stream, or
+ * where no scratch is to be had, a slower form without it adds the rows in another
+ * (also fixed) order. */
 int lb_column_stats(const float* x, long long n, int dim, float* mean, float* std, void* hip_stream);
 
 /* One bias-corrected Adam update of params (FP32 master copy) with moments m,

@@ -882,9 +882,9 @@ int workspace(size_t bytes, void** out) {
 
 // Scratch of one call, allocated and freed in stream order from a pool of the
 // device's own, so calls on any streams and threads have their own.  The pool
-// keeps at most kScratchKeep bytes between calls.  ptr stays NULL under stream
-// capture (an allocation has no place in the graph) and where the device has no
-// memory pools.
+// keeps at most kScratchKeep bytes between calls.  ptr stays NULL where there is none to be
+// had: under stream capture (an allocation has no place in the graph), on a device
+// without memory pools, and when the allocation fails; callers then take a form without it.
 constexpr uint64_t kScratchKeep = uint64_t(8) << 20;
 std::mutex g_pool_mu;
 hipMemPool_t g_pool[kMaxDevices] = {};
@@ -898,40 +898,43 @@ struct Scratch {
   ~Scratch() {
     if (ptr) (void)hipFreeAsync(ptr, stream);
   }
-  int allocate(size_t bytes, hipStream_t s) {
+  void allocate(size_t bytes, hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-      (void)hipGetLastError();
-      return LB_OK;
-    }
-    if (cap != hipStreamCaptureStatusNone) return LB_OK;
-    int dev = 0, has = 0;
-    HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
-    if (dev < 0 || dev >= kMaxDevices) return LB_OK;
+    hipError_t e = hipStreamIsCapturing(s, &cap);
+    if (e == hipSuccess && cap != hipStreamCaptureStatusNone) return;
     hipMemPool_t pool = nullptr;
-    {
-      std::lock_guard<std::mutex> lock(g_pool_mu);
-      if (!g_pool[dev]) {
-        HIP_TRY(hipDeviceGetAttribute(&has, hipDeviceAttributeMemoryPoolsSupported, dev), "hipDeviceGetAttribute");
-        if (!has) return LB_OK;
-        hipMemPoolProps props{};
-        props.allocType = hipMemAllocationTypePinned;
-        props.location.type = hipMemLocationTypeDevice;
-        props.location.id = dev;
-        HIP_TRY(hipMemPoolCreate(&g_pool[dev], &props), "hipMemPoolCreate");
-        uint64_t keep = kScratchKeep;
-        HIP_TRY(hipMemPoolSetAttribute(g_pool[dev], hipMemPoolAttrReleaseThreshold, &keep), "hipMemPoolSetAttribute");
-      }
-      pool = g_pool[dev];
-    }
-    const hipError_t e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
+    if (e == hipSuccess) e = device_pool(&pool);
+    if (e == hipSuccess) e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
     if (e != hipSuccess) {
       ptr = nullptr;
       (void)hipGetLastError();
-      return fail(LB_ERR_OOM, "scratch of %zu bytes: %s", bytes, hipGetErrorString(e));
     }
     stream = s;
-    return LB_OK;
+  }
+
+ private:
+  static hipError_t device_pool(hipMemPool_t* pool) {
+    int dev = 0, has = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorNotSupported;
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    if (!g_pool[dev]) {
+      e = hipDeviceGetAttribute(&has, hipDeviceAttributeMemoryPoolsSupported, dev);
+      if (e != hipSuccess || !has) return hipErrorNotSupported;
+      hipMemPoolProps props{};
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      e = hipMemPoolCreate(pool, &props);
+      if (e != hipSuccess) return e;
+      uint64_t keep = kScratchKeep;
+      if (hipMemPoolSetAttribute(*pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess)
+        (void)hipGetLastError();  // it then keeps nothing between calls
+      g_pool[dev] = *pool;
+    }
+    *pool = g_pool[dev];
+    return hipSuccess;
   }
 };
 
@@ -1025,7 +1028,7 @@ int lb_column_stats(const float* x, long long n, int dim, float* mean, float* st
   Scratch part;
   if (!lbrr::column_stats_direct(n, dim)) {
     const size_t bytes = sizeof(double) * 2 * size_t(dim) * size_t(lbrr::column_stats_runs(n, dim));
-    if (int r = part.allocate(bytes, s)) return r;
+    part.allocate(bytes, s);
   }
   const hipError_t e = lbrr::column_stats(x, n, dim, static_cast<double*>(part.ptr), mean, std, s);
   if (e != hipSuccess) return hip_fail(e, "column stats kernel");

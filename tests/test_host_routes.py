@@ -71,3 +71,14 @@ def test_boxes_past_the_pairs_addressing_take_single_steps(child, lattice, nx, n
     steps = [n for n in names if "k_step" in n]
     assert len(steps) == (2 if pairs else 4), steps
     assert all(("k_step_pair" in n) == pairs for n in steps), steps
+
+
+@pytest.mark.parametrize("fail", ["fake_fail_pool_create", "fake_fail_pool_malloc", "fake_capturing", None])
+def test_column_stats_without_scratch(child, fail):
+    """Where the device gives no scratch the statistics take the form that needs none."""
+    code, names = child(f"""
+if {fail!r}: ctypes.c_int.in_dll(fake, {fail!r}).value = 1
+report(launches(lambda: P.lb_column_stats(4096, 1000000, 36, 8192, 12288, None)))
+""")
+    assert code == 0
+    assert len(names) == (1 if fail else 2) and ("k_column_stats" in names[0]) == bool(fail), names
