@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 PRELUDE = """
-import ctypes, json, sys, time, types
+import ctypes, json, re, sys, time, types
 sys.modules["torch"] = types.ModuleType("torch")  # the binding imports it first, for its HIP runtime
 sys.path.insert(0, {root!r})
 fake = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
@@ -82,3 +82,59 @@ report(launches(lambda: P.lb_column_stats(4096, 1000000, 36, 8192, 12288, None))
 """)
     assert code == 0
     assert len(names) == (1 if fail else 2) and ("k_column_stats" in names[0]) == bool(fail), names
+
+
+# Tile heights the 3D moment step is built for, with their columns (mom_rows_option, tile.hpp)
+HEIGHTS = {"mom_fp32": ((13, 64), (11, 64), (8, 64)), "mom_fp64": ((5, 64), (4, 64), (12, 32))}
+
+
+def planned(storage, nx, ny, nz):
+    """(rows, blocks) of the cheapest plan, every chunk count of every height tried."""
+    up = lambda a, b: -(-a // b)
+    best = None
+    for rows, width in HEIGHTS[storage]:
+        if width == 32 and nx > 32:
+            continue
+        gx, gy, weight = up(nx, 64), up(ny, rows), rows // 2 + 2 if width == 32 else rows + 3
+        for chunks in range(1, nz + 1):
+            lz = up(nz, chunks)
+            groups = up(gy * up(nz, lz), 8)
+            cost = up(gx * groups, 32) * (lz + 2) * weight
+            if best is None or cost < best[0]:
+                best = cost, rows, up(nx, width) * 8 * groups
+    return list(best[1:])
+
+
+MOMENT_BOXES = [(1, 1, 1), (24, 24, 330), (330, 24, 24), (64, 64, 64), (75, 131, 150), (301, 130, 65), (31, 3, 997),
+                (200, 200, 200), (256, 256, 256), (130, 60, 40), (1000, 7, 91)]
+
+
+@pytest.mark.parametrize("storage", sorted(HEIGHTS))
+def test_moment_plans_are_the_cheapest(child, storage):
+    """The plan of a moment step, searched in jumps, is the one that trying every chunk count finds."""
+    got = child(f"""
+out = []
+for nx, ny, nz in {MOMENT_BOXES!r}:
+    code, names = launches(lambda: P.lb_step(handle("D3Q27", nx, ny, nz, {storage!r}), 1))
+    assert code == 0 and "k_mstep_t" in names[-1]
+    fake.fake_grid.restype = ctypes.POINTER(ctypes.c_uint32)
+    out.append([int(re.search("Li4E[fd]Li([0-9]+)E", names[-1])[1]), fake.fake_grid(len(names) - 1)[0]])
+report(out)
+""")
+    assert got == [planned(storage, *box) for box in MOMENT_BOXES]
+
+
+def test_planning_a_long_box_takes_no_time(child):
+    """A plan is made by every lb_step call: far below a launch's own time, however many planes there are."""
+    us = child("""
+h = handle("D3Q27", 24, 24, 65535, "mom_fp32")
+best = 1e9
+for _ in range(20):
+    t = time.perf_counter()
+    P.check(P.lb_step(h, 1))
+    best = min(best, time.perf_counter() - t)
+    fake.fake_reset()
+report(best * 1e6)
+""")
+    print(f"{us:.1f} us a call")
+    assert us < 200
