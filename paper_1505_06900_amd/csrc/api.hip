@@ -72,10 +72,14 @@ struct TilePlan {
 };
 
 // 3D (tile.hpp): a compute unit holds one block, a block's time grows with the
-// planes it rebuilds (lz + 2) and with its waves (rows + 3; narrow tiles, taken for at
-// most their 32 columns, rows / 2 + 2), and the tile rows are
+// planes it rebuilds (lz + 2) and with its waves (rows + 3), and the tile rows are
 // dealt to the eight XCDs in turn, so the plan taken is the one with the smallest
 //   rounds * (lz + 2) * (rows + 3),  rounds = blocks per XCD / compute units per XCD, rounded up.
+// A narrow tile (32 columns by 12 rows in eight waves) costs 9.5 rows' waves, 8.5 with
+// walls: so it comes out of the best times of both widths (D3Q27 and D3Q19, 150 planes of 131
+// rows by 65, 100, 130 and 200 columns: 9.5 to 10.5, walled 8.0 to 9.1).  It is the better one
+// where 64-column tiles would stay half empty (us a step, 5 rows x 64 -> 12 x 32: D3Q27
+// 65 x 131 x 150 99.8 -> 73.7, 130 x 131 x 150 135 -> 120, 100 x 131 x 150 101 -> 97).
 // Chunk counts that give the same lz are tried once, and none past the one where even
 // full rounds, columns * (planes + 2 chunks) of work for the whole chip, cost more than the
 // best so far: every lb_step call makes its plan, on the host (24 x 24 x 65535, trying
@@ -84,14 +88,15 @@ struct TilePlan {
 TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, bool walls, int forced_lz,
                    int forced_rows) {
   TilePlan p;
-  const int64_t gx = (nx + 63) / 64, slots = compute_units() / 8 > 0 ? compute_units() / 8 : 1;
+  const int64_t slots = compute_units() / 8 > 0 ? compute_units() / 8 : 1;
   int64_t cost = 0;
   bool built = false;
   for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) built = built || rows == forced_rows;
   for (int i = 0; const int rows = ops.tile_rows(storage, i, walls); ++i) {
-    if (built ? rows != forced_rows : rows == lbrr::kNarrowRows && nx > 32) continue;
-    const int64_t gy = (ny + rows - 1) / rows;
-    const int64_t weight = rows == lbrr::kNarrowRows ? rows / 2 + 2 : rows + 3;
+    if (built && rows != forced_rows) continue;
+    const bool narrow = rows == lbrr::kNarrowRows;
+    const int64_t gx = narrow ? (nx + 31) / 32 : (nx + 63) / 64, gy = (ny + rows - 1) / rows;
+    const int64_t weight = narrow ? (walls ? 17 : 19) : 2 * (rows + 3);
     for (int chunks = 1;;) {
       const int lz = forced_lz > 0 ? forced_lz : (nz + chunks - 1) / chunks;
       const int64_t g = gy * ((nz + lz - 1) / lz);

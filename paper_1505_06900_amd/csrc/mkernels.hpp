@@ -587,9 +587,9 @@ __global__ void __launch_bounds__(256) k_mpopulations(const S* __restrict__ src,
 // 58.8, D3Q19 FP32 51.9 / 58.8 / 56.1 / 61.6 / 59.7, D3Q27 FP64 3 / 4 / 5 rows 23.5 / 27.0 /
 // 27.5 (6 rows spill: 12.7), D3Q19 FP64 26.0 / 30.0 / 30.1.  The lower tiles serve boxes whose rows
 // the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).  FP64 boxes
-// of at most 32 columns leave half of a 64-column tile idle: 32 columns by 12 rows in
+// whose last 64-column tile would stay half idle take 32 columns by 12 rows in
 // the same eight waves (us a step, D3Q19 273 x 67 x 25 41.8 -> 30.9, 200 x 200 x 32 79.8 -> 52.9;
-// at 40 columns 64-column tiles 83.1, 32-column ones 88.1).
+// tile_plan weighs the two).
 template <class S>
 constexpr int mom_rows_option(int i) {
   constexpr int f32[] = {13, 11, 8}, f64[] = {5, 4, kNarrowRows};

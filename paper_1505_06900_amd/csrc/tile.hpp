@@ -3,7 +3,7 @@
 // and brings the populations of the tile and of its one-node rim into LDS plane by
 // plane.  TY + 2 waves hold the tile's columns of rows y0 - 1 .. y0 + TY (a wave per
 // row) and one more wave the two columns beside the tile.  TY = kNarrowRows is the
-// tile of narrow boxes: 32 columns, two rows a wave.
+// narrow tile: 32 columns, two rows a wave.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -93,20 +93,19 @@ def planned(storage, nx, ny, nz):
     up = lambda a, b: -(-a // b)
     best = None
     for rows, width in HEIGHTS[storage]:
-        if width == 32 and nx > 32:
-            continue
-        gx, gy, weight = up(nx, 64), up(ny, rows), rows // 2 + 2 if width == 32 else rows + 3
+        gx, gy, weight = up(nx, width), up(ny, rows), 9.5 if width == 32 else rows + 3
         for chunks in range(1, nz + 1):
             lz = up(nz, chunks)
             groups = up(gy * up(nz, lz), 8)
             cost = up(gx * groups, 32) * (lz + 2) * weight
             if best is None or cost < best[0]:
-                best = cost, rows, up(nx, width) * 8 * groups
+                best = cost, rows, gx * 8 * groups
     return list(best[1:])
 
 
 MOMENT_BOXES = [(1, 1, 1), (24, 24, 330), (330, 24, 24), (64, 64, 64), (75, 131, 150), (301, 130, 65), (31, 3, 997),
-                (200, 200, 200), (256, 256, 256), (130, 60, 40), (1000, 7, 91)]
+                (200, 200, 200), (256, 256, 256), (130, 60, 40), (1000, 7, 91),
+                (65, 131, 150), (36, 60, 40), (25, 67, 273), (200, 131, 150)]
 
 
 @pytest.mark.parametrize("storage", sorted(HEIGHTS))
@@ -122,6 +121,16 @@ for nx, ny, nz in {MOMENT_BOXES!r}:
 report(out)
 """)
     assert got == [planned(storage, *box) for box in MOMENT_BOXES]
+
+
+def test_narrow_tiles_where_wide_ones_stay_half_empty(child):
+    """FP64 moment boxes a little over a multiple of 64 columns take the tiles of 32 columns."""
+    boxes = [(65, 131, 150), (65, 130, 301), (75, 131, 150), (130, 131, 150), (200, 131, 150)]
+    names = child(f"""
+report([launches(lambda: P.lb_step(handle("D3Q27", nx, ny, nz, "mom_fp64", walls), 1))[1][-1]
+        for walls in (0, 7) for nx, ny, nz in {boxes!r}])
+""")
+    assert all("Li4EdLi12E" in n for n in names), names
 
 
 def test_planning_a_long_box_takes_no_time(child):
