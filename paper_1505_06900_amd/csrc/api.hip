@@ -139,14 +139,19 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // columns, has at least 6.5 MB, 20 MB with walls (single -> pairs, walls along z / on
 // all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
 // / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
+// With walls along x every tile row has wall nodes in its first and its last tile, so where
+// the last of a few tiles stays half empty, boxes that the last-level cache mostly
+// holds are better in single steps (us for four, single -> pairs, walls along x: D3Q27 FP32
+// 75 x 131 x 150 270 -> 293, D3Q19 FP32 183 -> 208, FP64 342 -> 395, 65 x 130 x 301 675 -> 721; against
+// D3Q27 FP32 65 x 130 x 301 627 -> 563, D3Q19 FP64 75 x 300 x 300 1738 -> 1513).
 // LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
-TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, bool walls) {
+TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, int walls) {
   TilePlan p;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int forced_lz = env_int("LBRR_PAIR_LZ", -1);
   if (forced_lz == 0 || !lbrr::pair_offsets_fit(ops.d, a, int(elem_size(storage)))) return p;
   if (ops.d == 2) {
-    p.rows = ops.tile_rows(storage, 0, walls);
+    p.rows = ops.tile_rows(storage, 0, walls != 0);
     if (p.rows == 0) return p;
     const int64_t gx = (nx + 253) / 254, cus = compute_units();  // k_step_pair2: 254 columns a block
     p.lz = forced_lz > 0 ? forced_lz : 0;
@@ -156,9 +161,12 @@ TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, bool w
     return p;
   }
   const int64_t gx = (nx + 63) / 64;
-  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)) * nx / (64.0 * double(gx));
-  if (forced_lz < 0 && state < (walls ? 2e7 : 6.5e6)) return p;
-  return tile_plan(ops, storage, nx, ny, nz, walls, forced_lz, env_int("LBRR_PAIR_ROWS", 0));
+  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)), used = nx / (64.0 * double(gx));
+  if (forced_lz < 0) {
+    if (state * used < (walls ? 2e7 : 6.5e6)) return p;
+    if ((walls & 1) && used < 0.62 && state < (storage == LB_STORE_FP64 ? 7e8 : 1.8e8)) return p;
+  }
+  return tile_plan(ops, storage, nx, ny, nz, walls != 0, forced_lz, env_int("LBRR_PAIR_ROWS", 0));
 }
 
 // The moment-state step: four rows per block in 2D (see kRowX in mkernels.hpp), the
@@ -649,7 +657,7 @@ int lb_step(lb_handle h, long long n) {
   StepArgs ap = a;
   ap.lz = 0;
   if (n >= 4 && !h->moment() && !h->closure_on) {
-    const TilePlan p = pair_plan(*h->ops, h->storage, a, h->walls != 0);
+    const TilePlan p = pair_plan(*h->ops, h->storage, a, h->walls);
     ap.rows = p.rows;
     ap.lz = p.lz;
     ap.walls = h->walls;

@@ -147,3 +147,16 @@ report(best * 1e6)
 """)
     print(f"{us:.1f} us a call")
     assert us < 200
+
+
+@pytest.mark.parametrize("lattice,storage,shape,walls,pairs", [
+    ("D3Q27", "fp32", (75, 131, 150), 1, False), ("D3Q19", "fp32", (75, 131, 150), 7, False),
+    ("D3Q19", "fp64", (75, 131, 150), 1, False), ("D3Q19", "fp64", (65, 130, 301), 7, False),
+    ("D3Q27", "fp32", (65, 130, 301), 7, True), ("D3Q19", "fp64", (75, 300, 300), 1, True),
+    ("D3Q27", "fp32", (75, 131, 150), 6, True), ("D3Q19", "fp64", (75, 131, 150), 0, True),
+    ("D3Q19", "fp32", (100, 131, 150), 1, True), ("D3Q19", "fp64", (128, 128, 128), 7, True),
+])
+def test_pairs_with_walls_along_x(child, lattice, storage, shape, walls, pairs):
+    """Half-empty tiles whose first and last columns are walls: single steps up to the size the pair's saving shows."""
+    code, names = child(f"report(launches(lambda: P.lb_step(handle({lattice!r}, *{shape!r}, {storage!r}, {walls}), 4)))")
+    assert code == 0 and len(names) == (3 if pairs else 5), names
