@@ -125,6 +125,13 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 //   FP64  256^2  4.49 / 3.75 / 3.76 / 4.46 / 5.69 / 9.22    501^2  8.30 / 6.89 / 5.06 / 6.07 / 6.52 / 9.32
 //        1024^2 27.0 / 26.3 / 21.6 / 18.3 / 19.9 / 18.9    2048^2 101 / 85.0 / 69.4 / 62.1 / 61.0 / 61.3
 // (walled boxes within a few per cent of these: 501^2 FP64 8.51 / 7.16 / 5.22 / 5.86).
+// lz = 1 only while two blocks a compute unit do: four steps of 288^2 FP64 in single
+// steps 15.8 us, pairs at lz = 1 18.3 (576 blocks), at 2 16.2; 384^2 20.9 / 20.0 / 17.6.
+// Narrow rows leave most of a block's 254 columns idle where k_step's blocks are 64 wide:
+// below 0.3 of them used, pairs are for as many rows as the chip takes at once (four
+// steps, single -> pairs: 20 columns FP32 1000 rows 13.8 -> 11.3, 3000 13.8 -> 17.4, 20000
+// 39.7 -> 66.7; FP64 1000 13.9 -> 13.8, 64 columns 13.0 -> 15.4), and for rows used to 0.15 of a
+// state that caches no longer hold (64 columns, 20000 rows FP32 67.5 -> 60.8).
 //
 // 3D (GLUPS, order 4, single steps -> pairs), cubes of side n:
 //            n = 256         320         200         128          64
@@ -155,8 +162,11 @@ TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, int wa
     if (p.rows == 0) return p;
     const int64_t gx = (nx + 253) / 254, cus = compute_units();  // k_step_pair2: 254 columns a block
     p.lz = forced_lz > 0 ? forced_lz : 0;
-    for (int lz : {1, 2})
-      if (p.lz == 0 && gx * ((ny + lz - 1) / lz) <= 3 * cus) p.lz = lz;
+    const double used = nx / (254.0 * double(gx)), state = double(nx) * ny * ops.q * double(elem_size(storage));
+    const bool narrow = used < 0.3 && gx * ny > (storage == LB_STORE_FP64 ? 2 : 4) * cus;
+    if (forced_lz < 0 && narrow && (used < 0.15 || state < 32e6)) return TilePlan();
+    if (p.lz == 0 && gx * ny <= 2 * cus) p.lz = 1;
+    if (p.lz == 0 && gx * ((ny + 1) / 2) <= 3 * cus) p.lz = 2;
     if (p.lz == 0) p.lz = gx * ((ny + 3) / 4) <= 12 * cus ? 4 : 6;
     return p;
   }

@@ -160,3 +160,21 @@ def test_pairs_with_walls_along_x(child, lattice, storage, shape, walls, pairs):
     """Half-empty tiles whose first and last columns are walls: single steps up to the size the pair's saving shows."""
     code, names = child(f"report(launches(lambda: P.lb_step(handle({lattice!r}, *{shape!r}, {storage!r}, {walls}), 4)))")
     assert code == 0 and len(names) == (3 if pairs else 5), names
+
+
+@pytest.mark.parametrize("storage,nx,ny,rows", [
+    # rows a block takes; 0: single steps
+    ("fp32", 64, 64, 1), ("fp32", 256, 256, 1), ("fp64", 256, 256, 1), ("fp64", 288, 288, 2), ("fp32", 384, 384, 2),
+    ("fp32", 2048, 2048, 6), ("fp32", 20, 256, 1), ("fp32", 20, 1000, 2), ("fp32", 20, 3000, 0), ("fp32", 64, 3000, 0),
+    ("fp32", 64, 20000, 6), ("fp64", 64, 1000, 0), ("fp64", 20, 20000, 0), ("fp64", 130, 3000, 4), ("fp32", 100000, 1, 1),
+])
+def test_pairs_in_2d(child, storage, nx, ny, rows):
+    """Rows a block of a 2D pair takes: few while there are few blocks; narrow boxes with many rows keep single steps."""
+    code, names = child(f"""
+code, names = launches(lambda: P.lb_step(handle("D2Q9", {nx}, {ny}, 1, {storage!r}), 4))
+fake.fake_grid.restype = ctypes.POINTER(ctypes.c_uint32)
+report([code, [[n, fake.fake_grid(i)[0]] for i, n in enumerate(names) if "k_step" in n]])
+""")
+    assert code == 0 and len(names) == (2 if rows else 4), names
+    if rows:
+        assert all("k_step_pair2" in n and g == -(-nx // 254) * -(-ny // rows) for n, g in names), names
