@@ -1,6 +1,7 @@
 // C ABI of the library (declarations and contracts in include/lbrr.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -69,6 +70,7 @@ int env_int(const char* name, int none) {
 // lattice, tiles of planes of a 3D one).
 struct TilePlan {
   int rows = 0, lz = 0;
+  bool whole = false;  // step pairs: only for runs of a multiple of four steps
 };
 
 // 3D (tile.hpp): a compute unit holds one block, a block's time grows with the
@@ -132,6 +134,12 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // steps, single -> pairs: 20 columns FP32 1000 rows 13.8 -> 11.3, 3000 13.8 -> 17.4, 20000
 // 39.7 -> 66.7; FP64 1000 13.9 -> 13.8, 64 columns 13.0 -> 15.4), and for rows used to 0.15 of a
 // state that caches no longer hold (64 columns, 20000 rows FP32 67.5 -> 60.8).
+// A state of 2.5 to 8 MB stays in the XCDs' L2 caches, where each finds the rows it wrote.
+// Pairs and single steps share the rows out differently, so single steps for the last of
+// a run cost more there than pairs gain (us, four and six steps: 320^2 FP32 single 13.3
+// and 20.3, pairs 12.9 and 22.7; 256^2 FP64 15.2 and 22.7, 14.7 and 25.3; but 192^2 FP32 14.0 and
+// 20.6, 8.9 and 15.7, 512^2 22.2 and 33.3, 16.1 and 31.0): runs that are no multiple of four
+// steps stay single.
 //
 // 3D (GLUPS, order 4, single steps -> pairs), cubes of side n:
 //            n = 256         320         200         128          64
@@ -168,6 +176,7 @@ TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, int wa
     if (p.lz == 0 && gx * ny <= 2 * cus) p.lz = 1;
     if (p.lz == 0 && gx * ((ny + 1) / 2) <= 3 * cus) p.lz = 2;
     if (p.lz == 0) p.lz = gx * ((ny + 3) / 4) <= 12 * cus ? 4 : 6;
+    p.whole = forced_lz < 0 && state >= 2.5e6 && state <= 8e6;
     return p;
   }
   const int64_t gx = (nx + 63) / 64;
@@ -665,46 +674,34 @@ int lb_step(lb_handle h, long long n) {
   // modulo 2, as single steps would (an even number of steps ends in the buffer
   // it started from, which replays of a captured run rely on).
   StepArgs ap = a;
-  ap.lz = 0;
-  if (n >= 4 && !h->moment() && !h->closure_on) {
-    const TilePlan p = pair_plan(*h->ops, h->storage, a, h->walls);
-    ap.rows = p.rows;
-    ap.lz = p.lz;
-    ap.walls = h->walls;
-  }
-  for (long long k = 0; k < n; ++k) {
-    long long left = n - k;  // steps up to the end of the call or the next check
-    if (h->check_every > 0) {
-      const long long to_check = h->check_every - h->steps % h->check_every;
-      if (to_check < left) left = to_check;
-    }
-    hipError_t e = hipSuccess;
-    if (ap.lz > 0 && left >= 4) {
-      for (int j = 0; j < 2 && e == hipSuccess; ++j) {
-        e = h->ops->step_pair(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], ap, h->stream);
-        if (e == hipSuccess) {
-          h->cur ^= 1;
-          h->steps += 2;
-        }
-      }
+  TilePlan pairs;
+  if (n >= 4 && !h->moment() && !h->closure_on) pairs = pair_plan(*h->ops, h->storage, a, h->walls);
+  ap.rows = pairs.rows;
+  ap.lz = pairs.lz;
+  ap.walls = h->walls;
+  while (n > 0) {
+    long long run = n;  // steps up to the end of the call or the next check
+    if (h->check_every > 0) run = std::min(run, h->check_every - h->steps % h->check_every);
+    n -= run;
+    long long paired = pairs.lz > 0 && !(pairs.whole && run % 4) ? run / 4 * 2 : 0;  // launches of two steps
+    for (run -= 2 * paired; paired > 0 || run > 0;) {
+      const int steps = paired > 0 ? 2 : 1;
+      const void* src = h->buf[h->cur];
+      void* dst = h->buf[1 - h->cur];
+      hipError_t e;
+      if (paired > 0)
+        e = h->ops->step_pair(h->order, h->storage, src, dst, ap, h->stream);
+      else if (h->closure_on)
+        e = lbrr::closure_step(h->order, h->storage, src, dst, a, h->cl_packed, h->cl_params, h->cl_norm, h->stream);
+      else if (h->walls && !h->moment())
+        e = h->ops->step_walls(h->order, h->storage, src, dst, a, h->walls, h->stream);
+      else
+        e = h->ops->step(h->order, h->storage, src, dst, a, h->stream);
       if (e != hipSuccess) return hip_fail(e, "step kernel launch");
-      k += 3;
-      if (h->check_every > 0 && h->steps % h->check_every == 0) {
-        double t[5];
-        if (int r = totals(h, t)) return r;
-      }
-      continue;
+      h->cur ^= 1;
+      h->steps += steps;
+      --(steps == 2 ? paired : run);
     }
-    if (h->closure_on)
-      e = lbrr::closure_step(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], a, h->cl_packed, h->cl_params,
-                             h->cl_norm, h->stream);
-    else if (h->walls && !h->moment())
-      e = h->ops->step_walls(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], a, h->walls, h->stream);
-    else
-      e = h->ops->step(h->order, h->storage, h->buf[h->cur], h->buf[1 - h->cur], a, h->stream);
-    if (e != hipSuccess) return hip_fail(e, "step kernel launch");
-    h->cur ^= 1;
-    ++h->steps;
     if (h->check_every > 0 && h->steps % h->check_every == 0) {
       double t[5];
       if (int r = totals(h, t)) return r;
