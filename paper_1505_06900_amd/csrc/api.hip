@@ -54,6 +54,11 @@ size_t elem_size(int storage) {
   return 2;
 }
 
+// Row pitch in bytes: whole 128-byte lines, so that every row starts on a line and a
+// wave's 64 consecutive x stay within the fewest lines (with nx = 300 unpadded, D3Q27
+// FP32 ran at 13.9 GLUPS against 27 for 256 or 320).
+size_t row_bytes(int64_t nx, size_t es) { return (size_t(nx) * es + 127) / 128 * 128; }
+
 int compute_units() {
   int cus = 256;
   int dev = 0;
@@ -70,6 +75,7 @@ int env_int(const char* name, int none) {
 // lattice, tiles of planes of a 3D one).
 struct TilePlan {
   int rows = 0, lz = 0;
+  double fill = 0.0;   // 3D: nodes updated, of those the chip's compute units take through the launch
   bool whole = false;  // step pairs: only for runs of a multiple of four steps
 };
 
@@ -107,6 +113,7 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
       if (p.lz == 0 || c < cost) {
         p.rows = rows;
         p.lz = lz;
+        p.fill = double(nx) * ny * nz / (double(narrow ? 32 : 64) * rows * double(rounds * (lz + 2)) * double(8 * slots));
         cost = c;
       }
       if (forced_lz > 0 || lz == 1) break;
@@ -154,11 +161,18 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // columns, has at least 6.5 MB, 20 MB with walls (single -> pairs, walls along z / on
 // all axes: D3Q19 FP32 256^3 39.3 -> 56.2 / 51.3, 128^3 37.7 -> 46.5 / 42.8, 64^3 28.7 -> 30.0
 // / 26.9; D3Q27 FP32 256^3 26.9 -> 41.1 / 37.8; D3Q19 FP64 256^3 18.1 -> 31.1 / 27.3).
-// With walls along x every tile row has wall nodes in its first and its last tile, so where
-// the last of a few tiles stays half empty, boxes that the last-level cache mostly
-// holds are better in single steps (us for four, single -> pairs, walls along x: D3Q27 FP32
-// 75 x 131 x 150 270 -> 293, D3Q19 FP32 183 -> 208, FP64 342 -> 395, 65 x 130 x 301 675 -> 721; against
-// D3Q27 FP32 65 x 130 x 301 627 -> 563, D3Q19 FP64 75 x 300 x 300 1738 -> 1513).
+// The pair pays for tiles, chunk edges and compute units left empty, single steps for
+// nothing of the kind, so pairs also need a plan whose launch is filled to 0.30 (single -> pairs, us
+// for four steps: D3Q27 FP32 500 x 2 x 1000 fill 0.22 157 -> 185, 163 x 5 x 235 0.29 51 -> 38, 500 x 3 x 1000
+// 0.34 230 -> 221; D3Q27 FP64 16 x 400 x 400 0.24 1189 -> 1232, 22 x 240 x 240 0.31 595 -> 505; one plane
+// of 500 x 1000 0.32 177 -> 196, so two at least, six between walls: D3Q19 FP32 500 x 1000 x 3 0.47
+// 169 -> 188), with walls to 0.42 (walls on y and z: D3Q27 FP32 400 x 5 x 400
+// 0.41 142 -> 159, 163 x 10 x 235 even, 500 x 6 x 1000 0.66 456 -> 375; D3Q19 FP64 28 x 240 x 240 0.40 473 -> 519), with
+// walls on x, which every tile row's first and last tile hold, to 0.50 (D3Q27 FP32 75 x 131 x 150 0.48 270 ->
+// 293, D3Q19 FP64 65 x 130 x 301 0.43 675 -> 721, 100 x 131 x 150 0.62 475 -> 417).
+// FP32 rows that end inside a 64-byte half line are written twice where the caches do not hold the state, by a
+// pair half as often: from 280 MB of padded rows 0.10, 0.15 and 0.42 suffice (D3Q27 7 x 400 x 400 fill 0.10
+// 1037 -> 586, walls on y and z 11 x 400 x 400 0.16 1030 -> 805, on x 65 x 130 x 301 0.43 627 -> 563).
 // LBRR_PAIR_LZ (0: no pairs) and LBRR_PAIR_ROWS override the choice.
 TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, int walls) {
   TilePlan p;
@@ -180,12 +194,14 @@ TilePlan pair_plan(const LatticeOps& ops, int storage, const StepArgs& a, int wa
     return p;
   }
   const int64_t gx = (nx + 63) / 64;
-  const double state = double(nx) * ny * nz * ops.q * double(elem_size(storage)), used = nx / (64.0 * double(gx));
-  if (forced_lz < 0) {
-    if (state * used < (walls ? 2e7 : 6.5e6)) return p;
-    if ((walls & 1) && used < 0.62 && state < (storage == LB_STORE_FP64 ? 7e8 : 1.8e8)) return p;
-  }
-  return tile_plan(ops, storage, nx, ny, nz, walls != 0, forced_lz, env_int("LBRR_PAIR_ROWS", 0));
+  const size_t es = elem_size(storage);
+  const double state = double(nx) * ny * nz * ops.q * double(es), used = nx / (64.0 * double(gx));
+  if (forced_lz < 0 && state * used < (walls ? 2e7 : 6.5e6)) return p;
+  p = tile_plan(ops, storage, nx, ny, nz, walls != 0, forced_lz, env_int("LBRR_PAIR_ROWS", 0));
+  if (forced_lz > 0) return p;
+  const bool torn = es == 4 && nx * es % 64 != 0 && double(row_bytes(nx, es)) * ny * nz * ops.q >= 2.8e8;
+  const double least = walls & 1 ? (torn ? 0.42 : 0.50) : (walls ? (torn ? 0.15 : 0.42) : (torn ? 0.10 : 0.30));
+  return p.fill < least || nz < (walls & 4 ? 6 : 2) ? TilePlan() : p;
 }
 
 // The moment-state step: four rows per block in 2D (see kRowX in mkernels.hpp), the
@@ -442,10 +458,7 @@ int ensure_buffers(lb_ctx* h) {
   const size_t es = elem_size(h->storage);
   const int64_t nx = h->nx, ny = h->ny, nz = h->nz, q = h->nvalues();
   h->layout = h->moment() ? moment_layout_choice() : layout_choice(h->d(), nx, ny, es);
-  // Row pitch: nx rounded up to whole 128-byte lines, so that every row starts
-  // on a line and a wave's 64 consecutive x stay within the fewest lines (with
-  // nx = 300 unpadded, D3Q27 FP32 ran at 13.9 GLUPS against 27 for 256 or 320).
-  const int64_t px = int64_t((size_t(nx) * es + 127) / 128 * 128 / es);
+  const int64_t px = int64_t(row_bytes(nx, es) / es);
   size_t elems = 0;
   if (h->layout == 1) {  // rows of all populations together
     h->si = px;
