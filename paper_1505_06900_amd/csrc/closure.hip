@@ -1046,10 +1046,13 @@ int column_stats_runs(int64_t n, int dim) {
   return int(need < most ? need : most);
 }
 
-// Below this the one-block-per-column kernel is done sooner than scratch is
-// allocated (about 23 us a call with it): 4.7 us at 3000 x 36, 33 us at 30000 x 36,
-// 15 us at 30000 x 3, 44 us at 100000 x 3.
-bool column_stats_direct(int64_t n, int dim) { return n <= (dim < 16 ? 50000 : 20000); }
+// Where the one-block-per-column kernel is done sooner than scratch is allocated (about
+// 22 us a call with it, up to 1 M x 16): while x stays in an XCD's L2 it takes time by its rows
+// alone, 12.6 us at 20001 x 16, 20.8 at 36000 x 16, 13.0 at 20001 x 36, 20.5 at 29000 x 36;
+// past 4 MB every column's block fetches every line from memory: 43.8 us at 32000 x 36.
+bool column_stats_direct(int64_t n, int dim) {
+  return n <= 20000 || (n <= (dim < 16 ? 50000 : 38000) && n * dim <= 1000000);
+}
 
 hipError_t column_stats(const float* x, int64_t n, int dim, double* part, float* mean, float* sd, hipStream_t s) {
   if (!part) {

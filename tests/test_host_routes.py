@@ -215,3 +215,13 @@ report([code, [n for n in names if "k_step" in n]])
 """)
     two = sum("k_step_pair2" in n for n in names)
     assert code == 0 and (two, len(names) - two) == launched, names
+
+
+@pytest.mark.parametrize("n,dim,direct", [(20000, 1000, True), (20001, 16, True), (36000, 16, True), (40000, 16, False),
+                                          (27000, 36, True), (28000, 36, False), (20001, 100, False), (50000, 15, True),
+                                          (50001, 1, False), (2**31, 1, False), (30000, 2**20, False)])
+def test_column_stats_form(child, n, dim, direct):
+    """One block a column while that is done before scratch would be allocated."""
+    code, names = child(f"report(launches(lambda: P.lb_column_stats(4096, {n}, {dim}, 8192, 12288, None)))")
+    assert code == 0
+    assert len(names) == (1 if direct else 2) and ("k_column_stats" in names[0]) == direct, names
