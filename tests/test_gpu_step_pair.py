@@ -92,3 +92,46 @@ def test_pairs_equal_single_steps_2d(lbrr, gpu, order, storage, walls, monkeypat
             assert steps == 9
             assert gpu.isfinite(got).all()
             assert gpu.equal(got, want), (shape, lz)
+
+
+@pytest.mark.parametrize("lattice,shape,storage,walls", [
+    ("D3Q27", (20, 26, 70), "fp32", (0, 0, 0)), ("D3Q19", (20, 26, 70), "fp64", (0, 0, 0)),
+    ("D3Q19", (20, 26, 70), "fp32", (1, 1, 1)), ("D2Q9", (1, 33, 600), "fp64", (0, 1, 0))])
+@pytest.mark.parametrize("steps", [8, 10])
+def test_pairs_in_a_graph(lbrr, gpu, lattice, shape, storage, walls, steps, monkeypatch):
+    """Captured launches of two steps, replayed between eager steps of the same handle and checked against the
+    single steps of another after every replay.  10 steps: four pairs and two single steps."""
+    torch = gpu
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    rho = 1.0 + 0.01 * torch.randn(shape, generator=g, device="cuda", dtype=torch.float64)
+    u = 0.03 * torch.randn((lbrr.DIM[lattice],) + shape, generator=g, device="cuda", dtype=torch.float64)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    sims = []
+    with torch.cuda.stream(s):
+        for _ in range(2):
+            sim = lbrr.Simulation(lattice, shape, 0.62, 4, storage=storage, stream=s)
+            sim.set_walls(*(bool(w) for w in walls))
+            sims.append(sim.init_fields(rho, u))
+    torch.cuda.synchronize()
+    single, graphed = sims
+    graph = torch.cuda.CUDAGraph()
+    monkeypatch.setenv("LBRR_PAIR_LZ", "6")
+    with torch.cuda.graph(graph, stream=s):
+        graphed.step(steps)
+    for k in range(4):
+        with torch.cuda.stream(s):
+            graph.replay()
+            monkeypatch.setenv("LBRR_PAIR_LZ", "0")
+            single.step(steps + 4)
+            monkeypatch.setenv("LBRR_PAIR_LZ", "6")
+            graphed.step(4)
+        torch.cuda.synchronize()
+        a, b = single.get_populations(), graphed.get_populations()
+        torch.cuda.synchronize()
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b), f"replay {k + 1}"
+    del graph
+    for sim in sims:
+        sim.close()

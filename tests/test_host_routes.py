@@ -168,6 +168,8 @@ report(best * 1e6)
     # torn lines out of cache
     ("D3Q27", "fp32", (7, 400, 400), 0, True), ("D3Q27", "fp32", (11, 400, 400), 6, True),
     ("D3Q27", "fp32", (16, 400, 400), 6, False), ("D3Q27", "fp32", (7, 240, 240), 0, False),
+    # no such kernel: its registers spill
+    ("D3Q27", "fp64", (256, 256, 256), 4, False), ("D3Q19", "fp64", (256, 256, 256), 4, True),
     # cubes
     ("D3Q27", "fp32", (64, 64, 64), 0, True), ("D3Q19", "fp32", (256, 256, 256), 0, True),
     ("D3Q27", "fp64", (64, 64, 64), 0, True), ("D3Q27", "fp32", (40, 40, 40), 0, False),
