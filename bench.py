@@ -373,7 +373,7 @@ def write_traffic(fetch_dir, write_dir, out_path):
     ff, fw = copy_kib / fetch[kf], copy_kib / write[kf]
     nodes = 256**3
     out = {"source_hash": kernel_source_hash(), "copy_calibration": {"fetch_factor": ff, "write_factor": fw},
-           "workload": "D3Q27 order 4, 256^3, one step launch"}
+           "workload": "D3Q27 order 4, 256^3, one launch of the step kernel (fp32, fp64: two steps)"}
     tags = {"fp32": ("k_step", "float"), "fp16": ("k_step", "DF16_"), "fp64": ("k_step", "double"),
             "mom_fp32": ("k_mstep", "float"), "mom_fp64": ("k_mstep", "double")}
     for st, (kern, tag) in tags.items():

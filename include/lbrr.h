@@ -255,9 +255,9 @@ const char* lb_last_error(void);
  * for the neighbours x + (dx, dy), dy = -1, 0, 1 (outer), dx = -1, 0, 1
  * (inner): rho - rho0, u_x, u_y of g.  Outputs: corrections of a1^(2)
  * (xx, xy, yy).
- * All pointers of these entry points are device pointers.  The MLP entry
- * points share one library-owned workspace per process: calls that overlap
- * on one device race.
+ * All pointers of these entry points are device pointers.  lb_mlp_gradient
+ * keeps its partial sums in one library-owned workspace per process: calls of
+ * it that overlap on one device race.
  */
 #define LB_MLP_NPARAM 6723
 #define LB_MLP_NNORM 78
@@ -265,8 +265,8 @@ const char* lb_last_error(void);
 
 /* Enable (enable = 1) or disable the closure for lb_step of a D2Q9 handle
  * (LB_ERR_UNSUPPORTED otherwise).  params / norm are copied (stream-ordered);
- * with the closure on, each step first writes (rho - rho0, u) of the stored
- * state to a handle-owned buffer, then runs the fused step with the MLP. */
+ * with the closure on, each step is one launch that forms the features, runs the
+ * MLP and collides. */
 int lb_set_closure(lb_handle h, const float* params, const float* norm, int enable);
 
 /* Features (nodes x 36, row-major) of the step that would follow the current

@@ -346,12 +346,13 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float* __r
 // and one partial squared-error sum per block.
 //
 // Bound: latency, a chain of eight phases with a barrier between them.  A block has
-// sixteen waves so that no phase gives a wave more than one tile (four waves: up to
-// four), the serial sums (loss, biases) fall to waves that have none, and the
-// weights are rounded to BF16 as they are loaded.  Batch of 4096 (128 blocks): 15.1
+// sixteen waves so that no phase gives a wave more than one tile, or in the phase of dW2
+// and dZ1 one of each (four waves: up to six), the serial sums (loss, biases) fall to the last
+// waves, which have the fewest, and the weights are rounded to BF16 as they are loaded.  Batch of 4096 (128 blocks): 15.1
 // us and a packing launch of 2.5 us with four waves, 9.7 us so, same bits.
 constexpr int kTS = 32;  // samples per block
 constexpr int kTrainThreads = 1024;
+static_assert(kTrainThreads / 64 >= 12, "dW3 falls to waves 8 to 11");
 
 // Batch rows outside [0, nrows) are clamped to the nearest valid row.
 __device__ __forceinline__ int64_t clamp_row(int r, int64_t nrows) {
@@ -645,8 +646,8 @@ __global__ void __launch_bounds__(256) k_column_final(const double* __restrict__
   }
 }
 
-// The same with one block per column and no partials, for calls under stream
-// capture (whose scratch could not be allocated on the stream).
+// The same with one block per column and no partials: for fewer rows than pay for scratch
+// (column_stats_direct), and where there is none (stream capture, no memory).
 __global__ void __launch_bounds__(256) k_column_stats(const float* __restrict__ x, int64_t n, int dim,
                                                       float* __restrict__ mean, float* __restrict__ sd) {
   __shared__ double red[2][256];

@@ -374,7 +374,8 @@ __device__ __forceinline__ void coefficients(const Hydro<R>& h, R omega1, R (&C)
 
 // The collision conserves mass and momentum (Sec. 2), and the weighted form
 // keeps that in any precision: g(0) is formed first and the outer values share
-// what is left of C0, g(+-1) = (C0 - g(0))/2 +- C1/2.  Then g(-1) + g(0) + g(+1)
+// what is left of C0, g(+-1) = (C0 - g(0))/2 +- C1/2 (without C2: of the product 2/3 C0
+// before it is rounded, in one multiply-add).  Then g(-1) + g(0) + g(+1)
 // returns C0 and g(+1) - g(-1) returns C1 up to the round-to-nearest errors of
 // the operations alone.  With the sum 1/6 C0 + 1/2 C2 written out instead, the
 // rounded constants give 2 fl(1/6) + fl(2/3) = 1 + 2^-25 in FP32, so that every

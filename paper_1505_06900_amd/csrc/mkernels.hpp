@@ -48,7 +48,7 @@ namespace lbrr {
 template <class L>
 constexpr int kNM = (L::D == 3) ? 10 : 6;
 
-constexpr int kPrefetch = 2;  // planes of moments in flight ahead of the rebuild
+constexpr int kPrefetch = 2;  // 2D: rows of moments in flight ahead of the rebuild
 
 // 2D: nodes per rebuilt row of a block.  Measured, D2Q9 order 4 FP32, GLUPS at
 // 2 / 4 / 8 / 16 rows per chunk: 2048^2 rows of 128: 81 / 86 / 82 / 79, of 256:
@@ -160,60 +160,55 @@ __device__ __forceinline__ void add_row(Moments<R>& s, const R (*pop)[BX], int t
 // off-equilibrium bounce-back at u = 0, where w_i = w_opp), else w_i (rho - rho0);
 // rho - rho0 follows from the zeroth moment of the completed set, the node keeps
 // j = 0, and a1^(2) is the second moment of the completed set minus
-// (rho - rho0) c_s^2 I.  Every step is linear in the arriving populations, so
-// their contributions are summed layer by layer as they arrive: a known
-// population whose opposite is unknown counts twice (at xi and at -xi: the
-// momentum cancels), and the buried ones enter when the node is finalised.
+// (rho - rho0) c_s^2 I.  The 3D step keeps the arrivals of a node and completes them as
+// the population step does (LayerValues, tile.hpp).  The 2D step keeps sums: every step
+// is linear in the arriving populations, so their contributions are added row by row as
+// they arrive, a known population whose opposite is unknown counts twice (at xi and at
+// -xi: the momentum cancels), and the buried ones enter when the node is finalised.
 
-// Does a population moving along (cx, cy, cz) arrive from outside the box?
-__device__ __forceinline__ bool from_outside(int sx, int sy, int sz, int cx, int cy, int cz) {
-  return (sx != 0 && cx == -sx) || (sy != 0 && cy == -sy) || (sz != 0 && cz == -sz);
+// Does a population moving along (cx, cy) arrive from outside the box?
+__device__ __forceinline__ bool from_outside(int sx, int sy, int cx, int cy) {
+  return (sx != 0 && cx == -sx) || (sy != 0 && cy == -sy);
 }
 
-// Contribution of the known population v moving along (cx, cy, cz) to the moment
-// sums of a wall node (sides sx, sy, sz).
+// Contribution of the known population v moving along (cx, cy) to the moment sums of a
+// wall node (sides sx, sy).
 template <class R>
-__device__ __forceinline__ void add_known(Moments<R>& s, R v, int cx, int cy, int cz, int sx, int sy, int sz) {
-  const bool twice = from_outside(sx, sy, sz, -cx, -cy, -cz);
+__device__ __forceinline__ void add_known(Moments<R>& s, R v, int cx, int cy, int sx, int sy) {
+  const bool twice = from_outside(sx, sy, -cx, -cy);
   const R k = twice ? R(2) * v : v;
   s.d0 = s.d0 + k;
   if (!twice) {
     s.jx = s.jx + R(cx) * v;
     s.jy = s.jy + R(cy) * v;
-    s.jz = s.jz + R(cz) * v;
   }
   s.pxx = s.pxx + R(cx * cx) * k;
   s.pyy = s.pyy + R(cy * cy) * k;
-  s.pzz = s.pzz + R(cz * cz) * k;
   s.pxy = s.pxy + R(cx * cy) * k;
-  s.pxz = s.pxz + R(cx * cz) * k;
-  s.pyz = s.pyz + R(cy * cz) * k;
 }
 
-// 2D wall node: the populations with c_y = CY rebuilt on one row arriving at inner node tx.
+// Wall node: the populations with c_y = CY rebuilt on one row arriving at inner node tx.
 template <class L, int CY, int BX, class R>
 __device__ __forceinline__ void add_row_walls(Moments<R>& s, const R (*pop)[BX], int tx, int sx, int sy) {
   sfor<0, 3>([&](auto X) {
     constexpr int cx = int(X) - 1;
-    if (!from_outside(sx, sy, 0, cx, CY, 0)) add_known(s, pop[velocity_index<L>(cx, CY, 0)][tx - cx], cx, CY, 0, sx, sy, 0);
+    if (!from_outside(sx, sy, cx, CY)) add_known(s, pop[velocity_index<L>(cx, CY, 0)][tx - cx], cx, CY, sx, sy);
   });
 }
 
 // Stored moments of a wall node from its sums (known and bounced populations).
 template <class L, class R>
-__device__ __forceinline__ void finalize_walls(const Moments<R>& s, int sx, int sy, int sz, R (&m)[kNM<L>]) {
-  R wb = R(0), bxx = R(0), byy = R(0), bzz = R(0), bxy = R(0), bxz = R(0), byz = R(0);  // buried: sum w, w xi xi
+__device__ __forceinline__ void finalize_walls(const Moments<R>& s, int sx, int sy, R (&m)[kNM<L>]) {
+  static_assert(L::D == 2, "2D");
+  R wb = R(0), bxx = R(0), byy = R(0), bxy = R(0);  // buried: sum w, w xi xi
   sfor<0, L::Q>([&](auto I) {
-    constexpr int cx = L::cx(I), cy = L::cy(I), cz = L::cz(I);
-    if (from_outside(sx, sy, sz, cx, cy, cz) && from_outside(sx, sy, sz, -cx, -cy, -cz)) {
+    constexpr int cx = L::cx(I), cy = L::cy(I);
+    if (from_outside(sx, sy, cx, cy) && from_outside(sx, sy, -cx, -cy)) {
       const R w = R(L::w(I));
       wb = wb + w;
       bxx = bxx + R(cx * cx) * w;
       byy = byy + R(cy * cy) * w;
-      bzz = bzz + R(cz * cz) * w;
       bxy = bxy + R(cx * cy) * w;
-      bxz = bxz + R(cx * cz) * w;
-      byz = byz + R(cy * cz) * w;
     }
   });
   const R drho = s.d0 / (R(1) - wb);
@@ -221,19 +216,9 @@ __device__ __forceinline__ void finalize_walls(const Moments<R>& s, int sx, int 
   m[0] = drho;
   m[1] = R(0);
   m[2] = R(0);
-  if constexpr (L::D == 3) {
-    m[3] = R(0);
-    m[4] = s.pxx + drho * bxx - drho * cs2;
-    m[5] = s.pyy + drho * byy - drho * cs2;
-    m[6] = s.pzz + drho * bzz - drho * cs2;
-    m[7] = s.pxy + drho * bxy;
-    m[8] = s.pxz + drho * bxz;
-    m[9] = s.pyz + drho * byz;
-  } else {
-    m[3] = s.pxx + drho * bxx - drho * cs2;
-    m[4] = s.pyy + drho * byy - drho * cs2;
-    m[5] = s.pxy + drho * bxy;
-  }
+  m[3] = s.pxx + drho * bxx - drho * cs2;
+  m[4] = s.pyy + drho * byy - drho * cs2;
+  m[5] = s.pxy + drho * bxy;
 }
 
 // v in a register of its own.
@@ -375,8 +360,8 @@ __global__ void __launch_bounds__(Tile<TY>::threads()) k_mstep_t(const S* __rest
 // 0, +1 arrive on rows p - 1, p, p + 1, so each inner thread keeps running
 // moment sums for three target rows, and row p - 1 is complete once row p has
 // been rebuilt.  Rows of BX nodes keep the loads and stores of a field nearly
-// line-aligned (one partial 128-byte line per row and field), and the two-stage
-// prefetch ring of the 3D step overlaps them with the rebuilds.
+// line-aligned (one partial 128-byte line per row and field); the moments of two
+// rows are in flight ahead of the rebuild.
 template <class L, int N, class S, int BX, bool W>
 __global__ void __launch_bounds__(BX) k_mstep2(const S* __restrict__ src, S* __restrict__ dst, StepArgs a) {
   using R = S;
@@ -403,7 +388,7 @@ __global__ void __launch_bounds__(BX) k_mstep2(const S* __restrict__ src, S* __r
   // being y0 - 1 + k (k = 0 .. n + 1, n = y1 - y0).  Row k adds its c_y = +1
   // populations to target k (first contribution), c_y = 0 to target k - 1 and
   // c_y = -1 to target k - 2, which is then complete.  Register roles rotate
-  // with period 3 as in the 3D step: moments of row k in buffer k mod 3, sums
+  // with period 3: moments of row k in buffer k mod 3, sums
   // of target j in slot j mod 3, the march unrolled by 3 with no copies.
   const int y0 = blockIdx.y * a.lz;
   const int y1 = (y0 + a.lz < a.ny) ? y0 + a.lz : a.ny;
@@ -441,7 +426,7 @@ __global__ void __launch_bounds__(BX) k_mstep2(const S* __restrict__ src, S* __r
         if (k >= 2) {  // target row py - 1 is complete
           const int sm = wall_side(a.walls, 1, py - 1, a.ny);
           add_row_walls<L, -1, BX, R>(T[P2], pop, tx, sx, sm);
-          if (sx != 0 || sm != 0) finalize_walls<L, R>(T[P2], sx, sm, 0, out);
+          if (sx != 0 || sm != 0) finalize_walls<L, R>(T[P2], sx, sm, out);
           else finalize_state<L, R>(T[P2], rho0, out);
         }
       } else {
@@ -586,7 +571,10 @@ __global__ void __launch_bounds__(256) k_mpopulations(const S* __restrict__ src,
 // at 256^3, order 4, by rows: D3Q27 FP32 5 / 8 / 9 / 11 / 13 rows 52.6 / 56.6 / 54.1 / 56.3 /
 // 58.8, D3Q19 FP32 51.9 / 58.8 / 56.1 / 61.6 / 59.7, D3Q27 FP64 3 / 4 / 5 rows 23.5 / 27.0 /
 // 27.5 (6 rows spill: 12.7), D3Q19 FP64 26.0 / 30.0 / 30.1.  The lower tiles serve boxes whose rows
-// the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).  FP64 boxes
+// the first divides badly, and small ones (64^3 FP32 13 rows 19.3, 8 rows 25.1).  Walled on all
+// axes the 13- and 11-row D3Q27 FP32 forms spill 7 and 5 registers and stay level (us a step, 13 / 11 / 8
+// rows: 256^3 360 / 365 / 367, 200^3 211 / 234 / 236, 128^3 56 / 56 / 53, D3Q19 301 / 304 / 328, 168 / 185 / 196,
+// 48 / 46 / 46).  FP64 boxes
 // whose last 64-column tile would stay half idle take 32 columns by 12 rows in
 // the same eight waves (us a step, D3Q19 273 x 67 x 25 41.8 -> 30.9, 200 x 200 x 32 79.8 -> 52.9;
 // tile_plan weighs the two).

@@ -15,8 +15,8 @@
 // 2 x 1.34 ms, reads 1.55x, 6.0 TB/s.  So it is held by its traffic again, at 0.57 of
 // the traffic of two single steps.
 //
-// FP16 storage keeps single steps: they are near their VALU bound (D3Q19) or
-// would have to round the first step's populations to keep the bits.
+// FP16 storage keeps single steps: they are near their VALU bound (D3Q19 order 4: VALU
+// issuing 86% of the launch), and a pair's rim adds a tenth to the collisions.
 #pragma once
 
 #include <hip/hip_runtime.h>
