@@ -76,7 +76,7 @@ int env_int(const char* name, int none) {
 struct TilePlan {
   int rows = 0, lz = 0;
   double fill = 0.0;   // 3D: nodes updated, of those the chip's compute units take through the launch
-  bool whole = false;  // step pairs: only for runs of a multiple of four steps
+  bool whole = false;  // step pairs: not for a call of five, six or seven steps
 };
 
 // 3D (tile.hpp): a compute unit holds one block, a block's time grows with the
@@ -142,11 +142,11 @@ TilePlan tile_plan(const LatticeOps& ops, int storage, int nx, int ny, int nz, b
 // 39.7 -> 66.7; FP64 1000 13.9 -> 13.8, 64 columns 13.0 -> 15.4), and for rows used to 0.15 of a
 // state that caches no longer hold (64 columns, 20000 rows FP32 67.5 -> 60.8).
 // A state of 2.5 to 8 MB stays in the XCDs' L2 caches, where each finds the rows it wrote.
-// Pairs and single steps share the rows out differently, so single steps for the last of
-// a run cost more there than pairs gain (us, four and six steps: 320^2 FP32 single 13.3
-// and 20.3, pairs 12.9 and 22.7; 256^2 FP64 15.2 and 22.7, 14.7 and 25.3; but 192^2 FP32 14.0 and
-// 20.6, 8.9 and 15.7, 512^2 22.2 and 33.3, 16.1 and 31.0): runs that are no multiple of four
-// steps stay single.
+// Pairs and single steps share the rows out differently, so single steps after one pair of
+// pairs cost more there than it gains: calls of five to seven steps stay single (us a call
+// waited for, six steps, single / pairs: 320^2 FP32 31.3 / 34.1, 384^2 33.2 / 36.5, 256^2 FP64
+// 34.3 / 36.4).  Longer calls, and runs between checks, gain by fewer launches (ten steps:
+// 64.5 / 48.4, 65.0 / 51.4, 69.7 / 50.9; 27 steps checked every seven 293 / 178, 301 / 189, 309 / 195).
 //
 // 3D (GLUPS, order 4, single steps -> pairs), cubes of side n:
 //            n = 256         320         200         128          64
@@ -689,6 +689,7 @@ int lb_step(lb_handle h, long long n) {
   StepArgs ap = a;
   TilePlan pairs;
   if (n >= 4 && !h->moment() && !h->closure_on) pairs = pair_plan(*h->ops, h->storage, a, h->walls);
+  if (pairs.whole && n > 4 && n < 8 && h->check_every == 0) pairs = TilePlan();
   ap.rows = pairs.rows;
   ap.lz = pairs.lz;
   ap.walls = h->walls;
@@ -696,7 +697,7 @@ int lb_step(lb_handle h, long long n) {
     long long run = n;  // steps up to the end of the call or the next check
     if (h->check_every > 0) run = std::min(run, h->check_every - h->steps % h->check_every);
     n -= run;
-    long long paired = pairs.lz > 0 && !(pairs.whole && run % 4) ? run / 4 * 2 : 0;  // launches of two steps
+    long long paired = pairs.lz > 0 ? run / 4 * 2 : 0;  // launches of two steps
     for (run -= 2 * paired; paired > 0 || run > 0;) {
       const int steps = paired > 0 ? 2 : 1;
       const void* src = h->buf[h->cur];

@@ -202,12 +202,13 @@ report([code, [[n, fake.fake_grid(i)[0]] for i, n in enumerate(names) if "k_step
 @pytest.mark.parametrize("storage,side,check,steps,launched", [
     # launches of two steps and of one
     ("fp32", 192, 0, 6, (2, 2)), ("fp32", 320, 0, 6, (0, 6)), ("fp32", 320, 0, 8, (4, 0)), ("fp32", 320, 4, 10, (4, 2)),
-    ("fp32", 320, 6, 14, (0, 14)), ("fp64", 256, 0, 5, (0, 5)), ("fp64", 256, 0, 12, (6, 0)), ("fp64", 512, 0, 7, (2, 3)),
+    ("fp32", 320, 0, 10, (4, 2)), ("fp32", 320, 7, 27, (8, 11)), ("fp32", 320, 6, 7, (2, 3)), ("fp64", 256, 0, 5, (0, 5)),
+    ("fp64", 256, 0, 7, (0, 7)), ("fp64", 256, 0, 4, (2, 0)), ("fp64", 256, 0, 12, (6, 0)), ("fp64", 512, 0, 7, (2, 3)),
     ("fp32", 512, 5, 13, (4, 5)), ("fp32", 64, 1, 9, (0, 9)), ("fp32", 64, 0, 3, (0, 3)),
 ])
 def test_steps_left_over_by_pairs(child, storage, side, check, steps, launched):
-    """Where the caches of the XCDs hold a 2D state, a run (to the end of the call or the next check) that pairs do
-    not divide takes single steps throughout."""
+    """Pairs two at a time up to the end of the call or the next check, then single steps; calls of five to seven
+    steps stay single where the caches of the XCDs hold a 2D state."""
     code, names = child(f"""
 h = handle("D2Q9", {side}, {side}, 1, {storage!r})
 P.check(P.lb_set_check_interval(h, {check}))
